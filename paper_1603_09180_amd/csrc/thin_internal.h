@@ -58,15 +58,29 @@ struct WorkList {
 //   flags: bit 0 destructible, bit 1 peak and bit 2 end point (skeleton
 //          tables only), bits 4..6 T--, bits 8..10 T+
 //   comps: byte c = ring mask of the c-th counted lower component
-struct alignas(8) TopoEntry {  // 8-byte aligned: one 64-bit load per lookup
+struct alignas(8) TopoEntry {
     uint32_t flags;
     uint32_t comps;
 };
 
-// Host-side generation of the 256 entries of one (adjacency, operator) table;
-// the device holds 4 x 256 entries, table index adjacency + 2 * operator.
+// Host-side generation of the 256 entries of one (adjacency, operator) table,
+// table index adjacency + 2 * operator.
 constexpr int kTables = 4;
 void build_topology_table(int adjacency, int op, TopoEntry out[256]);
+
+// The same table as the kernels read it (the device holds 4 x 256 entries):
+// indexed by the lower-neighbour mask in the bit order the packed decision
+// produces (NW, SW, NE, W, N, S, SE, E from bit 0 on).
+//   need:  bits 0..7 how many counted lower components must hold a pixel
+//          within lambda of the centre (0: lower whatever their contrast; 8:
+//          never), bit 31 set when the centre's own contrast must be within
+//          lambda too (skeleton tables: peaks and end points)
+//   comps: byte c = mask of the c-th counted lower component, same bit order
+struct alignas(8) DecEntry {  // one 64-bit load per lookup
+    uint32_t need;
+    uint32_t comps;
+};
+void build_decision_table(int adjacency, int op, DecEntry out[256]);
 
 // Residency variants.  kVarFlags keeps the tile in LDS with a re-examination
 // flag byte per pixel, every thread checking fixed cells each step;
@@ -74,15 +88,22 @@ void build_topology_table(int adjacency, int op, TopoEntry out[256]);
 // bitmaps; kVarRegs keeps each thread's 4x4 windows in registers;
 // kVarBits keeps the flags as one bit per candidate and class and gathers
 // each step's flagged candidates into a dense list; kVarBitsSeeded adds the
-// previous round's change bitmaps to kVarBits.
-constexpr int kVarFlags = 0, kVarSeeded = 1, kVarRegs = 2, kVarBits = 3, kVarBitsSeeded = 4;
+// previous round's change bitmaps to kVarBits, kVarRegsSeeded to kVarRegs.
+constexpr int kVarFlags = 0, kVarSeeded = 1, kVarRegs = 2, kVarBits = 3, kVarBitsSeeded = 4,
+              kVarRegsSeeded = 5;
 
 // Variants that read and write per-tile change bitmaps between rounds.
-constexpr bool var_seeded(int v) { return v == kVarSeeded || v == kVarBitsSeeded; }
+constexpr bool var_seeded(int v)
+{
+    return v == kVarSeeded || v == kVarBitsSeeded || v == kVarRegsSeeded;
+}
 // The same variant without history (for callers that keep none).
 constexpr int var_unseeded(int v)
 {
-    return v == kVarSeeded ? kVarFlags : (v == kVarBitsSeeded ? kVarBits : v);
+    return v == kVarSeeded       ? kVarFlags
+           : v == kVarBitsSeeded ? kVarBits
+           : v == kVarRegsSeeded ? kVarRegs
+                                 : v;
 }
 
 // Tiled engine geometry chosen at run time among the compiled variants.
@@ -109,19 +130,19 @@ constexpr int kOnlyU16 = 8;      // visit only u16 images
 // A grid of as many blocks as fit on num_cus CUs loops over the tiles.
 hipError_t launch_round(hipStream_t stream, TileShape shape, const ImgDev* imgs, ImgCnt* cnt,
                         const int32_t* tile_img, int32_t* tile_last, int ntiles, int round,
-                        const TopoEntry* lut, int num_cus, uint32_t* hist_bits,
+                        const DecEntry* lut, int num_cus, uint32_t* hist_bits,
                         int32_t* hist_round, WorkList wl, const int32_t* round_base, int kflags);
 // *round_base += n (the last node of a chunk graph).
 hipError_t launch_advance(hipStream_t stream, int32_t* round_base, int n);
 // Words of one tile's change bitmap (two copies of ntiles bitmaps are needed).
 int history_words(TileShape s);
 hipError_t launch_step(hipStream_t stream, const ImgDev* img_host, const ImgDev* img_dev,
-                       ImgCnt* cnt, int step, const TopoEntry* lut);
+                       ImgCnt* cnt, int step, const DecEntry* lut);
 // Cooperative engine: every round in one launch, grid-wide barriers between
 // rounds.  active: 3 zeroed counters; rounds_out receives the rounds run.
 hipError_t launch_coop(hipStream_t stream, TileShape shape, const ImgDev* imgs, ImgCnt* cnt,
                        const int32_t* tile_img, int32_t* tile_last, int ntiles,
-                       const TopoEntry* lut, int32_t* active, int32_t* rounds_out,
+                       const DecEntry* lut, int32_t* active, int32_t* rounds_out,
                        int max_rounds, int num_cus, uint32_t* hist_bits, int32_t* hist_round,
                        int kflags);
 bool tile_shape_supported(TileShape s);
@@ -171,7 +192,7 @@ inline int64_t wl_bitmap_words(int64_t h, int64_t w)
 // last step image i ran.  gbits selects the variant with the pending bitmaps
 // in global memory (every image of the launch must have gbits set then).
 hipError_t launch_worklist(hipStream_t stream, const WlImg* imgs, int nimg, int dtype,
-                           bool gbits, ImgCnt* cnt, const TopoEntry* lut, int32_t* steps_out);
+                           bool gbits, ImgCnt* cnt, const DecEntry* lut, int32_t* steps_out);
 
 // Writes descriptor d to *dst on `stream` (a kernel argument, so no host
 // buffer has to outlive the call).

@@ -48,107 +48,124 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int STAGE_CHUNK = 8;  // global loads in flight per thread while staging a tile
 
-// Upper-neighbour mask of a candidate of value v: bit p set when ring
-// neighbour p (order E, NE, N, NW, W, SW, S, SE) has a value >= v.
-__device__ __forceinline__ uint32_t upper_mask(uint32_t v, const uint32_t (&nb)[8])
+// ---------------------------------------------------------------- decision
+//
+// The decision is VALU-bound wherever whole waves examine candidates, so it
+// works on the ring in pairs: four registers of two 16-bit neighbours, one
+// with the centre twice.  d = saturating centre - neighbour is nonzero
+// exactly for the lower neighbours (L), d - lambda for those out of lambda's
+// reach, and the least d - 1 over L (a zero d wraps to the top) is the
+// contrast less one.  Each mask costs a packed minimum with 1, three
+// shift-ors and one dot product that places both halves.
+
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ u16x2 as_pair(uint32_t x) { return __builtin_bit_cast(u16x2, x); }
+__device__ __forceinline__ uint32_t as_word(u16x2 x) { return __builtin_bit_cast(uint32_t, x); }
+
+// (1, 1), hidden from the optimiser: it would turn the packed minimum with a
+// known 1 into two compares and selects.
+__device__ __forceinline__ u16x2 pair_of_ones()
 {
-    uint32_t u = 0;
-#pragma unroll
-    for (int p = 0; p < 8; ++p) u |= (uint32_t)(nb[p] >= v) << p;
-    return u;
+    uint32_t one = 0x00010001u;
+    asm("" : "+s"(one));
+    return as_pair(one);
 }
 
-// Decision and new value for one candidate with upper mask u and its table
-// entry e = lut[u] (the entries of the image's adjacency and operator).
-__device__ __forceinline__ bool decide_entry_branchy(uint32_t v, const uint32_t (&nb)[8],
-                                                     uint32_t u, TopoEntry e, uint32_t lambda,
-                                                     uint32_t& alpha)
+// lambda as the decision takes it: contrasts are at most 65535.
+struct Lambda {
+    uint32_t one;   // min(lambda, 65535)
+    u16x2 two;      // the same in both halves
+};
+__device__ __forceinline__ Lambda lambda_of(uint32_t lambda)
 {
-    bool lower = (e.flags & 1u) != 0u;
-    const uint32_t k = (e.flags >> 4) & 7u;  // T--
-    if (!lower && lambda != 0u && k >= 2u) {
-        // lower neighbours y with v - F(y) <= lambda, i.e. F(y) >= v - lambda
-        const uint32_t floor_v = v > lambda ? v - lambda : 0u;
-        uint32_t q = 0;
-#pragma unroll
-        for (int p = 0; p < 8; ++p) q |= (uint32_t)(nb[p] >= floor_v) << p;
-        q &= ~u;
-        const uint32_t hit = e.comps & (q * 0x01010101u);
-        const uint32_t nonzero = (((hit & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | hit) & 0x80808080u;
-        lower = (uint32_t)__popc(nonzero) + 1u >= k;
-    }
-    // Skeleton tables mark peaks (bit 1) and end points (bit 2); leveling
-    // tables mark neither.  A peak is lowered when its contrast v - alpha- is
-    // at most lambda; an end point that passed the test above is kept when
-    // its contrast exceeds lambda (a lambda-end point).
-    const uint32_t pe = e.flags & 6u;
-    if (lower || pe != 0u) {
-        // max over L: the eight masked values are independent, the maxima
-        // form a tree of depth three
-        uint32_t m[8];
-#pragma unroll
-        for (int p = 0; p < 8; ++p) m[p] = ((u >> p) & 1u) ? 0u : nb[p];
-        const uint32_t a = max(max(max(m[0], m[1]), max(m[2], m[3])),
-                               max(max(m[4], m[5]), max(m[6], m[7])));
-        alpha = a;
-        if (pe != 0u) lower = (lower || pe == 2u) && v - a <= lambda;
-    }
-    return lower;
+    Lambda l;
+    l.one = lambda < 65535u ? lambda : 65535u;
+    l.two = as_pair(l.one * 0x00010001u);
+    return l;
 }
 
-// The same decision in straight-line form.
-__device__ __forceinline__ bool decide_entry_straight(uint32_t v, const uint32_t (&nb)[8],
-                                                      uint32_t u, TopoEntry e, uint32_t lambda,
-                                                      uint32_t& alpha)
+// The ring around a candidate: p0 = (NW, N), p1 = (SW, S), p2 = (NE, SE),
+// p3 = (W, E), first in the low half; v = the candidate in both halves.
+struct Ring {
+    u16x2 p0, p1, p2, p3, v;
+};
+
+// From the 16-bit neighbours E, NE, N, NW, W, SW, S, SE.
+__device__ __forceinline__ Ring ring_of(uint32_t v, const uint32_t (&nb)[8])
 {
-    // Straight-line form: every term is computed and selected (inside a
-    // wave both sides of a data-dependent branch usually run anyway).
-    const uint32_t k = (e.flags >> 4) & 7u;  // T--
-    // lower neighbours y with v - F(y) <= lambda, i.e. F(y) >= v - lambda
-    const uint32_t floor_v = v > lambda ? v - lambda : 0u;
-    uint32_t q = 0;
-#pragma unroll
-    for (int p = 0; p < 8; ++p) q |= (uint32_t)(nb[p] >= floor_v) << p;
-    q &= ~u;
-    const uint32_t hit = e.comps & (q * 0x01010101u);
+    return Ring{as_pair(nb[3] | nb[2] << 16), as_pair(nb[5] | nb[6] << 16),
+                as_pair(nb[1] | nb[7] << 16), as_pair(nb[4] | nb[0] << 16),
+                as_pair(v * 0x00010001u)};
+}
+
+// From three rows of bytes (W, centre, E in the low three bytes).
+__device__ __forceinline__ Ring ring_of_bytes(uint32_t up, uint32_t mid, uint32_t down)
+{
+    return Ring{as_pair(__builtin_amdgcn_perm(0u, up, 0x0C010C00u)),
+                as_pair(__builtin_amdgcn_perm(0u, down, 0x0C010C00u)),
+                as_pair(__builtin_amdgcn_perm(down, up, 0x0C060C02u)),
+                as_pair(__builtin_amdgcn_perm(0u, mid, 0x0C020C00u)),
+                as_pair(__builtin_amdgcn_perm(0u, mid, 0x0C010C01u))};
+}
+
+// From three rows of four 16-bit pixels (two words each), the candidate in
+// column 1 (RIGHT = false) or 2 (RIGHT = true).
+template <bool RIGHT>
+__device__ __forceinline__ Ring ring_of_words(uint32_t u0, uint32_t u1, uint32_t m0, uint32_t m1,
+                                              uint32_t d0, uint32_t d1)
+{
+    constexpr uint32_t straddle = 0x05040302u;  // high half of word 0, low half of word 1
+    if constexpr (!RIGHT)
+        return Ring{as_pair(u0), as_pair(d0), as_pair(__builtin_amdgcn_perm(d1, u1, 0x05040100u)),
+                    as_pair(__builtin_amdgcn_perm(m1, m0, 0x05040100u)),
+                    as_pair(__builtin_amdgcn_perm(0u, m0, 0x03020302u))};
+    else
+        return Ring{as_pair(__builtin_amdgcn_perm(u1, u0, straddle)),
+                    as_pair(__builtin_amdgcn_perm(d1, d0, straddle)),
+                    as_pair(__builtin_amdgcn_perm(d1, u1, 0x07060302u)),
+                    as_pair(__builtin_amdgcn_perm(m1, m0, 0x07060302u)),
+                    as_pair(__builtin_amdgcn_perm(0u, m1, 0x01000100u))};
+}
+
+// (x of p0..p3 in the low halves, then in the high halves) as a byte, times scale.
+__device__ __forceinline__ uint32_t mask_of(u16x2 b0, u16x2 b1, u16x2 b2, u16x2 b3,
+                                            unsigned short scale)
+{
+    const uint32_t m = as_word(b0) | as_word(b1) << 1 | as_word(b2) << 2 | as_word(b3) << 3;
+    const u16x2 w = {scale, (unsigned short)(16 * scale)};
+    return __builtin_amdgcn_udot2(as_pair(m), w, 0u, false);
+}
+
+// Whether the candidate is lowered, and its new value alpha- when it is (the
+// decision table's fields: see DecEntry).  lut points at the 256 entries of
+// the image's adjacency and operator.
+__device__ __forceinline__ bool decide(const Ring& q, const DecEntry* lut, const Lambda& lam,
+                                       uint32_t& alpha)
+{
+    const u16x2 one = pair_of_ones();
+    const u16x2 d0 = __builtin_elementwise_sub_sat(q.v, q.p0);
+    const u16x2 d1 = __builtin_elementwise_sub_sat(q.v, q.p1);
+    const u16x2 d2 = __builtin_elementwise_sub_sat(q.v, q.p2);
+    const u16x2 d3 = __builtin_elementwise_sub_sat(q.v, q.p3);
+    const uint32_t at = mask_of(__builtin_elementwise_min(d0, one), __builtin_elementwise_min(d1, one),
+                                __builtin_elementwise_min(d2, one), __builtin_elementwise_min(d3, one),
+                                sizeof(DecEntry));
+    const uint64_t raw = *reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(lut) + at);
+    const uint32_t need = (uint32_t)raw, comps = (uint32_t)(raw >> 32);
+    auto beyond = [&](u16x2 d) __attribute__((always_inline)) {
+        return __builtin_elementwise_min(__builtin_elementwise_sub_sat(d, lam.two), one);
+    };
+    const uint32_t far = mask_of(beyond(d0), beyond(d1), beyond(d2), beyond(d3), 1);
+    const u16x2 c = __builtin_elementwise_min(__builtin_elementwise_min(d0 - one, d1 - one),
+                                              __builtin_elementwise_min(d2 - one, d3 - one));
+    const uint32_t contrast1 = min(as_word(c) & 0xFFFFu, as_word(c) >> 16);  // v - alpha- - 1
+    // counted components that hold a pixel within lambda's reach
+    const uint32_t hit = comps & ~__builtin_amdgcn_perm(0u, far, 0u);
     const uint32_t nonzero = (((hit & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | hit) & 0x80808080u;
-    const bool divergent_ok = lambda != 0u && k >= 2u && (uint32_t)__popc(nonzero) + 1u >= k;
-    bool lower = (e.flags & 1u) != 0u || divergent_ok;
-    // max over L: the eight masked values are independent, the maxima form
-    // a tree of depth three
-    uint32_t m[8];
-#pragma unroll
-    for (int p = 0; p < 8; ++p) m[p] = ((u >> p) & 1u) ? 0u : nb[p];
-    const uint32_t a = max(max(max(m[0], m[1]), max(m[2], m[3])),
-                           max(max(m[4], m[5]), max(m[6], m[7])));
-    // Skeleton tables mark peaks (bit 1) and end points (bit 2); leveling
-    // tables mark neither.  A peak is lowered when its contrast v - alpha- is
-    // at most lambda; an end point that passed the test above is kept when
-    // its contrast exceeds lambda (a lambda-end point).
-    const uint32_t pe = e.flags & 6u;
-    const bool small = v - a <= lambda;
-    lower = pe == 0u ? lower : ((lower || pe == 2u) && small);
-    alpha = a;
-    return lower;
-}
-
-// Decision and new value for one candidate; nb in ring order E, NE, N, NW,
-// W, SW, S, SE.  lut points at the 256 entries of the image's adjacency and
-// operator.  STRAIGHT selects the straight-line form (measured faster where
-// whole waves examine candidates together: the register-window and bit-flag
-// residencies) over the branching one (faster for the flag residencies).
-template <bool STRAIGHT>
-__device__ __forceinline__ bool decide(uint32_t v, const uint32_t (&nb)[8], const TopoEntry* lut,
-                                       uint32_t lambda, uint32_t& alpha)
-{
-    const uint32_t u = upper_mask(v, nb);
-    // both words in one 64-bit load, so the lambda test waits for no second read
-    const uint64_t raw = reinterpret_cast<const uint64_t*>(lut)[u];
-    TopoEntry e;
-    e.flags = (uint32_t)raw;
-    e.comps = (uint32_t)(raw >> 32);
-    return STRAIGHT ? decide_entry_straight(v, nb, u, e, lambda, alpha)
-                    : decide_entry_branchy(v, nb, u, e, lambda, alpha);
+    alpha = (as_word(q.v) & 0xFFFFu) - 1u - contrast1;
+    return (uint32_t)__popc(nonzero) >= (need & 0xFFu) &&
+           ((int32_t)need >= 0 || contrast1 < lam.one);
 }
 
 __device__ __forceinline__ uint32_t load_px(const void* base, int dtype, int64_t idx)
@@ -199,9 +216,9 @@ __global__ void k_advance(int32_t* round_base, int n)
 
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_step(const ImgDev* __restrict__ img, ImgCnt* cnt,
-                                                   int step, const TopoEntry* __restrict__ lut_g)
+                                                   int step, const DecEntry* __restrict__ lut_g)
 {
-    __shared__ TopoEntry s_lut[256];
+    __shared__ DecEntry s_lut[256];
     const ImgDev d = *img;
     for (int i = threadIdx.x; i < 256; i += kThreads) s_lut[i] = lut_g[d.adj * 256 + i];
     __syncthreads();
@@ -217,7 +234,7 @@ __global__ __launch_bounds__(kThreads) void k_step(const ImgDev* __restrict__ im
         const uint32_t nb[8] = {px[1], px[-P + 1], px[-P], px[-P - 1],
                                 px[-1], px[P - 1], px[P], px[P + 1]};
         uint32_t alpha;
-        if (decide<false>(v, nb, s_lut, d.lambda, alpha)) {
+        if (decide(ring_of(v, nb), s_lut, lambda_of(d.lambda), alpha)) {
             px[0] = (T)alpha;
             lowered = true;
         }
@@ -576,6 +593,40 @@ __device__ __forceinline__ uint32_t history_word_t(const Seed* sd, int gi, int a
     return sd->prev_round[n] == sd->r - 1 ? bits : 0u;
 }
 
+// Inclusive prefix sum over the 64 lanes of a wave with DPP moves: shifts by
+// 1, 2, 4 and 8 lanes within each row of 16, then the last lane of row 0 and
+// of row 2 broadcast into the next row, then lane 31 into rows 2 and 3.
+// Lanes a move cannot reach add the 0 kept in `old`.
+__device__ __forceinline__ int wave_inclusive_sum(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return v;
+}
+
+// The block's totals of the lanes' counts, one LDS atomic per wave and total
+// (per-lane atomics on one address cost microseconds at the end of a
+// residency).
+__device__ __forceinline__ void block_counts(int count, int last, int exams, int* s_count,
+                                             int* s_last, int* s_exam, int tid)
+{
+    const int c = wave_inclusive_sum(count), e = wave_inclusive_sum(exams);
+    int l = last;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) l = max(l, __shfl_xor(l, o));
+    if ((tid & 63) == 63) {
+        if (c) {
+            atomicAdd(s_count, c);
+            atomicMax(s_last, l);
+        }
+        if (e) atomicAdd(s_exam, e);
+    }
+}
+
 // Geometry of a tile residency: a TH x TW interior plus a K-pixel halo,
 // staged in LDS as u16, processed by NT threads.
 template <int TH, int TW, int K, int NT, bool SEED>
@@ -648,7 +699,7 @@ struct Tile {
     static __device__ __forceinline__ int run(const View d, int gy0, int gx0, int t0, int nsteps,
                               const void* src, void* dst, uint16_t* s_img, uint8_t* s_dirty,
                               uint32_t* s_bits, uint32_t* s_cw, const Seed* sd,
-                              const TopoEntry* lut, int* s_count, int* s_last, int* s_exam,
+                              const DecEntry* lut, int* s_count, int* s_last, int* s_exam,
                               int tid, int& last_tau)
     {
         const int ry0 = gy0 - K, rx0 = gx0 - K;
@@ -703,7 +754,7 @@ struct Tile {
             __syncthreads();
         }
 
-        const uint32_t lambda = d.lambda;
+        const Lambda lambda = lambda_of(d.lambda);
         int my_count = 0, my_last = -1;  // interior lowerings, last step with one
         int my_exams = 0;                // candidates characterised
         // Each thread owns fixed positions of the candidate lattice (one in
@@ -735,7 +786,7 @@ struct Tile {
                     const uint32_t nbv[8] = {p[1], p[-RWP + 1], p[-RWP], p[-RWP - 1],
                                              p[-1], p[RWP - 1], p[RWP], p[RWP + 1]};
                     uint32_t alpha;
-                    if (decide<false>(v, nbv, lut, lambda, alpha)) {
+                    if (decide(ring_of(v, nbv), lut, lambda, alpha)) {
                         p[0] = (uint16_t)alpha;
                         uint8_t* q = s_dirty + o;
                         q[-RWP - 1] = 1; q[-RWP] = 1; q[-RWP + 1] = 1;
@@ -759,11 +810,7 @@ struct Tile {
         }
 
         store(d, gy0, gx0, src, dst, s_img, tid);
-        if (my_count) {
-            atomicAdd(s_count, my_count);
-            atomicMax(s_last, my_last);
-        }
-        if (my_exams) atomicAdd(s_exam, my_exams);
+        block_counts(my_count, my_last, my_exams, s_count, s_last, s_exam, tid);
         __syncthreads();
         if constexpr (SEED) {
             if (sd != nullptr) {
@@ -780,32 +827,44 @@ struct Tile {
 // Residency with register windows.  Each thread owns fixed cells of the 2x2
 // lattice of the region and keeps, per cell, the 4x4 window of pixels covered
 // by the 3x3 neighbourhoods of the cell's four candidates (one per parity
-// class).  A parity step changes only pixels of its class, which occupy four
-// window positions, one of them the cell's own candidate; so before each
-// step a thread re-reads from LDS the three positions of the previous step's
-// class that belong to other cells.  A candidate is examined only when a
-// pixel of its 3x3 changed since it was last examined (one bit per class and
-// cell, set by re-read values that differ and by the cell's own lowerings):
-// the re-examination rule of section 2.2, as in the flag variant.  LDS holds
-// the whole region as the exchange medium between cells and as the source of
-// the final interior store.
-template <int TH, int TW, int K, int NT>
+// class), two pixels to a register.  A parity step changes only pixels of its
+// class, which occupy four window positions, one of them the cell's own
+// candidate; so before each step a thread re-reads from LDS the three
+// positions of the previous step's class that belong to other cells.  A
+// candidate is examined only when a pixel of its 3x3 changed since it was
+// last examined (set by re-read values that differ and by the cell's own
+// lowerings): the re-examination rule of section 2.2, as in the flag variant.
+// LDS holds the whole region as the exchange medium between cells and as the
+// source of the final interior store.
+//
+// A step is a chain of dependent latencies (window read, decision, table
+// read, barrier), so everything beside it is scalar: the pending candidates
+// of a wave's cells are one 64-bit mask per class in scalar registers,
+// updated with the compare results themselves, and a wave without an active
+// candidate branches past the decision; counts are population counts of the
+// same masks.  With SEED the masks start from the previous round's change
+// bitmaps (else every candidate starts pending), so that a quiet wave is
+// quiet from the first step on.
+template <int TH, int TW, int K, int NT, bool SEED>
 struct RTile {
     using Elem = uint16_t;
     static constexpr int RH = TH + 2 * K;
     static constexpr int RW = TW + 2 * K;
     static constexpr int RWP = RW + 2;                // a spare column on each side
     static constexpr int IMG_ELEMS = (RH + 2) * RWP;  // a spare row above and below
-    static constexpr int DIRTY_ELEMS = 1;
+    static constexpr int DIRTY_ELEMS = 4 * ((K + 3) / 4);  // "lowered" flag of each step
     static constexpr int LAT_H = RH / 2, LAT_W = RW / 2;
     static constexpr int PPT = (LAT_H * LAT_W + NT - 1) / NT;  // lattice cells per thread
-    static constexpr int WPR = 1, BITS_WORDS = 1, CW_WORDS = 1;
+    static constexpr int WPR = TW >= 32 ? TW / 32 : 1;
+    static constexpr int RWW = (RW + 31) / 32;
+    static constexpr int BITS_WORDS = SEED ? TH * WPR : 1;
+    static constexpr int CW_WORDS = SEED ? RH * (RWW + 1) : 1;  // a zero word ends each row
     static_assert(K % 4 == 0, "a residency must start at parity class 0");
     static_assert(K <= TH && K <= TW, "halo must not exceed the tile side");
     static_assert(TH % 2 == 0 && TW % 2 == 0, "tile sides must be even");
-
-    // LDS index of region pixel (y, x), y in [-1, RH], x in [-1, RW].
-    static __device__ __forceinline__ int at(int y, int x) { return (y + 1) * RWP + x + 1; }
+    static_assert(RH / 2 <= 254 && RW / 2 <= 254, "step limits are bytes");
+    static_assert(!SEED || TW % 32 == 0, "history bitmaps need a tile width multiple of 32");
+    static_assert(!SEED || 2 * K <= TH, "history seeding needs the region inside the 3x3 tile block");
 
     // Classes whose candidate's 3x3 contains window position (i, j); the
     // candidate of class (ci, cj) sits at (1 + ci, 1 + cj).
@@ -818,16 +877,36 @@ struct RTile {
         return m;
     }
 
+    // What a residency can start before the block knows whether the tile
+    // runs: the step flags and, when seeded, the previous round's change map
+    // of the region (read by none of the previous tile's tail).
+    static __device__ __forceinline__ void prefetch(const View& d, int gy0, int gx0, const Seed* sd,
+                                                    uint8_t* s_flags, uint32_t* s_cw, int tid)
+    {
+        if (tid < DIRTY_ELEMS / 4) reinterpret_cast<uint32_t*>(s_flags)[tid] = 0u;
+        if constexpr (SEED) {
+            if (sd != nullptr && sd->r > 0) {
+                const int ry0 = gy0 - K, rx0 = gx0 - K;
+                for (int it = tid; it < RH * (RWW + 1); it += NT) {
+                    const int y = it / (RWW + 1), j = it - y * (RWW + 1);
+                    const int gi = ry0 + y;
+                    uint32_t word = 0u;
+                    if (j < RWW && gi >= 0 && gi < d.h) {
+                        const int c0 = rx0 + 32 * j;
+                        const int a = (c0 >= 0) ? (c0 >> 5) : -((31 - c0) >> 5);
+                        const int sh = c0 - 32 * a;
+                        const uint32_t lo = history_word_t<TH, TW>(sd, gi, a);
+                        const uint32_t hi = history_word_t<TH, TW>(sd, gi, a + 1);
+                        word = sh ? ((lo >> sh) | (hi << (32 - sh))) : lo;
+                    }
+                    s_cw[it] = word;
+                }
+            }
+        }
+    }
 
     // Tile and halo from src into s_img, spare rows and columns zeroed (they
     // are read into windows but never used by a candidate); no barrier.
-    // Work a residency can start before the block knows whether the tile
-    // runs (none for this type).
-    static __device__ __forceinline__ void prefetch(const View&, int, int, const Seed*, uint8_t*,
-                                                    uint32_t*, int)
-    {
-    }
-
     static __device__ __forceinline__ void stage(const View& d, int gy0, int gx0, const void* src,
                                                  const void*, uint16_t* s_img, int tid)
     {
@@ -849,157 +928,203 @@ struct RTile {
     }
 
     struct Cells {
-        uint32_t win[PPT][16];  // 4x4 windows, row-major
-        int base[PPT];          // LDS index of window position (0, 0)
-        int cr[PPT], cc[PPT];   // region position of the cell's (0,0) candidate
-        uint32_t pend[PPT];     // bit c: the class-c candidate needs examining
+        uint32_t win[PPT][8];   // 4x4 windows, rows of two words
+        int base[PPT];          // LDS word of window position (0, 0)
+        uint32_t last[PPT];     // byte c: 1 + the last step the class-c candidate may run in
+        uint64_t pend[PPT][4];  // lanes whose class-c candidate needs examining
+        uint64_t inside[PPT];   // lanes whose cell is in the tile's interior
+    };
+    struct Counts {
+        int lowered = 0, exams = 0, last = -1;  // of the wave
     };
 
     // One parity step of class C (steps of a residency start at class 0).
     template <int C>
-    static __device__ __forceinline__ void step(Cells& q, uint16_t* s_img, int tau, int r_lo,
-                                                int r_hi, int c_lo, int c_hi,
-                                                const TopoEntry* lut, uint32_t lambda,
-                                                int& my_count, int& my_exams, bool& inner)
+    static __device__ __forceinline__ void step(Cells& q, uint16_t* s_img, uint8_t* s_flags,
+                                                uint32_t* s_bits, int tau, int nsteps, int tid,
+                                                const DecEntry* lut, const Lambda& lambda,
+                                                Counts& n)
     {
         constexpr int si = C >> 1, sj = C & 1;
         constexpr int P = (C + 3) & 3, pi = P >> 1, pj = P & 1;
+        const uint32_t* words = reinterpret_cast<const uint32_t*>(s_img);
         if (tau > 0) {
-            // Window rows of class-P pixels are 1 - pi and 3 - pi, columns
-            // 1 - pj and 3 - pj; (1 + pi, 1 + pj) is the cell's own.
+            // Window rows of class-P pixels are 1 - pi and 3 - pi; their
+            // columns 1 - pj and 3 - pj are one half of each row's two words
+            // (the other half may be changing in this very step, and is
+            // read with its own class).  (1 + pi, 1 + pj) is the cell's own.
+            constexpr uint32_t half = pj ? 0x0000FFFFu : 0xFFFF0000u;
 #pragma unroll
             for (int k = 0; k < PPT; ++k) {
+                uint32_t got[4];
 #pragma unroll
-                for (int di = 0; di < 2; ++di) {
+                for (int e = 0; e < 4; ++e) {
+                    const int i = 1 - pi + 2 * (e >> 1), w = e & 1;
+                    if (e != 2 * pi + pj) got[e] = words[q.base[k] + i * (RWP / 2) + w];
+                }
 #pragma unroll
-                    for (int dj = 0; dj < 2; ++dj) {
-                        if (di == pi && dj == pj) continue;
-                        const int i = 1 - pi + 2 * di, j = 1 - pj + 2 * dj;
-                        const uint32_t nv = s_img[q.base[k] + i * RWP + j];
-                        if (nv != q.win[k][4 * i + j]) {
-                            q.win[k][4 * i + j] = nv;
-                            q.pend[k] |= affect(i, j);
-                        }
+                for (int e = 0; e < 4; ++e) {
+                    if (e == 2 * pi + pj) continue;
+                    const int i = 1 - pi + 2 * (e >> 1), w = e & 1;
+                    const uint32_t was = q.win[k][2 * i + w];
+                    const uint32_t now = (got[e] & half) | (was & ~half);
+                    const uint64_t changed = __ballot(now != was);
+                    q.win[k][2 * i + w] = now;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (affect(i, 2 * w + 1 - pj) >> c & 1u) q.pend[k][c] |= changed;
+                }
+            }
+        }
+        constexpr int ci = 1 + si;
+        uint64_t any = 0;
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+            const uint64_t act = q.pend[k][C] & __ballot((int)(q.last[k] >> (8 * C) & 0xFFu) > tau);
+            if (act == 0) continue;
+            n.exams += __popcll(act);
+            q.pend[k][C] &= ~act;
+            uint32_t(&w)[8] = q.win[k];
+            uint32_t alpha;
+            const bool yes =
+                decide(ring_of_words<sj != 0>(w[2 * ci - 2], w[2 * ci - 1], w[2 * ci], w[2 * ci + 1],
+                                              w[2 * ci + 2], w[2 * ci + 3]),
+                       lut, lambda, alpha);
+            const uint64_t low = act & __ballot(yes);
+            if (low == 0) continue;
+            any |= low;
+            const bool mine = __builtin_amdgcn_inverse_ballot_w64(low);
+            const uint32_t own = w[2 * ci + sj];
+            const uint32_t put = sj ? ((own & 0xFFFF0000u) | alpha) : ((own & 0xFFFFu) | alpha << 16);
+            w[2 * ci + sj] = mine ? put : own;
+            if (mine) s_img[2 * q.base[k] + ci * RWP + 1 + sj] = (uint16_t)alpha;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) q.pend[k][c] |= low;
+            const uint64_t in = low & q.inside[k];
+            if (in != 0) {
+                n.lowered += __popcll(in);
+                n.last = tau;
+                if constexpr (SEED) {
+                    if (tau >= nsteps - 4 && __builtin_amdgcn_inverse_ballot_w64(in)) {
+                        const int idx = tid + k * NT, a = idx / LAT_W, b = idx - a * LAT_W;
+                        const int y = 2 * a + si - K, x = 2 * b + sj - K;
+                        atomicOr(&s_bits[y * WPR + (x >> 5)], 1u << (x & 31));
                     }
                 }
             }
         }
-        constexpr int ci = 1 + si, cj = 1 + sj;
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const int lr = q.cr[k] + si, lc = q.cc[k] + sj;
-            if (lr < r_lo || lr > r_hi || lc < c_lo || lc > c_hi) continue;
-            if (((q.pend[k] >> C) & 1u) == 0u) continue;
-            q.pend[k] &= ~(1u << C);
-            ++my_exams;
-            uint32_t(&w)[16] = q.win[k];
-            const uint32_t nb[8] = {w[4 * ci + cj + 1],       w[4 * (ci - 1) + cj + 1],
-                                    w[4 * (ci - 1) + cj],     w[4 * (ci - 1) + cj - 1],
-                                    w[4 * ci + cj - 1],       w[4 * (ci + 1) + cj - 1],
-                                    w[4 * (ci + 1) + cj],     w[4 * (ci + 1) + cj + 1]};
-            uint32_t alpha;
-            if (decide<true>(w[4 * ci + cj], nb, lut, lambda, alpha)) {
-                w[4 * ci + cj] = alpha;
-                s_img[q.base[k] + ci * RWP + cj] = (uint16_t)alpha;
-                q.pend[k] = 0xFu;
-                if (lr >= K && lr < K + TH && lc >= K && lc < K + TW) {
-                    ++my_count;
-                    inner = true;
-                }
-            }
-        }
-    }
-
-    template <int C>
-    static __device__ __forceinline__ void full_step(Cells& q, const View& d, int ry0, int rx0,
-                                                     uint16_t* s_img, int tau,
-                                                     const TopoEntry* lut, int& my_last,
-                                                     int& my_count, int& my_exams)
-    {
-        // Exact region after tau steps, clipped to the image interior.
-        const int r_lo = max(tau + 1, 1 - ry0), r_hi = min(RH - 2 - tau, d.h - 2 - ry0);
-        const int c_lo = max(tau + 1, 1 - rx0), c_hi = min(RW - 2 - tau, d.w - 2 - rx0);
-        bool inner = false;
-        step<C>(q, s_img, tau, r_lo, r_hi, c_lo, c_hi, lut, d.lambda, my_count, my_exams, inner);
-        if (inner) my_last = tau;
+        if (any != 0 && (tid & 63) == 0) s_flags[tau] = 1;
         __syncthreads();
     }
 
-    // Same contract as Tile::run (history arguments unused).
+    // Same contract as Tile::run.
     static __device__ __forceinline__ int run(const View d, int gy0, int gx0, int t0, int nsteps,
-                              const void* src, void* dst, uint16_t* s_img, uint8_t*, uint32_t*,
-                              uint32_t*, const Seed*, const TopoEntry* lut, int* s_count,
-                              int* s_last, int* s_exam, int tid, int& last_tau)
+                              const void* src, void* dst, uint16_t* s_img, uint8_t* s_flags,
+                              uint32_t* s_bits, uint32_t* s_cw, const Seed* sd,
+                              const DecEntry* lut, int* s_count, int* s_last, int* s_exam, int tid,
+                              int& last_tau)
     {
         (void)t0;  // a multiple of 4: step tau has class tau mod 4
         const int ry0 = gy0 - K, rx0 = gx0 - K;
+        const bool seeded = SEED && sd != nullptr && sd->r > 0;
         if (tid == 0) {
             *s_count = 0;
             *s_last = -1;
             *s_exam = 0;
         }
-        // The barrier after the windows are read also orders the counter
-        // reset above before the steps' updates.
+        if constexpr (SEED)
+            for (int i = tid; i < TH * WPR; i += NT) s_bits[i] = 0u;
+        // The barrier after the windows are read also orders the resets above
+        // before the steps' updates.
         Cells q;
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
             const int idx = tid + k * NT;
             const bool valid = idx < LAT_H * LAT_W;
             const int a = valid ? idx / LAT_W : 0, b = valid ? idx % LAT_W : 0;
-            q.cr[k] = valid ? 2 * a : RH;  // RH: never in range
-            q.cc[k] = 2 * b;
-            q.base[k] = 2 * a * RWP + 2 * b;  // at(2a - 1, 2b - 1)
-            q.pend[k] = 0xFu;
+            q.base[k] = a * RWP + b;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const uint32_t* row = reinterpret_cast<const uint32_t*>(s_img + q.base[k] + i * RWP);
-                const uint32_t w0 = row[0], w1 = row[1];
-                q.win[k][4 * i + 0] = w0 & 0xFFFFu;
-                q.win[k][4 * i + 1] = w0 >> 16;
-                q.win[k][4 * i + 2] = w1 & 0xFFFFu;
-                q.win[k][4 * i + 3] = w1 >> 16;
+                const uint32_t* row = reinterpret_cast<const uint32_t*>(s_img) + q.base[k] + i * (RWP / 2);
+                q.win[k][2 * i] = row[0];
+                q.win[k][2 * i + 1] = row[1];
+            }
+            // A class-(si, sj) candidate at region pixel (lr, lc) may run in
+            // step tau while it lies tau + 1 pixels inside the region, and
+            // only in the image's interior.
+            uint32_t last = 0u;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int lr = 2 * a + (c >> 1), lc = 2 * b + (c & 1);
+                const int in = min(min(lr, RH - 1 - lr), min(lc, RW - 1 - lc));
+                const int gi = ry0 + lr, gj = rx0 + lc;
+                const bool ok = valid && gi >= 1 && gi <= d.h - 2 && gj >= 1 && gj <= d.w - 2;
+                last |= (ok ? (uint32_t)in : 0u) << (8 * c);
+            }
+            q.last[k] = last;
+            const bool inside = valid && 2 * a >= K && 2 * a < K + TH && 2 * b >= K && 2 * b < K + TW;
+            q.inside[k] = __ballot(inside);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) q.pend[k][c] = ~0ull;
+            if constexpr (SEED) if (seeded) {
+                // the change map over the cell's window, rows 2a - 1 .. 2a + 2
+                // (clamped: candidates of the region's rim never run),
+                // columns 2b - 1 .. 2b + 2 in bits 0..3
+                uint32_t m[4];
+                const int col = 2 * b, wj = col >> 5, sh = col & 31;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int y = min(max(2 * a - 1 + i, 0), RH - 1);
+                    const uint32_t* row = s_cw + y * (RWW + 1) + wj;
+                    const uint64_t two = ((uint64_t)row[1] << 32 | row[0]) << 1;
+                    // column 2b - 1 is the last bit of the word before when 2b
+                    // starts a word
+                    const uint32_t carry = sh == 0 && wj > 0 ? row[-1] >> 31 : 0u;
+                    m[i] = (uint32_t)(two >> sh) | carry;
+                }
+                const uint32_t up = m[0] | m[1] | m[2], down = m[1] | m[2] | m[3];
+                q.pend[k][0] = __ballot((up & 0x7u) != 0u);
+                q.pend[k][1] = __ballot((up & 0xEu) != 0u);
+                q.pend[k][2] = __ballot((down & 0x7u) != 0u);
+                q.pend[k][3] = __ballot((down & 0xEu) != 0u);
             }
         }
         __syncthreads();
 
-        int my_count = 0, my_last = -1;  // interior lowerings, last step with one
-        int my_exams = 0;                // candidates characterised
+        const Lambda lambda = lambda_of(d.lambda);
+        Counts n;
         for (int tau = 0; tau < nsteps; tau += 4) {
-            full_step<0>(q, d, ry0, rx0, s_img, tau, lut, my_last, my_count, my_exams);
-            if (tau + 1 < nsteps)
-                full_step<1>(q, d, ry0, rx0, s_img, tau + 1, lut, my_last, my_count, my_exams);
-            if (tau + 2 < nsteps)
-                full_step<2>(q, d, ry0, rx0, s_img, tau + 2, lut, my_last, my_count, my_exams);
-            if (tau + 3 < nsteps)
-                full_step<3>(q, d, ry0, rx0, s_img, tau + 3, lut, my_last, my_count, my_exams);
+            // four quiet steps: nothing in the region can change any more
+            // (candidates left pending lie outside the exact region for good)
+            if (tau > 0 && __builtin_amdgcn_readfirstlane(
+                               (int)reinterpret_cast<const uint32_t*>(s_flags)[tau / 4 - 1]) == 0)
+                break;
+            step<0>(q, s_img, s_flags, s_bits, tau, nsteps, tid, lut, lambda, n);
+            if (tau + 1 < nsteps) step<1>(q, s_img, s_flags, s_bits, tau + 1, nsteps, tid, lut, lambda, n);
+            if (tau + 2 < nsteps) step<2>(q, s_img, s_flags, s_bits, tau + 2, nsteps, tid, lut, lambda, n);
+            if (tau + 3 < nsteps) step<3>(q, s_img, s_flags, s_bits, tau + 3, nsteps, tid, lut, lambda, n);
         }
 
         store(d, gy0, gx0, src, dst, s_img, tid);
-        if (my_count) {
-            atomicAdd(s_count, my_count);
-            atomicMax(s_last, my_last);
+        if ((tid & 63) == 0) {
+            if (n.lowered) {
+                atomicAdd(s_count, n.lowered);
+                atomicMax(s_last, n.last);
+            }
+            if (n.exams) atomicAdd(s_exam, n.exams);
         }
-        if (my_exams) atomicAdd(s_exam, my_exams);
         __syncthreads();
+        if constexpr (SEED) {
+            if (sd != nullptr) {
+                for (int i = tid; i < TH * WPR; i += NT)
+                    sd->cur_bits[(int64_t)sd->g * TH * WPR + i] = s_bits[i];
+                if (tid == 0) sd->cur_round[sd->g] = sd->r;
+            }
+        }
         last_tau = *s_last;
         return *s_count;
     }
 };
-
-// Inclusive prefix sum over the 64 lanes of a wave with DPP moves: shifts by
-// 1, 2, 4 and 8 lanes within each row of 16, then the last lane of row 0 and
-// of row 2 broadcast into the next row, then lane 31 into rows 2 and 3.
-// Lanes a move cannot reach add the 0 kept in `old`.
-__device__ __forceinline__ int wave_inclusive_sum(int v)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    return v;
-}
 
 // Residency with bit flags and dense work lists.  Two sets of bitmaps, one
 // bit per lattice cell and parity class (4 x LAT_H rows of LWW words each):
@@ -1025,7 +1150,8 @@ struct BTile {
     static constexpr int RH = TH + 2 * K;
     static constexpr int RW = TW + 2 * K;
     static constexpr int RWP = RW;
-    static constexpr int IMG_ELEMS = RH * RWP;
+    // the widened reads of the last candidate reach a pixel past the region
+    static constexpr int IMG_ELEMS = RH * RWP + 4;
     static constexpr int LAT_H = RH / 2, LAT_W = RW / 2;
     static constexpr int NCELL = LAT_H * LAT_W;
     static constexpr int LWW = (LAT_W + 31) / 32;     // bitmap words per lattice row
@@ -1133,7 +1259,7 @@ struct BTile {
     static __device__ __forceinline__ int run(const View d, int gy0, int gx0, int t0, int nsteps,
                                               const void* src, void* dst, E* s_img,
                                               uint8_t* s_flags, uint32_t* s_bits, uint32_t* s_cw,
-                                              const Seed* sd, const TopoEntry* lut, int* s_count,
+                                              const Seed* sd, const DecEntry* lut, int* s_count,
                                               int* s_last, int* s_exam, int tid, int& last_tau)
     {
         (void)t0;  // a multiple of 4: step tau has class tau mod 4
@@ -1191,7 +1317,7 @@ struct BTile {
         }
         __syncthreads();
 
-        const uint32_t lambda = d.lambda;
+        const Lambda lambda = lambda_of(d.lambda);
         const int wave = tid >> 6, lane = tid & 63;
         // The bitmap word this lane owns; lanes without one read a valid word
         // (the last) and take nothing.  Every read below is unconditional, so
@@ -1323,11 +1449,26 @@ struct BTile {
                 const int a = cell >> 8, b = cell & 0xFF;
                 const int lr = 2 * a + si, lc = 2 * b + sj;
                 E* p = s_img + lr * RWP + lc;
-                const uint32_t v = p[0];
-                const uint32_t nbv[8] = {p[1], p[-RWP + 1], p[-RWP], p[-RWP - 1],
-                                         p[-1], p[RWP - 1], p[RWP], p[RWP + 1]};
+                Ring q;
+                if constexpr (sizeof(E) == 1) {
+                    // the two aligned words around W, centre, E (unaligned
+                    // LDS reads cost more than the funnel shift)
+                    const int x0 = lr * RWP + lc - 1;
+                    const uint32_t* w = reinterpret_cast<const uint32_t*>(s_img) + (x0 >> 2);
+                    uint32_t row[3];
+#pragma unroll
+                    for (int y = 0; y < 3; ++y)
+                        row[y] = __builtin_amdgcn_alignbyte(w[(y - 1) * (RWP / 4) + 1],
+                                                            w[(y - 1) * (RWP / 4)], x0 & 3);
+                    q = ring_of_bytes(row[0], row[1], row[2]);
+                } else {
+                    // aligned words: an even column is the third of its four pixels
+                    const uint32_t* w = reinterpret_cast<const uint32_t*>(p - (sj ? 1 : 2));
+                    q = ring_of_words<sj == 0>(w[-RWP / 2], w[-RWP / 2 + 1], w[0], w[1],
+                                               w[RWP / 2], w[RWP / 2 + 1]);
+                }
                 uint32_t alpha;
-                if (decide<true>(v, nbv, lut, lambda, alpha)) {
+                if (decide(q, lut, lambda, alpha)) {
                     p[0] = (E)alpha;
                     lowered = true;
                     atomicOr(&s_dl[c * CLASS_WORDS + a * LWW + (b >> 5)], 1u << (b & 31));
@@ -1360,11 +1501,7 @@ struct BTile {
         }
 
         store(d, gy0, gx0, src, dst, s_img, tid);
-        if (my_count) {
-            atomicAdd(s_count, my_count);
-            atomicMax(s_last, my_last);
-        }
-        if (my_exams) atomicAdd(s_exam, my_exams);
+        block_counts(my_count, my_last, my_exams, s_count, s_last, s_exam, tid);
         __syncthreads();
         if constexpr (SEED) {
             if (sd != nullptr) {
@@ -1382,7 +1519,7 @@ struct BTile {
 // variants (the other variants keep u16).
 template <int TH, int TW, int K, int NT, int VAR, typename E = uint16_t>
 using TileOf = typename std::conditional<
-    VAR == kVarRegs, RTile<TH, TW, K, NT>,
+    VAR == kVarRegs || VAR == kVarRegsSeeded, RTile<TH, TW, K, NT, VAR == kVarRegsSeeded>,
     typename std::conditional<VAR == kVarBits || VAR == kVarBitsSeeded,
                               BTile<TH, TW, K, NT, VAR == kVarBitsSeeded, E>,
                               Tile<TH, TW, K, NT, VAR == kVarSeeded>>::type>::type;
@@ -1398,7 +1535,7 @@ constexpr int lds_waves_per_eu()
 {
     if constexpr (!(TH >= 128 && (VAR == kVarBits || VAR == kVarBitsSeeded))) return 1;
     constexpr int lds = (int)sizeof(typename T::Elem) * T::IMG_ELEMS + T::DIRTY_ELEMS +
-                        4 * T::BITS_WORDS + 4 * T::CW_WORDS + (int)sizeof(TopoEntry) * 256 + 64;
+                        4 * T::BITS_WORDS + 4 * T::CW_WORDS + (int)sizeof(DecEntry) * 256 + 64;
     constexpr int by_lds = (160 * 1024) / lds;
     constexpr int by_threads = 2048 / NT;
     constexpr int blocks = by_lds < by_threads ? by_lds : by_threads;
@@ -1425,8 +1562,8 @@ __device__ __forceinline__ int round_tile(const ImgDev* __restrict__ imgs, ImgCn
                           const int32_t* __restrict__ tile_img, int32_t* tile_state, int g,
                           int round, int ntiles, uint32_t* hist_bits, int32_t* hist_round,
                           typename TileOf<TH, TW, K, NT, VAR, E>::Elem* s_img, uint8_t* s_dirty,
-                          uint32_t* s_bits, uint32_t* s_cw, const TopoEntry* __restrict__ lut_g,
-                          TopoEntry* s_lut, int& lut_adj, int* s_count, int* s_last,
+                          uint32_t* s_bits, uint32_t* s_cw, const DecEntry* __restrict__ lut_g,
+                          DecEntry* s_lut, int& lut_adj, int* s_count, int* s_last,
                           int* s_exam, const WorkList& wl, int kflags)
 {
     using T = TileOf<TH, TW, K, NT, VAR, E>;
@@ -1594,7 +1731,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, NT),
 void k_round(const ImgDev* __restrict__ imgs, ImgCnt* cnt,
                                               const int32_t* __restrict__ tile_img,
                                               int32_t* tile_last, int ntiles, int round,
-                                              const TopoEntry* __restrict__ lut_g,
+                                              const DecEntry* __restrict__ lut_g,
                                               uint32_t* hist_bits, int32_t* hist_round,
                                               WorkList wl, const int32_t* round_base,
                                               int kflags)
@@ -1605,7 +1742,7 @@ void k_round(const ImgDev* __restrict__ imgs, ImgCnt* cnt,
     __shared__ __align__(16) uint8_t s_dirty[T::DIRTY_ELEMS];
     __shared__ uint32_t s_bits[T::BITS_WORDS];
     __shared__ uint32_t s_cw[T::CW_WORDS];
-    __shared__ TopoEntry s_lut[256];
+    __shared__ DecEntry s_lut[256];
     __shared__ int s_count, s_last, s_exam;
     int lut_adj = -1;
     const bool all = wl.list == nullptr || round == wl.full;
@@ -1656,7 +1793,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, NT),
 void k_coop(const ImgDev* __restrict__ imgs, ImgCnt* cnt,
                                              const int32_t* __restrict__ tile_img,
                                              int32_t* tile_last, int ntiles,
-                                             const TopoEntry* __restrict__ lut_g, int32_t* active,
+                                             const DecEntry* __restrict__ lut_g, int32_t* active,
                                              int32_t* rounds_out, int max_rounds,
                                              uint32_t* hist_bits, int32_t* hist_round, int kflags)
 {
@@ -1665,7 +1802,7 @@ void k_coop(const ImgDev* __restrict__ imgs, ImgCnt* cnt,
     __shared__ __align__(16) uint8_t s_dirty[T::DIRTY_ELEMS];
     __shared__ uint32_t s_bits[T::BITS_WORDS];
     __shared__ uint32_t s_cw[T::CW_WORDS];
-    __shared__ TopoEntry s_lut[256];
+    __shared__ DecEntry s_lut[256];
     __shared__ int s_count, s_last, s_exam;
     const int tid = threadIdx.x;
     int lut_adj = -1;
@@ -1696,7 +1833,7 @@ void k_coop(const ImgDev* __restrict__ imgs, ImgCnt* cnt,
 template <int TH, int TW, int K, int NT, int VAR, typename E>
 hipError_t launch_coop_t(hipStream_t stream, const ImgDev* imgs, ImgCnt* cnt,
                          const int32_t* tile_img, int32_t* tile_last, int ntiles,
-                         const TopoEntry* lut, int32_t* active, int32_t* rounds_out,
+                         const DecEntry* lut, int32_t* active, int32_t* rounds_out,
                          int max_rounds, int num_cus, uint32_t* hist_bits, int32_t* hist_round,
                          int kflags)
 {
@@ -1717,7 +1854,7 @@ hipError_t launch_coop_t(hipStream_t stream, const ImgDev* imgs, ImgCnt* cnt,
 template <int TH, int TW, int K, int NT, int VAR, typename E>
 hipError_t launch_round_t(hipStream_t stream, const ImgDev* imgs, ImgCnt* cnt,
                           const int32_t* tile_img, int32_t* tile_last, int ntiles, int round,
-                          const TopoEntry* lut, int num_cus, uint32_t* hist_bits,
+                          const DecEntry* lut, int num_cus, uint32_t* hist_bits,
                           int32_t* hist_round, WorkList wl, const int32_t* round_base, int kflags)
 {
     // As many blocks as fit on the device at once (registers, LDS and thread
@@ -1789,10 +1926,10 @@ __device__ __forceinline__ void wl_and(uint32_t* w, uint32_t m)
 template <typename E, bool GBITS>
 __global__ __launch_bounds__(kWlThreads) void k_worklist(const WlImg* __restrict__ imgs,
                                                        ImgCnt* cnt,
-                                                       const TopoEntry* __restrict__ lut_g,
+                                                       const DecEntry* __restrict__ lut_g,
                                                        int32_t* steps_out)
 {
-    __shared__ TopoEntry s_lut[256];
+    __shared__ DecEntry s_lut[256];
     __shared__ uint32_t s_lbits[GBITS ? 1 : kWlLdsWords];
     __shared__ uint32_t s_list[5][kWlListCap];
     __shared__ int s_n[5], s_ovf[5], s_map[4];
@@ -1881,7 +2018,7 @@ __global__ __launch_bounds__(kWlThreads) void k_worklist(const WlImg* __restrict
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
-    const uint32_t lambda = im.lambda;
+    const Lambda lambda = lambda_of(im.lambda);
     unsigned long long my_exam = 0ull;
     for (;;) {
         const int t = s_step;
@@ -1922,7 +2059,7 @@ __global__ __launch_bounds__(kWlThreads) void k_worklist(const WlImg* __restrict
                 const uint32_t nbv[8] = {p[1], p[-P + 1], p[-P], p[-P - 1],
                                          p[-1], p[P - 1], p[P], p[P + 1]};
                 uint32_t alpha;
-                if (!decide<false>(v, nbv, s_lut, lambda, alpha)) continue;
+                if (!decide(ring_of(v, nbv), s_lut, lambda, alpha)) continue;
                 p[0] = (E)alpha;
                 ++my_low;
                 relower |= 1u << bit;
@@ -1999,7 +2136,7 @@ hipError_t launch_init_state(hipStream_t stream, ImgCnt* cnt, int nimg, int32_t*
 }
 
 hipError_t launch_worklist(hipStream_t stream, const WlImg* imgs, int nimg, int dtype,
-                           bool gbits, ImgCnt* cnt, const TopoEntry* lut, int32_t* steps_out)
+                           bool gbits, ImgCnt* cnt, const DecEntry* lut, int32_t* steps_out)
 {
     if (nimg <= 0) return hipSuccess;
     const dim3 grid(nimg), block(kWlThreads);
@@ -2026,7 +2163,7 @@ hipError_t launch_advance(hipStream_t stream, int32_t* round_base, int n)
 }
 
 hipError_t launch_step(hipStream_t stream, const ImgDev* img_host, const ImgDev* img_dev,
-                       ImgCnt* cnt, int step, const TopoEntry* lut)
+                       ImgCnt* cnt, int step, const DecEntry* lut)
 {
     const int lat_w = (img_host->w + 1) / 2;
     const int lat_h = (img_host->h + 1) / 2;
@@ -2085,6 +2222,8 @@ hipError_t launch_step(hipStream_t stream, const ImgDev* img_host, const ImgDev*
     X(32, 32, 8, 256, 2)    \
     X(32, 32, 16, 256, 2)   \
     X(32, 32, 16, 1024, 2)  \
+    X(32, 32, 16, 1024, 5)  \
+    X(32, 32, 16, 512, 5)   \
     X(32, 32, 32, 1024, 2)  \
     X(64, 64, 16, 1024, 2)  \
     X(64, 64, 32, 1024, 2)
@@ -2120,7 +2259,9 @@ TileShape complete_shape(int th, int tw, int k)
 
 static int lds_bytes(TileShape s)
 {
-    if (s.var == kVarRegs) return (s.th + 2 * s.k + 2) * (s.tw + 2 * s.k + 2) * 2 + 2048 + 64;
+    if (s.var == kVarRegs || s.var == kVarRegsSeeded)
+        return (s.th + 2 * s.k + 2) * (s.tw + 2 * s.k + 2) * 2 + 2048 + 64 +
+               (s.var == kVarRegs ? 8 : 4 * (s.th + (s.th + 2 * s.k) * ((s.tw + 2 * s.k + 31) / 32 + 1)));
     const int region = (s.th + 2 * s.k) * (s.tw + 2 * s.k);
     const int hist = var_seeded(s.var)
                          ? (s.th * (s.tw / 32) + (s.th + 2 * s.k) * ((s.tw + 2 * s.k + 31) / 32)) * 4
@@ -2144,7 +2285,7 @@ int round_blocks_per_cu(TileShape s)
 
 hipError_t launch_round(hipStream_t stream, TileShape shape, const ImgDev* imgs, ImgCnt* cnt,
                         const int32_t* tile_img, int32_t* tile_last, int ntiles, int round,
-                        const TopoEntry* lut, int num_cus, uint32_t* hist_bits,
+                        const DecEntry* lut, int num_cus, uint32_t* hist_bits,
                         int32_t* hist_round, WorkList wl, const int32_t* round_base, int kflags)
 {
     // The bit-flag variants keep u8 images as u8 in LDS: a launch with
@@ -2171,7 +2312,7 @@ hipError_t launch_round(hipStream_t stream, TileShape shape, const ImgDev* imgs,
 
 hipError_t launch_coop(hipStream_t stream, TileShape shape, const ImgDev* imgs, ImgCnt* cnt,
                        const int32_t* tile_img, int32_t* tile_last, int ntiles,
-                       const TopoEntry* lut, int32_t* active, int32_t* rounds_out,
+                       const DecEntry* lut, int32_t* active, int32_t* rounds_out,
                        int max_rounds, int num_cus, uint32_t* hist_bits, int32_t* hist_round,
                        int kflags)
 {

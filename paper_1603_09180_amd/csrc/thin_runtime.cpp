@@ -32,6 +32,7 @@
 using thin::ImgCnt;
 using thin::ImgDev;
 using thin::TileShape;
+using thin::DecEntry;
 using thin::TopoEntry;
 
 namespace {
@@ -119,7 +120,7 @@ struct thin_ctx {
     TileShape forced{0, 0, 0, 0, 0};
     int num_cus = 256;
 
-    TopoEntry* d_lut = nullptr;
+    DecEntry* d_lut = nullptr;
     uint64_t allocated = 0;        // bytes of scratch currently held
     DevBuf twin, imgs, cnt, tile_img, tile_last, small, hist_bits, hist_round, wl_list, wl_meta;
     DevBuf wl_imgs, wl_bits;       // pixel work-list engine: descriptors, global pending bitmaps
@@ -241,7 +242,7 @@ bool bits_variant(TileShape s) { return s.var == thin::kVarBits || s.var == thin
 // bit 0 when u8 images take part, bit 1 when u16 ones do.
 hipError_t launch_rounds_split(hipStream_t stream, TileShape shape, const ImgDev* imgs,
                                ImgCnt* cnt, const int32_t* tile_img, int32_t* tile_last,
-                               int ntiles, int round, const TopoEntry* lut, int num_cus,
+                               int ntiles, int round, const DecEntry* lut, int num_cus,
                                uint32_t* hist_bits, int32_t* hist_round, thin::WorkList wl,
                                const int32_t* round_base, int kflags, int dtypes)
 {
@@ -396,7 +397,7 @@ TileShape choose_shape(const thin_ctx* ctx, int64_t total_pixels, int64_t images
     // throughput: dense per-step work lists with seeded flags in 128x128
     // tiles (less halo work per pixel).
     (void)images;
-    if (total_pixels <= (int64_t)1 << 20) return TileShape{32, 32, 16, 1024, thin::kVarRegs};
+    if (total_pixels <= (int64_t)1 << 20) return TileShape{32, 32, 16, 1024, thin::kVarRegsSeeded};
     return TileShape{128, 128, 16, 512, thin::kVarBitsSeeded};
 }
 
@@ -1388,9 +1389,9 @@ int thin_create(thin_ctx** out, const thin_config* cfg)
             ctx->tune_cache = c.tune_cache;
             load_tune_cache(ctx);
         }
-        TopoEntry table[thin::kTables * 256];
+        DecEntry table[thin::kTables * 256];
         for (int t = 0; t < thin::kTables; ++t)
-            thin::build_topology_table(t & 1, t >> 1, table + 256 * t);
+            thin::build_decision_table(t & 1, t >> 1, table + 256 * t);
         if (hipMalloc((void**)&ctx->d_lut, sizeof table) != hipSuccess) { rc = THIN_ENOMEM; break; }
         if (hipMemcpy(ctx->d_lut, table, sizeof table, hipMemcpyHostToDevice) != hipSuccess) {
             rc = THIN_EDEVICE;

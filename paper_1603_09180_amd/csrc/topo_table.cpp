@@ -4,7 +4,7 @@
 // lambda-skeleton also peak points, T+ = 0, and end points, exactly one
 // n-neighbour in the section of the point's own level).
 //
-// The kernels index it by the upper-neighbour mask U (bit p set when ring
+// It is indexed by the upper-neighbour mask U (bit p set when ring
 // neighbour p has F >= F(x)); the lower set is L = ~U.  The ring positions
 // 0..7 are E, NE, N, NW, W, SW, S, SE: even positions are the 4-neighbours of
 // the centre, odd positions its corners.  On this cycle two ring pixels are
@@ -81,6 +81,34 @@ void build_topology_table(int adjacency, int op, TopoEntry out[256])
         }
         out[u].flags = flags;
         out[u].comps = comps;
+    }
+}
+
+void build_decision_table(int adjacency, int op, DecEntry out[256])
+{
+    // ring position behind each bit of the packed order
+    static const int ring_of_bit[8] = {3, 5, 1, 4, 2, 6, 7, 0};  // NW SW NE W N S SE E
+    TopoEntry topo[256];
+    build_topology_table(adjacency, op, topo);
+    for (unsigned m = 0; m < 256; ++m) {
+        unsigned lower = 0;
+        for (int b = 0; b < 8; ++b)
+            if (m >> b & 1) lower |= 1u << ring_of_bit[b];
+        const TopoEntry& t = topo[~lower & 0xFFu];
+        const unsigned k = t.flags >> 4 & 7u;  // T--
+        // destructible: unconditional; k >= 2: all but at most one counted
+        // component within lambda; else not lowered
+        uint32_t need = (t.flags & 1u) ? 0u : (k >= 2u ? k - 1u : 8u);
+        if (t.flags & 2u) need = 1u << 31;   // peak: its contrast alone decides
+        else if (t.flags & 4u) need |= 1u << 31;
+        uint32_t comps = 0;
+        for (int c = 0; c < 4; ++c) {
+            const unsigned ring = t.comps >> (8 * c) & 0xFFu;
+            for (int b = 0; b < 8; ++b)
+                if (ring >> ring_of_bit[b] & 1u) comps |= 1u << (8 * c + b);
+        }
+        out[m].need = need;
+        out[m].comps = comps;
     }
 }
 

@@ -147,6 +147,53 @@ hipError_t launch_coop(hipStream_t stream, TileShape shape, const ImgDev* imgs, 
                        int kflags);
 bool tile_shape_supported(TileShape s);
 
+// Small-image engine (k_flow): all steps of its images in one cooperative
+// launch, tiles exchanging halos through tagged words.
+struct FlowImg {
+    void* image;
+    int64_t pitch;       // row pitch in elements
+    int64_t word0;       // its first exchange word
+    int32_t h, w;
+    int32_t dtype;       // 1 = u8, 2 = u16
+    uint32_t lambda;
+    int32_t adj;         // table index (adjacency + 2 * operator)
+    int32_t tiles_x, tiles_y;
+    int32_t tile0;       // its first tile
+    int32_t slot;        // its counters; ImgCnt.pad is its mark
+    int32_t ctl0;        // its ring of kFlowRing vote words
+};
+struct FlowShape {
+    int th, tw, k, nt;
+};
+struct FlowRun {
+    const FlowImg* imgs;
+    const int32_t* tile_img;  // tile -> image, null with one image
+    int ntiles;
+    int grid;
+    ImgCnt* cnt;
+    const DecEntry* lut;
+    int32_t* ctl;
+    uint64_t* exch;
+    int max_polls, max_rounds;
+};
+constexpr int kFlowNext = 0, kFlowAbort = 16;  // control words
+constexpr int kFlowCtl = 32;                   // first vote ring
+constexpr int kFlowRing = 1024;
+constexpr int kFlowVote = 4;                   // rounds between votes (a power of two)
+constexpr int kFlowMaxSide = 500;              // tiles across or down an image
+constexpr int kFlowRunning = 0, kFlowStable = 1, kFlowGivenUp = 2;  // marks
+// Exchange words of an image: two copies of one (u8) or two (u16) per 2x2 cell.
+inline int64_t flow_words(int64_t h, int64_t w, int dtype)
+{
+    return 2 * dtype * ((h + 1) / 2) * ((w + 1) / 2);
+}
+// Blocks of the shape that are resident on the device together.
+int flow_capacity(FlowShape s, int num_cus);
+hipError_t launch_flow(hipStream_t stream, FlowShape s, const FlowRun& r);
+// Clears counters, control and exchange words; writes *one to r.imgs when not null.
+hipError_t launch_flow_init(hipStream_t stream, const FlowRun& r, int nimg, int nctl,
+                            int64_t exch_words, const FlowImg* one);
+
 // Gradient front-end (gradient.hip): float32 coefficients of Deriche's
 // recursive smoothing (a0..a3) and derivative (d1, d2) filters, shared
 // feedback (b1, b2) and the steady states of the four recursions for a

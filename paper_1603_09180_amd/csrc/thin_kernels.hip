@@ -46,6 +46,15 @@ namespace thin {
 namespace {
 
 constexpr int kThreads = 256;
+// Compiled shapes of k_flow: tile height, width, steps between exchanges (the
+// halo), threads.
+#define THIN_FLOW_SHAPES(X) \
+    X(16, 16, 8, 256)       \
+    X(24, 48, 8, 640)       \
+    X(48, 48, 8, 1024)      \
+    X(128, 48, 8, 768)      \
+    X(176, 48, 8, 1024)
+
 constexpr int STAGE_CHUNK = 8;  // global loads in flight per thread while staging a tile
 
 // ---------------------------------------------------------------- decision
@@ -137,11 +146,15 @@ __device__ __forceinline__ uint32_t mask_of(u16x2 b0, u16x2 b1, u16x2 b2, u16x2 
     return __builtin_amdgcn_udot2(as_pair(m), w, 0u, false);
 }
 
-// Whether the candidate is lowered, and its new value alpha- when it is (the
-// decision table's fields: see DecEntry).  lut points at the 256 entries of
-// the image's adjacency and operator.
-__device__ __forceinline__ bool decide(const Ring& q, const DecEntry* lut, const Lambda& lam,
-                                       uint32_t& alpha)
+// A candidate's test in numbers (see DecEntry): it is lowered to alpha (its
+// alpha-) when near >= need and contrast1 < reach.  lut points at the 256
+// entries of the image's adjacency and operator.
+struct Verdict {
+    uint32_t near, need;        // counted components within lambda's reach: present, needed
+    uint32_t contrast1, reach;  // v - alpha- - 1, and its bound
+    uint32_t alpha;
+};
+__device__ __forceinline__ Verdict weigh(const Ring& q, const DecEntry* lut, const Lambda& lam)
 {
     const u16x2 one = pair_of_ones();
     const u16x2 d0 = __builtin_elementwise_sub_sat(q.v, q.p0);
@@ -159,13 +172,23 @@ __device__ __forceinline__ bool decide(const Ring& q, const DecEntry* lut, const
     const uint32_t far = mask_of(beyond(d0), beyond(d1), beyond(d2), beyond(d3), 1);
     const u16x2 c = __builtin_elementwise_min(__builtin_elementwise_min(d0 - one, d1 - one),
                                               __builtin_elementwise_min(d2 - one, d3 - one));
-    const uint32_t contrast1 = min(as_word(c) & 0xFFFFu, as_word(c) >> 16);  // v - alpha- - 1
     // counted components that hold a pixel within lambda's reach
     const uint32_t hit = comps & ~__builtin_amdgcn_perm(0u, far, 0u);
     const uint32_t nonzero = (((hit & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | hit) & 0x80808080u;
-    alpha = (as_word(q.v) & 0xFFFFu) - 1u - contrast1;
-    return (uint32_t)__popc(nonzero) >= (need & 0xFFu) &&
-           ((int32_t)need >= 0 || contrast1 < lam.one);
+    Verdict v;
+    v.near = (uint32_t)__popc(nonzero);
+    v.need = need & 0xFFu;
+    v.contrast1 = min(as_word(c) & 0xFFFFu, as_word(c) >> 16);
+    v.reach = (int32_t)need < 0 ? lam.one : 0x10000u;
+    v.alpha = (as_word(q.v) & 0xFFFFu) - 1u - v.contrast1;
+    return v;
+}
+__device__ __forceinline__ bool decide(const Ring& q, const DecEntry* lut, const Lambda& lam,
+                                       uint32_t& alpha)
+{
+    const Verdict v = weigh(q, lut, lam);
+    alpha = v.alpha;
+    return v.near >= v.need && v.contrast1 < v.reach;
 }
 
 __device__ __forceinline__ uint32_t load_px(const void* base, int dtype, int64_t idx)
@@ -824,27 +847,40 @@ struct Tile {
     }
 };
 
+// Barrier for exchanges through LDS: unlike __syncthreads it does not wait
+// for the wave's outstanding global stores.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Residency with register windows.  Each thread owns fixed cells of the 2x2
 // lattice of the region and keeps, per cell, the 4x4 window of pixels covered
 // by the 3x3 neighbourhoods of the cell's four candidates (one per parity
-// class), two pixels to a register.  A parity step changes only pixels of its
-// class, which occupy four window positions, one of them the cell's own
-// candidate; so before each step a thread re-reads from LDS the three
-// positions of the previous step's class that belong to other cells.  A
-// candidate is examined only when a pixel of its 3x3 changed since it was
-// last examined (set by re-read values that differ and by the cell's own
-// lowerings): the re-examination rule of section 2.2, as in the flag variant.
-// LDS holds the whole region as the exchange medium between cells and as the
-// source of the final interior store.
+// class), two pixels to a register.  LDS holds the whole region as the
+// exchange medium between cells and as the source of the final interior
+// store.  A candidate is examined only when a pixel of its 3x3 changed since
+// it was last examined (a window value re-read or received that differs, or
+// the cell's own lowerings): the re-examination rule of section 2.2.
 //
-// A step is a chain of dependent latencies (window read, decision, table
-// read, barrier), so everything beside it is scalar: the pending candidates
-// of a wave's cells are one 64-bit mask per class in scalar registers,
-// updated with the compare results themselves, and a wave without an active
-// candidate branches past the decision; counts are population counts of the
-// same masks.  With SEED the masks start from the previous round's change
-// bitmaps (else every candidate starts pending), so that a quiet wave is
-// quiet from the first step on.
+// What bounds it is the chain of dependent latencies of a step (read the
+// neighbours, decide, look the table up, write, barrier: about 1070 cycles of
+// which the barrier and the trip through LDS are 300), so:
+// - steps run in phases of two, classes (0,0) and (0,1), then (1,0) and (1,1).
+//   A phase changes one row of each cell, and its second class's candidates
+//   touch the first class's pixels only in their own row: the cell's own and
+//   the next cell's, which is the next lane's (lattice rows start at lanes
+//   0, 16 or 32 of a wave), so the second step takes it with a lane shift.
+//   One trip through LDS and one barrier per two steps.
+// - everything beside the chain is scalar: the pending candidates of a wave's
+//   cells are one 64-bit mask per class in scalar registers, updated with the
+//   compare results themselves, a wave without an active candidate branches
+//   past the decision, and counts are population counts of the same masks.
+// With SEED the masks start from the previous round's change bitmaps (else
+// every candidate starts pending), so that a quiet wave is quiet from the
+// first step on.
 template <int TH, int TW, int K, int NT, bool SEED>
 struct RTile {
     using Elem = uint16_t;
@@ -852,9 +888,12 @@ struct RTile {
     static constexpr int RW = TW + 2 * K;
     static constexpr int RWP = RW + 2;                // a spare column on each side
     static constexpr int IMG_ELEMS = (RH + 2) * RWP;  // a spare row above and below
-    static constexpr int DIRTY_ELEMS = 4 * ((K + 3) / 4);  // "lowered" flag of each step
+    static constexpr int DIRTY_ELEMS = 4 * ((K + 7) / 8);  // "lowered" flag of each phase
     static constexpr int LAT_H = RH / 2, LAT_W = RW / 2;
-    static constexpr int PPT = (LAT_H * LAT_W + NT - 1) / NT;  // lattice cells per thread
+    // lanes to a lattice row, and lattice cells per thread (with the lanes
+    // beyond LAT_W, which hold no cell)
+    static constexpr int LROW = LAT_W <= 16 ? 16 : (LAT_W <= 32 ? 32 : 64);
+    static constexpr int PPT = (LAT_H * LROW + NT - 1) / NT;
     static constexpr int WPR = TW >= 32 ? TW / 32 : 1;
     static constexpr int RWW = (RW + 31) / 32;
     static constexpr int BITS_WORDS = SEED ? TH * WPR : 1;
@@ -863,6 +902,20 @@ struct RTile {
     static_assert(K <= TH && K <= TW, "halo must not exceed the tile side");
     static_assert(TH % 2 == 0 && TW % 2 == 0, "tile sides must be even");
     static_assert(RH / 2 <= 254 && RW / 2 <= 254, "step limits are bytes");
+    static_assert(LAT_W <= 64 && NT % 64 == 0, "a lattice row lies in one wave");
+
+    // The lattice cell of a thread's k-th slot; false when it has none.
+    static __device__ __forceinline__ bool cell(int tid, int k, int& a, int& b)
+    {
+        const int idx = tid + k * NT;
+        a = idx / LROW;
+        b = idx % LROW;
+        const bool valid = a < LAT_H && b < LAT_W;
+        a = valid ? a : 0;
+        b = valid ? b : 0;
+        return valid;
+    }
+
     static_assert(!SEED || TW % 32 == 0, "history bitmaps need a tile width multiple of 32");
     static_assert(!SEED || 2 * K <= TH, "history seeding needs the region inside the 3x3 tile block");
 
@@ -938,110 +991,119 @@ struct RTile {
         int lowered = 0, exams = 0, last = -1;  // of the wave
     };
 
-    // One parity step of class C (steps of a residency start at class 0).
+    // Examines the active candidates of class C in step tau; the lanes whose
+    // candidate of slot k was lowered.
     template <int C>
-    static __device__ __forceinline__ void step(Cells& q, uint16_t* s_img, uint8_t* s_flags,
-                                                uint32_t* s_bits, int tau, int nsteps, int tid,
-                                                const DecEntry* lut, const Lambda& lambda,
-                                                Counts& n)
+    static __device__ __forceinline__ uint64_t examine(Cells& q, int k, uint16_t* s_img,
+                                                       uint32_t* s_bits, int tau, int nsteps,
+                                                       int tid, const DecEntry* lut,
+                                                       const Lambda& lambda, Counts& n)
     {
-        constexpr int si = C >> 1, sj = C & 1;
-        constexpr int P = (C + 3) & 3, pi = P >> 1, pj = P & 1;
-        const uint32_t* words = reinterpret_cast<const uint32_t*>(s_img);
-        if (tau > 0) {
-            // Window rows of class-P pixels are 1 - pi and 3 - pi; their
-            // columns 1 - pj and 3 - pj are one half of each row's two words
-            // (the other half may be changing in this very step, and is
-            // read with its own class).  (1 + pi, 1 + pj) is the cell's own.
-            constexpr uint32_t half = pj ? 0x0000FFFFu : 0xFFFF0000u;
+        constexpr int si = C >> 1, sj = C & 1, ci = 1 + si;
+        const uint64_t act = q.pend[k][C] & __ballot((int)(q.last[k] >> (8 * C) & 0xFFu) > tau);
+        if (act == 0) return 0;
+        q.pend[k][C] &= ~act;
+        uint32_t(&w)[8] = q.win[k];
+        const Verdict v =
+            weigh(ring_of_words<sj != 0>(w[2 * ci - 2], w[2 * ci - 1], w[2 * ci], w[2 * ci + 1],
+                                         w[2 * ci + 2], w[2 * ci + 3]),
+                  lut, lambda);
+        const uint64_t low = act & __ballot(v.near >= v.need) & __ballot(v.contrast1 < v.reach);
+        n.exams += __popcll(act);
+        if (low == 0) return 0;
+        const bool mine = __builtin_amdgcn_inverse_ballot_w64(low);
+        if (mine) s_img[2 * q.base[k] + ci * RWP + 1 + sj] = (uint16_t)v.alpha;
+        const uint32_t own = w[2 * ci + sj];
+        const uint32_t put = sj ? ((own & 0xFFFF0000u) | v.alpha) : ((own & 0xFFFFu) | v.alpha << 16);
+        w[2 * ci + sj] = mine ? put : own;
 #pragma unroll
-            for (int k = 0; k < PPT; ++k) {
-                uint32_t got[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int i = 1 - pi + 2 * (e >> 1), w = e & 1;
-                    if (e != 2 * pi + pj) got[e] = words[q.base[k] + i * (RWP / 2) + w];
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (e == 2 * pi + pj) continue;
-                    const int i = 1 - pi + 2 * (e >> 1), w = e & 1;
-                    const uint32_t was = q.win[k][2 * i + w];
-                    const uint32_t now = (got[e] & half) | (was & ~half);
-                    const uint64_t changed = __ballot(now != was);
-                    q.win[k][2 * i + w] = now;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        if (affect(i, 2 * w + 1 - pj) >> c & 1u) q.pend[k][c] |= changed;
-                }
+        for (int c = 0; c < 4; ++c) q.pend[k][c] |= low;
+        const uint64_t in = low & q.inside[k];
+        n.lowered += __popcll(in);
+        n.last = in != 0 ? tau : n.last;
+        if constexpr (SEED) {
+            if (tau >= nsteps - 4 && __builtin_amdgcn_inverse_ballot_w64(in)) {
+                int a, b;
+                cell(tid, k, a, b);
+                const int y = 2 * a + si - K, x = 2 * b + sj - K;
+                atomicOr(&s_bits[y * WPR + (x >> 5)], 1u << (x & 31));
             }
         }
-        constexpr int ci = 1 + si;
+        return low;
+    }
+
+    // Steps tau and tau + 1, of classes (R, 0) and (R, 1).
+    template <int R>
+    static __device__ __forceinline__ void phase(Cells& q, uint16_t* s_img, uint8_t* s_flags,
+                                                 uint32_t* s_bits, int tau, int nsteps, int tid,
+                                                 const DecEntry* lut, const Lambda& lambda,
+                                                 Counts& n)
+    {
+        const uint32_t* words = reinterpret_cast<const uint32_t*>(s_img);
+        if (tau > 0) {
+            // The phase before changed the pixel rows of the other parity: in
+            // the window the cell's own row of it (columns 0 and 3 belong to
+            // other cells) and one row of the cells above or below.  No row
+            // read here is written in this phase.
+            constexpr int own = R ? 1 : 2, far = R ? 3 : 0;
+            constexpr int fi = R ? 1 : 0;  // the classes whose 3x3 holds that row
+#pragma unroll
+            for (int k = 0; k < PPT; ++k) {
+                uint32_t now[4], x[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    now[e] = words[q.base[k] + (e < 2 ? own : far) * (RWP / 2) + (e & 1)];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    uint32_t& w = q.win[k][2 * (e < 2 ? own : far) + (e & 1)];
+                    x[e] = now[e] ^ w;
+                    w = now[e];
+                }
+                const uint64_t left = __ballot(x[0] != 0u), right = __ballot(x[1] != 0u);
+                // columns 0..2 of the far row touch (fi, 0), columns 1..3 (fi, 1)
+                const uint64_t f0 = __ballot((x[2] | (x[3] & 0xFFFFu)) != 0u);
+                const uint64_t f1 = __ballot((x[3] | x[2] >> 16) != 0u);
+                q.pend[k][0] |= left;
+                q.pend[k][2] |= left;
+                q.pend[k][1] |= right;
+                q.pend[k][3] |= right;
+                q.pend[k][2 * fi] |= f0;
+                q.pend[k][2 * fi + 1] |= f1;
+            }
+        }
         uint64_t any = 0;
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
-            const uint64_t act = q.pend[k][C] & __ballot((int)(q.last[k] >> (8 * C) & 0xFFu) > tau);
-            if (act == 0) continue;
-            n.exams += __popcll(act);
-            q.pend[k][C] &= ~act;
-            uint32_t(&w)[8] = q.win[k];
-            uint32_t alpha;
-            const bool yes =
-                decide(ring_of_words<sj != 0>(w[2 * ci - 2], w[2 * ci - 1], w[2 * ci], w[2 * ci + 1],
-                                              w[2 * ci + 2], w[2 * ci + 3]),
-                       lut, lambda, alpha);
-            const uint64_t low = act & __ballot(yes);
+            const uint64_t low =
+                examine<2 * R>(q, k, s_img, s_bits, tau, nsteps, tid, lut, lambda, n);
             if (low == 0) continue;
             any |= low;
-            const bool mine = __builtin_amdgcn_inverse_ballot_w64(low);
-            const uint32_t own = w[2 * ci + sj];
-            const uint32_t put = sj ? ((own & 0xFFFF0000u) | alpha) : ((own & 0xFFFFu) | alpha << 16);
-            w[2 * ci + sj] = mine ? put : own;
-            if (mine) s_img[2 * q.base[k] + ci * RWP + 1 + sj] = (uint16_t)alpha;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) q.pend[k][c] |= low;
-            const uint64_t in = low & q.inside[k];
-            if (in != 0) {
-                n.lowered += __popcll(in);
-                n.last = tau;
-                if constexpr (SEED) {
-                    if (tau >= nsteps - 4 && __builtin_amdgcn_inverse_ballot_w64(in)) {
-                        const int idx = tid + k * NT, a = idx / LAT_W, b = idx - a * LAT_W;
-                        const int y = 2 * a + si - K, x = 2 * b + sj - K;
-                        atomicOr(&s_bits[y * WPR + (x >> 5)], 1u << (x & 31));
-                    }
-                }
-            }
+            // the next cell's (R, 0) pixel is this window's column 3
+            const uint32_t mine = q.win[k][2 * (1 + R)];
+            const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(
+                (int)mine, (int)mine, 0x130, 0xf, 0xf, false);  // wave_shl:1
+            const uint32_t was = q.win[k][2 * (1 + R) + 1];
+            const uint32_t now = (next & 0xFFFF0000u) | (was & 0xFFFFu);
+            const uint64_t right = __ballot(now != was);
+            q.win[k][2 * (1 + R) + 1] = now;
+            q.pend[k][1] |= right;
+            q.pend[k][3] |= right;
         }
-        if (any != 0 && (tid & 63) == 0) s_flags[tau] = 1;
-        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < PPT; ++k)
+            any |= examine<2 * R + 1>(q, k, s_img, s_bits, tau + 1, nsteps, tid, lut, lambda, n);
+        if (any != 0 && (tid & 63) == 0) s_flags[tau >> 1] = 1;
+        lds_barrier();
     }
 
-    // Same contract as Tile::run.
-    static __device__ __forceinline__ int run(const View d, int gy0, int gx0, int t0, int nsteps,
-                              const void* src, void* dst, uint16_t* s_img, uint8_t* s_flags,
-                              uint32_t* s_bits, uint32_t* s_cw, const Seed* sd,
-                              const DecEntry* lut, int* s_count, int* s_last, int* s_exam, int tid,
-                              int& last_tau)
+    // Windows of the staged region, every candidate pending (no barrier).
+    static __device__ __forceinline__ void open(Cells& q, const View& d, int gy0, int gx0,
+                                                const uint16_t* s_img, int tid)
     {
-        (void)t0;  // a multiple of 4: step tau has class tau mod 4
-        const int ry0 = gy0 - K, rx0 = gx0 - K;
-        const bool seeded = SEED && sd != nullptr && sd->r > 0;
-        if (tid == 0) {
-            *s_count = 0;
-            *s_last = -1;
-            *s_exam = 0;
-        }
-        if constexpr (SEED)
-            for (int i = tid; i < TH * WPR; i += NT) s_bits[i] = 0u;
-        // The barrier after the windows are read also orders the resets above
-        // before the steps' updates.
-        Cells q;
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
-            const int idx = tid + k * NT;
-            const bool valid = idx < LAT_H * LAT_W;
-            const int a = valid ? idx / LAT_W : 0, b = valid ? idx % LAT_W : 0;
+            int a, b;
+            const bool valid = cell(tid, k, a, b);
             q.base[k] = a * RWP + b;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -1057,7 +1119,7 @@ struct RTile {
             for (int c = 0; c < 4; ++c) {
                 const int lr = 2 * a + (c >> 1), lc = 2 * b + (c & 1);
                 const int in = min(min(lr, RH - 1 - lr), min(lc, RW - 1 - lc));
-                const int gi = ry0 + lr, gj = rx0 + lc;
+                const int gi = gy0 - K + lr, gj = gx0 - K + lc;
                 const bool ok = valid && gi >= 1 && gi <= d.h - 2 && gj >= 1 && gj <= d.w - 2;
                 last |= (ok ? (uint32_t)in : 0u) << (8 * c);
             }
@@ -1066,44 +1128,102 @@ struct RTile {
             q.inside[k] = __ballot(inside);
 #pragma unroll
             for (int c = 0; c < 4; ++c) q.pend[k][c] = ~0ull;
-            if constexpr (SEED) if (seeded) {
-                // the change map over the cell's window, rows 2a - 1 .. 2a + 2
-                // (clamped: candidates of the region's rim never run),
-                // columns 2b - 1 .. 2b + 2 in bits 0..3
-                uint32_t m[4];
-                const int col = 2 * b, wj = col >> 5, sh = col & 31;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int y = min(max(2 * a - 1 + i, 0), RH - 1);
-                    const uint32_t* row = s_cw + y * (RWW + 1) + wj;
-                    const uint64_t two = ((uint64_t)row[1] << 32 | row[0]) << 1;
-                    // column 2b - 1 is the last bit of the word before when 2b
-                    // starts a word
-                    const uint32_t carry = sh == 0 && wj > 0 ? row[-1] >> 31 : 0u;
-                    m[i] = (uint32_t)(two >> sh) | carry;
-                }
-                const uint32_t up = m[0] | m[1] | m[2], down = m[1] | m[2] | m[3];
-                q.pend[k][0] = __ballot((up & 0x7u) != 0u);
-                q.pend[k][1] = __ballot((up & 0xEu) != 0u);
-                q.pend[k][2] = __ballot((down & 0x7u) != 0u);
-                q.pend[k][3] = __ballot((down & 0xEu) != 0u);
-            }
         }
-        __syncthreads();
+    }
 
-        const Lambda lambda = lambda_of(d.lambda);
-        Counts n;
+    // Pending candidates from the previous round's change map instead.
+    static __device__ __forceinline__ void seed(Cells& q, const uint32_t* s_cw, int tid)
+    {
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+            int a, b;
+            cell(tid, k, a, b);
+            // the change map over the cell's window, rows 2a - 1 .. 2a + 2
+            // (clamped: candidates of the region's rim never run), columns
+            // 2b - 1 .. 2b + 2 in bits 0..3
+            uint32_t m[4];
+            const int col = 2 * b, wj = col >> 5, sh = col & 31;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int y = min(max(2 * a - 1 + i, 0), RH - 1);
+                const uint32_t* row = s_cw + y * (RWW + 1) + wj;
+                const uint64_t two = ((uint64_t)row[1] << 32 | row[0]) << 1;
+                // column 2b - 1 is the last bit of the word before when 2b
+                // starts a word
+                const uint32_t carry = sh == 0 && wj > 0 ? row[-1] >> 31 : 0u;
+                m[i] = (uint32_t)(two >> sh) | carry;
+            }
+            const uint32_t up = m[0] | m[1] | m[2], down = m[1] | m[2] | m[3];
+            q.pend[k][0] = __ballot((up & 0x7u) != 0u);
+            q.pend[k][1] = __ballot((up & 0xEu) != 0u);
+            q.pend[k][2] = __ballot((down & 0x7u) != 0u);
+            q.pend[k][3] = __ballot((down & 0xEu) != 0u);
+        }
+    }
+
+    // Windows from the region's current values: a candidate whose 3x3 holds a
+    // value that differs becomes pending (no barrier).
+    static __device__ __forceinline__ void refresh(Cells& q, const uint16_t* s_img)
+    {
+        const uint32_t* words = reinterpret_cast<const uint32_t*>(s_img);
+#pragma unroll
+        for (int k = 0; k < PPT; ++k)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int i = e >> 1, w = e & 1;
+                const uint32_t now = words[q.base[k] + i * (RWP / 2) + w];
+                const uint64_t changed = __ballot(now != q.win[k][e]);
+                q.win[k][e] = now;
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if ((affect(i, 2 * w) | affect(i, 2 * w + 1)) >> c & 1u) q.pend[k][c] |= changed;
+            }
+    }
+
+    // nsteps steps (a multiple of 4) from class 0 on, ending in a barrier
+    // (s_flags cleared and s_img complete before).
+    static __device__ __forceinline__ void steps(Cells& q, uint16_t* s_img, uint8_t* s_flags,
+                                                 uint32_t* s_bits, int nsteps, int tid,
+                                                 const DecEntry* lut, const Lambda& lambda,
+                                                 Counts& n)
+    {
         for (int tau = 0; tau < nsteps; tau += 4) {
             // four quiet steps: nothing in the region can change any more
             // (candidates left pending lie outside the exact region for good)
             if (tau > 0 && __builtin_amdgcn_readfirstlane(
-                               (int)reinterpret_cast<const uint32_t*>(s_flags)[tau / 4 - 1]) == 0)
+                               (int)reinterpret_cast<const uint16_t*>(s_flags)[tau / 4 - 1]) == 0)
                 break;
-            step<0>(q, s_img, s_flags, s_bits, tau, nsteps, tid, lut, lambda, n);
-            if (tau + 1 < nsteps) step<1>(q, s_img, s_flags, s_bits, tau + 1, nsteps, tid, lut, lambda, n);
-            if (tau + 2 < nsteps) step<2>(q, s_img, s_flags, s_bits, tau + 2, nsteps, tid, lut, lambda, n);
-            if (tau + 3 < nsteps) step<3>(q, s_img, s_flags, s_bits, tau + 3, nsteps, tid, lut, lambda, n);
+            phase<0>(q, s_img, s_flags, s_bits, tau, nsteps, tid, lut, lambda, n);
+            phase<1>(q, s_img, s_flags, s_bits, tau + 2, nsteps, tid, lut, lambda, n);
         }
+    }
+
+    // Same contract as Tile::run.
+    static __device__ __forceinline__ int run(const View d, int gy0, int gx0, int t0, int nsteps,
+                              const void* src, void* dst, uint16_t* s_img, uint8_t* s_flags,
+                              uint32_t* s_bits, uint32_t* s_cw, const Seed* sd,
+                              const DecEntry* lut, int* s_count, int* s_last, int* s_exam, int tid,
+                              int& last_tau)
+    {
+        (void)t0;  // a multiple of 4: step tau has class tau mod 4
+        const bool seeded = SEED && sd != nullptr && sd->r > 0;
+        if (tid == 0) {
+            *s_count = 0;
+            *s_last = -1;
+            *s_exam = 0;
+        }
+        if constexpr (SEED)
+            for (int i = tid; i < TH * WPR; i += NT) s_bits[i] = 0u;
+        // The barrier after the windows are read also orders the resets above
+        // before the steps' updates.
+        Cells q;
+        open(q, d, gy0, gx0, s_img, tid);
+        if constexpr (SEED)
+            if (seeded) seed(q, s_cw, tid);
+        __syncthreads();
+
+        Counts n;
+        steps(q, s_img, s_flags, s_bits, nsteps, tid, lut, lambda_of(d.lambda), n);
 
         store(d, gy0, gx0, src, dst, s_img, tid);
         if ((tid & 63) == 0) {
@@ -1830,6 +1950,305 @@ void k_coop(const ImgDev* __restrict__ imgs, ImgCnt* cnt,
     if (blockIdx.x == 0 && tid == 0) *rounds_out = round + 1;
 }
 
+// ------------------------------------------------------------------ k_flow
+//
+// Small images: the whole run in one cooperative launch, every tile of an
+// image held by a block of its own from its first step to its last, windows
+// in registers and region in LDS.  Nothing is staged between rounds: after K
+// steps a block publishes its interior cells and takes its halo cells from
+// the tiles around it, and neighbours wait for each other only.
+//
+// A round of launches costs about 7500 cycles between launches, 6000 to stage
+// a tile and 4000 to set it up and store it, beside some 20000 for 16 steps
+// (512x512 ridges, 140 rounds: 2.56 ms).  Here an exchange costs about 4000
+// (one trip to memory and back, the region's windows compared), which lets a
+// round have 8 steps and a region two thirds the size: 12000 cycles a round,
+// 1.42 ms.  What bounds it now is the steps' chain of latencies (930 cycles a
+// step, two thirds of them the vector instructions of the busiest tile's
+// waves, few lanes of which are active).
+//
+// Exchange.  A cell (2x2 pixels) travels as 64-bit words whose high half is
+// the round's tag, so a word that carries the tag carries the data and no
+// second flag or fence is needed: u8 cells one word, u16 cells two (one per
+// pixel row).  Words are stored and polled with relaxed agent-scope atomics
+// (the XCDs' L2 caches are not coherent with each other).  Two copies
+// alternate by round parity: a tile overwrites its round r words in round
+// r + 2, which it enters only after every neighbour's round r + 1 words
+// arrived, and a neighbour publishes those after a barrier behind its reads
+// of round r.
+//
+// Candidates.  A candidate not pending was examined at the values its 3x3
+// holds now and not lowered; the decision is a function of the 3x3, so this
+// holds in the halo too, where the values of the last steps were not exact:
+// after the exchange each window is compared with the region's new values and
+// every candidate next to a difference becomes pending.
+//
+// Convergence.  After every kFlowVote-th round a tile adds one to that round's
+// votes, and one in the high half when it lowered an interior pixel during
+// the round's last 4 steps (one word, so that neither is seen without the
+// other).  The first tile reads one vote word a round; when all tiles have
+// voted and none was active it marks the image stable (ImgCnt.pad): every
+// tile's interior is then final, and its block stores it and takes the next
+// tile.  (All blocks reading the word that all blocks add to costs tens of
+// thousands of cycles a round.)  Tiles of one image are never further apart
+// in rounds than in tiles (at most kFlowMaxSide), so a ring of kFlowRing vote
+// words is enough; the first tile clears each half a ring after its use.
+//
+// Progress.  Blocks take tiles in order.  Every image before the oldest
+// unfinished one is finished, so its blocks come back for tiles; the oldest
+// unfinished one has at most gridDim.x tiles and all blocks are resident
+// (cooperative launch), so all its tiles get a block and none waits for a
+// tile without one.  Every wait and the number of rounds are bounded all the
+// same: a block that runs out marks its image given up, sets the abort word
+// and leaves, as do all that see either, and the host runs the images that
+// are not stable on the rounds of launches.  An image's mark changes once
+// (compare and swap), and its tiles are stored when it says stable only, so
+// images given up are untouched.
+
+__device__ __forceinline__ uint64_t flow_load(const uint64_t* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int32_t flow_load(const int32_t* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void flow_store(uint64_t* p, uint64_t v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void flow_store(int32_t* p, int32_t v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Waves per SIMD the compiler fits k_flow's registers to: two blocks to a
+// compute unit for the 48x48 tiles (they serve the images that need them
+// all), else what one block of 16 waves takes.
+constexpr int flow_waves_per_eu(int nt, int th) { return nt == 1024 && th == 48 ? 8 : 4; }
+
+// Marks an image unless it already has a mark; the mark it has.
+__device__ __forceinline__ int flow_mark(int32_t* at, int mark)
+{
+    const int was = atomicCAS(at, kFlowRunning, mark);
+    return __builtin_amdgcn_readfirstlane(was == kFlowRunning ? mark : was);
+}
+
+template <int TH, int TW, int K, int NT>
+__global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const FlowImg* __restrict__ imgs,
+                                             const int32_t* __restrict__ tile_img, int ntiles,
+                                             ImgCnt* cnt, const DecEntry* __restrict__ lut_g,
+                                             int32_t* ctl, uint64_t* exch, int max_polls,
+                                             int max_rounds)
+{
+    using T = RTile<TH, TW, K, NT, false>;
+    constexpr int PPT = T::PPT, RWP = T::RWP;
+    __shared__ __align__(16) uint16_t s_img[T::IMG_ELEMS];
+    __shared__ __align__(16) uint8_t s_flags[T::DIRTY_ELEMS];
+    __shared__ DecEntry s_lut[256];
+    __shared__ int s_tile, s_act, s_mark, s_count, s_last, s_exam;
+    const int tid = threadIdx.x;
+    int lut_adj = -1;
+    for (;;) {
+        if (tid == 0) s_tile = flow_load(&ctl[kFlowAbort]) ? ntiles : atomicAdd(&ctl[kFlowNext], 1);
+        __syncthreads();
+        const int g = s_tile;
+        if (g >= ntiles) break;
+        const FlowImg im = imgs[tile_img != nullptr ? tile_img[g] : 0];
+        const int lt = g - im.tile0, ty = lt / im.tiles_x, tx = lt - ty * im.tiles_x;
+        const int gy0 = ty * TH, gx0 = tx * TW;
+        View d;
+        d.pitch = im.pitch;
+        d.h = im.h;
+        d.w = im.w;
+        d.dtype = im.dtype;
+        d.lambda = im.lambda;
+        if (im.adj != lut_adj) {
+            lut_adj = im.adj;
+            for (int i = tid; i < 256; i += NT) s_lut[i] = lut_g[lut_adj * 256 + i];
+        }
+        if (tid == 0) {
+            s_act = 0;
+            s_mark = kFlowRunning;
+            s_count = 0;
+            s_last = -1;
+            s_exam = 0;
+        }
+        if (tid < T::DIRTY_ELEMS / 4) reinterpret_cast<uint32_t*>(s_flags)[tid] = 0u;
+        T::stage(d, gy0, gx0, im.image, im.image, s_img, tid);
+        __syncthreads();
+        typename T::Cells q;
+        T::open(q, d, gy0, gx0, s_img, tid);
+        // this thread's cells in the exchange: word index, or none (outside
+        // the image), and whether the tile owns them
+        const int cells_y = (im.h + 1) / 2, cells_x = (im.w + 1) / 2;
+        const int64_t ncells = (int64_t)cells_y * cells_x;
+        const int wpc = im.dtype == 1 ? 1 : 2;  // words per cell
+        int word[PPT];
+        bool own[PPT];
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+            int a, b;
+            const bool valid = T::cell(tid, k, a, b);
+            const int ga = (gy0 - K) / 2 + a, gb = (gx0 - K) / 2 + b;
+            const bool live = valid && ga >= 0 && ga < cells_y && gb >= 0 && gb < cells_x;
+            own[k] = live && a >= K / 2 && a < K / 2 + TH / 2 && b >= K / 2 && b < K / 2 + TW / 2;
+            word[k] = live ? wpc * (ga * cells_x + gb) : -1;
+        }
+        __syncthreads();  // every window is read
+
+        uint64_t* const ex = exch + im.word0;
+        const Lambda lambda = lambda_of(im.lambda);
+        int lowered = 0, exams = 0, last = -1;  // of the wave, over all rounds
+        int32_t* const image_mark = &cnt[im.slot].pad;
+        int32_t* const ring = ctl + im.ctl0;
+        const bool counts = lt == 0 && tid < 64;  // the wave that counts the image's votes
+        int vote = 0;                             // the next vote to count
+        int end = kFlowRunning;
+        int r = 0;
+        for (;; ++r) {
+            typename T::Counts n;
+            T::steps(q, s_img, s_flags, nullptr, K, tid, s_lut, lambda, n);
+            lowered += n.lowered;
+            exams += n.exams;
+            if (n.last >= 0) last = r * K + n.last;
+            if (n.last >= K - 4 && (tid & 63) == 0) s_act = 1;
+            const uint32_t tag = (uint32_t)r + 1u;
+            uint64_t* const slot = ex + (int64_t)(tag & 1) * wpc * ncells;
+#pragma unroll
+            for (int k = 0; k < PPT; ++k) {
+                if (!own[k]) continue;
+                // the cell's pixel rows: window columns 1 and 2 of rows 1 and 2
+                const uint32_t r0 = __builtin_amdgcn_alignbyte(q.win[k][3], q.win[k][2], 2);
+                const uint32_t r1 = __builtin_amdgcn_alignbyte(q.win[k][5], q.win[k][4], 2);
+                if (wpc == 1) {
+                    flow_store(&slot[word[k]],
+                               (uint64_t)tag << 32 | __builtin_amdgcn_perm(r1, r0, 0x06040200u));
+                } else {
+                    flow_store(&slot[word[k]], (uint64_t)tag << 32 | r0);
+                    flow_store(&slot[word[k] + 1], (uint64_t)tag << 32 | r1);
+                }
+            }
+            lds_barrier();  // s_act complete; every read of this round's flags done
+            if (tid == 0) {
+                if ((r & (kFlowVote - 1)) == kFlowVote - 1) {
+                    const int v = r / kFlowVote;
+                    (void)__hip_atomic_fetch_add(&ring[v & (kFlowRing - 1)], 1 + (s_act << 16),
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    // the word used half a ring ago: every tile is past it
+                    // and none is back at it
+                    if (lt == 0 && v >= kFlowRing / 2)
+                        flow_store(&ring[(v + kFlowRing / 2) & (kFlowRing - 1)], 0);
+                }
+                s_act = 0;
+            }
+            if (tid < T::DIRTY_ELEMS / 4) reinterpret_cast<uint32_t*>(s_flags)[tid] = 0u;
+            // halo cells of this round
+            uint64_t got[PPT][2];
+            int mark = kFlowRunning;
+            for (int polls = 0;; ++polls) {
+                // (every load goes out before the first is waited for; the
+                // words all blocks share are read as seldom as will do)
+                int32_t m = kFlowRunning, votes = 0;
+                if (polls == 0 ? tid < 64 : (polls & 3) == 3) m = flow_load(image_mark);
+                if (counts && polls == 0 && vote * kFlowVote + kFlowVote <= r)
+                    votes = flow_load(&ring[vote & (kFlowRing - 1)]);
+#pragma unroll
+                for (int k = 0; k < PPT; ++k) {
+                    if (word[k] < 0 || own[k]) continue;
+                    got[k][0] = flow_load(&slot[word[k]]);
+                    got[k][1] = flow_load(&slot[word[k] + wpc - 1]);
+                }
+                mark = __builtin_amdgcn_readfirstlane(m);
+                if (counts) {
+                    votes = __builtin_amdgcn_readfirstlane(votes);
+                    if ((votes & 0xFFFF) == im.tiles_x * im.tiles_y) {
+                        // every tile is through that round
+                        if (votes >> 16 == 0 && mark == kFlowRunning)
+                            mark = flow_mark(image_mark, kFlowStable);
+                        vote = max(vote + 1, r / kFlowVote - 1);
+                    }
+                }
+                bool wait = false;
+#pragma unroll
+                for (int k = 0; k < PPT; ++k) {
+                    if (word[k] < 0 || own[k]) continue;
+                    wait |= (uint32_t)(got[k][0] >> 32) != tag || (uint32_t)(got[k][1] >> 32) != tag;
+                }
+                if (__ballot(wait) == 0 || mark != kFlowRunning) break;
+                if (polls >= max_polls ||
+                    ((polls & 15) == 15 &&
+                     __builtin_amdgcn_readfirstlane(flow_load(&ctl[kFlowAbort])) != 0)) {
+                    mark = flow_mark(image_mark, kFlowGivenUp);
+                    break;
+                }
+                if (polls > 8) __builtin_amdgcn_s_sleep(1);
+            }
+            if (mark == kFlowRunning && r + 1 >= max_rounds) mark = flow_mark(image_mark, kFlowGivenUp);
+            if (mark != kFlowRunning && (tid & 63) == 0) s_mark = mark;
+#pragma unroll
+            for (int k = 0; k < PPT; ++k) {
+                if (word[k] < 0 || own[k]) continue;
+                const uint32_t v = (uint32_t)got[k][0];
+                const uint32_t r0 = wpc == 1 ? (v & 0xFFu) | (v & 0xFF00u) << 8 : v;
+                const uint32_t r1 = wpc == 1 ? (v >> 16 & 0xFFu) | (v >> 24) << 16 : (uint32_t)got[k][1];
+                uint16_t* p = s_img + 2 * q.base[k] + RWP + 1;
+                p[0] = (uint16_t)r0;
+                p[1] = (uint16_t)(r0 >> 16);
+                p[RWP] = (uint16_t)r1;
+                p[RWP + 1] = (uint16_t)(r1 >> 16);
+            }
+            lds_barrier();
+            end = s_mark;
+            if (end != kFlowRunning) break;
+            T::refresh(q, s_img);
+            lds_barrier();  // windows are read before the next step writes
+        }
+        if (end != kFlowStable) {
+            if (tid == 0) flow_store(&ctl[kFlowAbort], 1);
+            break;
+        }
+        T::store(d, gy0, gx0, im.image, im.image, s_img, tid);
+        if ((tid & 63) == 0) {
+            if (lowered) {
+                atomicAdd(&s_count, lowered);
+                atomicMax(&s_last, last);
+            }
+            if (exams) atomicAdd(&s_exam, exams);
+        }
+        __syncthreads();
+        if (tid == 0) {
+            ImgCnt* c = cnt + im.slot;
+            atomicAdd(&c->tile_rounds, (unsigned long long)(r + 1));
+            atomicAdd(&c->examinations, (unsigned long long)(uint32_t)s_exam);
+            if (s_count) {
+                atomicAdd(&c->lowerings, (unsigned long long)(uint32_t)s_count);
+                atomicMax(&c->last_step, s_last);
+            }
+        }
+        __syncthreads();  // the next tile resets the block's totals
+    }
+}
+
+// Clears the control words and the exchange words of a run and, for one image,
+// writes its descriptor.
+__global__ void k_flow_init(ImgCnt* cnt, int nimg, int32_t* ctl, int nctl, uint4* exch,
+                            int64_t nquad, FlowImg* dst, FlowImg one)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t k = i; k < nquad; k += step) exch[k] = make_uint4(0u, 0u, 0u, 0u);
+    for (int64_t k = i; k < nctl; k += step) ctl[k] = 0;
+    if (i < nimg) {
+        cnt[i].lowerings = 0ull;
+        cnt[i].tile_rounds = 0ull;
+        cnt[i].last_step = -1;
+        cnt[i].pad = kFlowRunning;
+        cnt[i].examinations = 0ull;
+    }
+    if (dst != nullptr && i == 0) *dst = one;
+}
+
 template <int TH, int TW, int K, int NT, int VAR, typename E>
 hipError_t launch_coop_t(hipStream_t stream, const ImgDev* imgs, ImgCnt* cnt,
                          const int32_t* tile_img, int32_t* tile_last, int ntiles,
@@ -2124,6 +2543,28 @@ __global__ __launch_bounds__(kWlThreads) void k_worklist(const WlImg* __restrict
     }
 }
 
+template <int TH, int TW, int K, int NT>
+int flow_capacity_t(int num_cus)
+{
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per_cu, reinterpret_cast<const void*>(&k_flow<TH, TW, K, NT>), NT, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return per_cu * num_cus;
+}
+
+template <int TH, int TW, int K, int NT>
+hipError_t launch_flow_t(hipStream_t stream, const FlowRun& r)
+{
+    int ntiles = r.ntiles, max_polls = r.max_polls, max_rounds = r.max_rounds;
+    void* args[] = {(void*)&r.imgs, (void*)&r.tile_img, (void*)&ntiles, (void*)&r.cnt, (void*)&r.lut,
+                    (void*)&r.ctl,  (void*)&r.exch,     (void*)&max_polls, (void*)&max_rounds};
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_flow<TH, TW, K, NT>),
+                                      dim3(r.grid), dim3(NT), args, 0, stream);
+}
+
 }  // namespace
 
 hipError_t launch_init_state(hipStream_t stream, ImgCnt* cnt, int nimg, int32_t* tile_last,
@@ -2147,6 +2588,36 @@ hipError_t launch_worklist(hipStream_t stream, const WlImg* imgs, int nimg, int 
         if (gbits) hipLaunchKernelGGL((k_worklist<uint16_t, true>), grid, block, 0, stream, imgs, cnt, lut, steps_out);
         else hipLaunchKernelGGL((k_worklist<uint16_t, false>), grid, block, 0, stream, imgs, cnt, lut, steps_out);
     }
+    return hipGetLastError();
+}
+
+int flow_capacity(FlowShape s, int num_cus)
+{
+#define X(a, b, c, n) \
+    if (s.th == a && s.tw == b && s.k == c && s.nt == n) return flow_capacity_t<a, b, c, n>(num_cus);
+    THIN_FLOW_SHAPES(X)
+#undef X
+    return 0;
+}
+
+hipError_t launch_flow(hipStream_t stream, FlowShape s, const FlowRun& r)
+{
+#define X(a, b, c, n) \
+    if (s.th == a && s.tw == b && s.k == c && s.nt == n) return launch_flow_t<a, b, c, n>(stream, r);
+    THIN_FLOW_SHAPES(X)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_flow_init(hipStream_t stream, const FlowRun& r, int nimg, int nctl,
+                            int64_t exch_words, const FlowImg* one)
+{
+    const int64_t quads = (exch_words + 1) / 2;
+    const int64_t want = max(max((int64_t)nimg, (int64_t)nctl), quads);
+    const int grid = (int)min((int64_t)1024, (want + kThreads - 1) / kThreads);
+    hipLaunchKernelGGL(k_flow_init, dim3(max(grid, (nimg + kThreads - 1) / kThreads)), dim3(kThreads),
+                       0, stream, r.cnt, nimg, r.ctl, nctl, reinterpret_cast<uint4*>(r.exch), quads,
+                       one ? const_cast<FlowImg*>(r.imgs) : nullptr, one ? *one : FlowImg{});
     return hipGetLastError();
 }
 

@@ -22,6 +22,7 @@
 #include <cstring>
 #include <iterator>
 #include <map>
+#include <set>
 #include <new>
 #include <string>
 #include <vector>
@@ -124,6 +125,10 @@ struct thin_ctx {
     uint64_t allocated = 0;        // bytes of scratch currently held
     DevBuf twin, imgs, cnt, tile_img, tile_last, small, hist_bits, hist_round, wl_list, wl_meta;
     DevBuf wl_imgs, wl_bits;       // pixel work-list engine: descriptors, global pending bitmaps
+    DevBuf flow_imgs, flow_ctl, flow_exch;  // small-image engine
+    int flow_side = -1;            // small-image engine: -1 by size, 0 off, k its k-th shape
+    int flow_polls = 1 << 22;      // polls of a wait before it gives up
+    int flow_cap[8] = {-1, -1, -1, -1, -1, -1, -1, -1};  // resident blocks by shape (-1: not asked)
     DevBuf grad;                   // gradient front-end scratch (8 floats per pixel)
     ImgCnt* h_snap[2] = {nullptr, nullptr};   // pinned snapshots of the counters
     size_t h_snap_cap = 0;
@@ -156,6 +161,7 @@ struct thin_ctx {
 
     // autotuned shapes by size class (log2 total pixels, log2 pixels per image)
     std::map<std::pair<int, int>, TileShape> tuned;
+    std::set<std::pair<int, int>> tuned_flow;   // tuned here, the small-image engine was faster
     std::string tune_cache;        // file of tuned shapes ("" = none)
     std::string arch;              // device architecture name, e.g. gfx950
 
@@ -822,6 +828,169 @@ int run_tiled(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work
                        true);
 }
 
+// --------------------------------------------------------- small-image engine
+
+// Tile shapes in the order they are tried: the first whose tiles all fit the
+// device at once.  A step's length is the chain of one block's waves, so the
+// smallest region that fits wins as long as it leaves the exchanges cheap
+// (512x512 ridges: 24x48 1.42 ms, 48x48 1.69, 128x48 2.88), and 16x16 only
+// where every tile has a compute unit to itself (200x210: 478 us against 525;
+// 512x512, four to a unit: 1675 against 1404).
+constexpr thin::FlowShape kFlowShapes[] = {
+    {16, 16, 8, 256}, {24, 48, 8, 640}, {48, 48, 8, 1024}, {128, 48, 8, 768}, {176, 48, 8, 1024}};
+
+int flow_tiles(const thin_image& im, thin::FlowShape s, int& tx, int& ty)
+{
+    ty = (int)((im.h + s.th - 1) / s.th);
+    tx = (int)((im.w + s.tw - 1) / s.tw);
+    if (ty > thin::kFlowMaxSide || tx > thin::kFlowMaxSide) return INT_MAX / 2;
+    return (int)std::min<int64_t>((int64_t)tx * ty, INT_MAX / 2);
+}
+
+// The small-image engine's shape (index) for these images, -1 for none.
+int choose_flow(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work)
+{
+    if (ctx->engine != THIN_ENGINE_TILED || ctx->forced.th || ctx->graph || ctx->tail ||
+        ctx->max_passes || ctx->flow_side == 0)
+        return -1;
+    int64_t total_px = 0;
+    for (int i : work) total_px += ims[i].h * ims[i].w;
+    const auto cls = size_class(total_px, (int64_t)work.size());
+    if (ctx->tuned.count(cls) && !ctx->tuned_flow.count(cls)) return -1;
+    for (int k = 0; k < (int)std::size(kFlowShapes); ++k) {
+        if (ctx->flow_side > 0 && k + 1 != ctx->flow_side) continue;
+        const thin::FlowShape s = kFlowShapes[k];
+        if (ctx->flow_cap[k] < 0) ctx->flow_cap[k] = thin::flow_capacity(s, ctx->num_cus);
+        const int64_t fit = k == 0 && ctx->flow_side < 0 ? std::min(ctx->flow_cap[k], ctx->num_cus)
+                                                        : ctx->flow_cap[k];
+        int64_t tiles = 0;
+        for (int i : work) {
+            int tx, ty;
+            tiles += flow_tiles(ims[i], s, tx, ty);
+            if (tiles > fit) break;
+        }
+        if (tiles <= fit) return k;
+    }
+    return -1;
+}
+
+// Device memory of a run of the small-image engine.
+struct FlowBufs {
+    thin::FlowImg* imgs;
+    int32_t* tile_img;   // unused with one image
+    ImgCnt* cnt;
+    int32_t* ctl;
+    uint64_t* exch;
+};
+
+int flow_control_words(int nimg) { return thin::kFlowCtl + nimg * thin::kFlowRing; }
+
+// Launches the small-image engine on `imgs` (tile map tile_img, exchange
+// words in all) and fills the statistics of images src[i]; rest receives
+// those it gave up on (untouched).  allocate: profiling events may be created.
+int drive_flow(thin_ctx* ctx, int which, const std::vector<thin::FlowImg>& imgs,
+               const std::vector<int32_t>& tile_img, int64_t words, const FlowBufs& b,
+               const std::vector<int>& src, thin_stats* stats, std::vector<int>& rest, bool allocate)
+{
+    const int nimg = (int)imgs.size();
+    thin::FlowRun run{};
+    run.imgs = b.imgs;
+    run.tile_img = nimg > 1 ? b.tile_img : nullptr;
+    run.ntiles = (int)tile_img.size();
+    run.grid = std::min(run.ntiles, ctx->flow_cap[which]);
+    run.cnt = b.cnt;
+    run.lut = ctx->d_lut;
+    run.ctl = b.ctl;
+    run.exch = b.exch;
+    run.max_polls = ctx->flow_polls;
+    run.max_rounds = 1 << 16;
+    int rc;
+    if (nimg > 1) {
+        HIP_TRY(ctx, hipMemcpyAsync(b.imgs, imgs.data(), sizeof(thin::FlowImg) * nimg,
+                                    hipMemcpyHostToDevice, ctx->stream));
+        HIP_TRY(ctx, hipMemcpyAsync(b.tile_img, tile_img.data(), sizeof(int32_t) * run.ntiles,
+                                    hipMemcpyHostToDevice, ctx->stream));
+    }
+    HIP_TRY(ctx, thin::launch_flow_init(ctx->stream, run, nimg, flow_control_words(nimg), words,
+                                        nimg == 1 ? &imgs[0] : nullptr));
+    const bool profile = ctx->profile && allocate;
+    if (profile) {
+        while (ctx->prof_ev.size() < 2) {
+            hipEvent_t e;
+            HIP_TRY(ctx, hipEventCreate(&e));
+            ctx->prof_ev.push_back(e);
+        }
+        HIP_TRY(ctx, hipEventRecord(ctx->prof_ev[0], ctx->stream));
+    }
+    HIP_TRY(ctx, thin::launch_flow(ctx->stream, kFlowShapes[which], run));
+    if (profile) HIP_TRY(ctx, hipEventRecord(ctx->prof_ev[1], ctx->stream));
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->h_snap[0], b.cnt, sizeof(ImgCnt) * nimg,
+                                hipMemcpyDeviceToHost, ctx->stream));
+    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    if (profile && (rc = collect_profile(ctx, 2))) return rc;
+    for (int n = 0; n < nimg; ++n) {
+        const ImgCnt& c = ctx->h_snap[0][n];
+        if (c.pad != thin::kFlowStable) {
+            rest.push_back(src[n]);
+            continue;
+        }
+        if (profile) ctx->prof_tile_rounds += c.tile_rounds;
+        thin_stats st;
+        fill_stats(&st, c, c.last_step + 5, INT_MAX, false);
+        if (stats) stats[src[n]] = st;
+    }
+    ctx->last_launches = 1;
+    ctx->last_tail_steps = 0;
+    return THIN_OK;
+}
+
+// Descriptors, tile map and exchange words of a run on `work`.
+int64_t plan_flow(int which, const thin_image* ims, const std::vector<int>& work,
+                  std::vector<thin::FlowImg>& imgs, std::vector<int32_t>& tile_img)
+{
+    int64_t words = 0;
+    for (int n = 0; n < (int)work.size(); ++n) {
+        const thin_image& im = ims[work[n]];
+        thin::FlowImg f{};
+        f.image = im.image;
+        f.pitch = pitch_of(im);
+        f.word0 = words;
+        f.h = (int32_t)im.h;
+        f.w = (int32_t)im.w;
+        f.dtype = im.dtype;
+        f.lambda = im.lambda;
+        f.adj = table_index(im);
+        f.tile0 = (int32_t)tile_img.size();
+        f.slot = n;
+        f.ctl0 = flow_control_words(n);
+        tile_img.insert(tile_img.end(), (size_t)flow_tiles(im, kFlowShapes[which], f.tiles_x, f.tiles_y), n);
+        words += (thin::flow_words(im.h, im.w, im.dtype) + 31) & ~int64_t(31);
+        imgs.push_back(f);
+    }
+    return words;
+}
+
+int run_flow(thin_ctx* ctx, int which, const thin_image* ims, const std::vector<int>& work,
+             thin_stats* stats, std::vector<int>& rest)
+{
+    const int nimg = (int)work.size();
+    std::vector<thin::FlowImg> imgs;
+    std::vector<int32_t> tile_img;
+    const int64_t words = plan_flow(which, ims, work, imgs, tile_img);
+    int rc;
+    if ((rc = ensure(ctx, ctx->flow_imgs, sizeof(thin::FlowImg) * nimg))) return rc;
+    if ((rc = ensure(ctx, ctx->cnt, sizeof(ImgCnt) * nimg))) return rc;
+    if ((rc = ensure(ctx, ctx->flow_ctl, sizeof(int32_t) * flow_control_words(nimg)))) return rc;
+    if ((rc = ensure(ctx, ctx->flow_exch, sizeof(uint64_t) * words))) return rc;
+    if (nimg > 1 && (rc = ensure(ctx, ctx->tile_img, sizeof(int32_t) * tile_img.size()))) return rc;
+    if ((rc = ensure_snap(ctx, nimg))) return rc;
+    const FlowBufs b{static_cast<thin::FlowImg*>(ctx->flow_imgs.ptr),
+                     static_cast<int32_t*>(ctx->tile_img.ptr), static_cast<ImgCnt*>(ctx->cnt.ptr),
+                     static_cast<int32_t*>(ctx->flow_ctl.ptr),
+                     static_cast<uint64_t*>(ctx->flow_exch.ptr)};
+    return drive_flow(ctx, which, imgs, tile_img, words, b, work, stats, rest, true);
+}
+
 // ---------------------------------------------------------- cooperative engine
 
 int run_coop(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work, thin_stats* stats)
@@ -1127,6 +1296,16 @@ int run_images(thin_ctx* ctx, const thin_image* ims, int n, thin_stats* stats)
     if (ctx->engine == THIN_ENGINE_STEP) return run_step_engine(ctx, ims, work, stats);
     if (ctx->engine == THIN_ENGINE_WORKLIST) return run_worklist(ctx, ims, work, stats);
     if (ctx->engine == THIN_ENGINE_COOP) return run_coop(ctx, ims, work, stats);
+    const int flow = choose_flow(ctx, ims, work);
+    if (flow >= 0) {
+        std::vector<int> rest;
+        const int rc = run_flow(ctx, flow, ims, work, stats, rest);
+        if (rc == THIN_OK && rest.empty()) return rc;
+        // Over the scratch cap (its exchange words take more than a twin), or
+        // images it gave up on: the rounds of launches.
+        if (rc != THIN_OK && rc != THIN_ENOMEM) return rc;
+        if (rc == THIN_OK) work.swap(rest);
+    }
     return run_tiled(ctx, ims, work, stats);
 }
 
@@ -1247,6 +1426,27 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
             res.candidates = (int32_t)timed.size();
             ctx->tuned[cls] = best;
             save_tune_cache(ctx, cls, best, res.ms);
+            // the small-image engine stays the choice of these images where
+            // it beats the best tile shape
+            ctx->tuned_flow.insert(cls);
+            const int flow = choose_flow(ctx, work_img.data(), work);
+            bool faster = false;
+            for (int k = 0; flow >= 0 && k < 2 && rc == THIN_OK; ++k) {
+                std::vector<int> rest;
+                if (hipMemcpyAsync(scratch, pristine, bytes, hipMemcpyDeviceToDevice, ctx->stream) !=
+                        hipSuccess ||
+                    hipStreamSynchronize(ctx->stream) != hipSuccess) {
+                    rc = fail(ctx, THIN_EDEVICE, "autotune copy failed");
+                    break;
+                }
+                const auto t0 = std::chrono::steady_clock::now();
+                const int r = run_flow(ctx, flow, work_img.data(), work, nullptr, rest);
+                const auto t1 = std::chrono::steady_clock::now();
+                if (r == THIN_EDEVICE) rc = r;
+                if (r != THIN_OK || !rest.empty()) break;
+                faster = std::chrono::duration<double, std::milli>(t1 - t0).count() < res.ms;
+            }
+            if (!faster) ctx->tuned_flow.erase(cls);
         } else if (prev_shape.th) {
             ctx->tuned[cls] = prev_shape;
         }
@@ -1281,6 +1481,24 @@ int run_noalloc(thin_ctx* ctx, const thin_image& im, thin_stats* stats)
     if (!ctx->noalloc || ctx->h_snap_cap < 1)
         return fail(ctx, THIN_EDEVICE, "the static scratch array was not set up by thin_create");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
+    const int flow = choose_flow(ctx, &im, {0});
+    if (flow >= 0) {
+        std::vector<thin::FlowImg> imgs;
+        std::vector<int32_t> tile_img;
+        const int64_t words = plan_flow(flow, &im, {0}, imgs, tile_img);
+        // counters, descriptor, control words, exchange words
+        const uint64_t o_ctl = 1024, o_exch = o_ctl + ((4 * (uint64_t)flow_control_words(1) + 255) & ~255ull);
+        static_assert(sizeof(ImgCnt) <= 256 && sizeof(thin::FlowImg) <= 256, "scratch layout");
+        if (o_exch + 8 * (uint64_t)words <= thin::kNoAllocScratchBytes) {
+            char* base = static_cast<char*>(ctx->noalloc);
+            const FlowBufs b{reinterpret_cast<thin::FlowImg*>(base + 256), nullptr,
+                             reinterpret_cast<ImgCnt*>(base), reinterpret_cast<int32_t*>(base + o_ctl),
+                             reinterpret_cast<uint64_t*>(base + o_exch)};
+            std::vector<int> rest;
+            if ((rc = drive_flow(ctx, flow, imgs, tile_img, words, b, {0}, stats, rest, false))) return rc;
+            if (rest.empty()) return THIN_OK;
+        }
+    }
     const TileShape shape = choose_shape(ctx, im.h * im.w, 1);
     if (!thin::tile_shape_supported(shape))
         return fail(ctx, THIN_EINVAL, "unsupported tile shape %dx%d k=%d", shape.th, shape.tw, shape.k);
@@ -1355,6 +1573,10 @@ int thin_create(thin_ctx** out, const thin_config* cfg)
             thin::tile_shape_supported(e))
             forced = e;
     }
+    // THIN_FLOW="shape[,polls]" picks the small-image engine's shape (1 on; 0:
+    // off; -1: by size) and the bound of its waits (tuning, tests).
+    int flow_side = -1, flow_polls = 1 << 22;
+    if (const char* env = getenv("THIN_FLOW")) (void)sscanf(env, "%d,%d", &flow_side, &flow_polls);
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0) {
         (void)hipGetLastError();
@@ -1369,6 +1591,8 @@ int thin_create(thin_ctx** out, const thin_config* cfg)
     ctx->max_device_bytes = c.max_device_bytes;
     ctx->max_passes = c.max_passes;
     ctx->forced = forced;
+    ctx->flow_side = flow_side;
+    ctx->flow_polls = flow_polls;
     ctx->profile = (c.flags & THIN_FLAG_PROFILE) != 0;
     ctx->tail = (c.flags & THIN_FLAG_TAIL) != 0;
     ctx->graph = (c.flags & THIN_FLAG_GRAPH) != 0;
@@ -1483,7 +1707,8 @@ int thin_destroy(thin_ctx* ctx)
                       &ctx->tile_last,  &ctx->small,      &ctx->wl_list,    &ctx->wl_meta,
                       &ctx->hist_bits,  &ctx->hist_round,  &ctx->serve_twin, &ctx->serve_state,
                       &ctx->serve_cnt,  &ctx->serve_imgs,  &ctx->serve_tile_img, &ctx->grad,
-                      &ctx->wl_imgs,    &ctx->wl_bits};
+                      &ctx->wl_imgs,    &ctx->wl_bits,     &ctx->flow_imgs,  &ctx->flow_ctl,
+                      &ctx->flow_exch};
     for (DevBuf* b : bufs)
         if (b->ptr) (void)hipFree(b->ptr);
     if (ctx->d_lut) (void)hipFree(ctx->d_lut);

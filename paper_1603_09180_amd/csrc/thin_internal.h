@@ -25,6 +25,7 @@ struct ImgDev {
     int32_t max_steps;   // parity-step cap (4 * max_passes), INT32_MAX if none
     int32_t slot;        // index of its counters (stable while the image is resident)
     int64_t state0;      // index of its first tile in the per-tile state array
+    int32_t fresh;       // serving: admitted since the last step (launch_serve_init)
 };
 
 // Per-image counters, written by the kernels with device-scope atomics.
@@ -120,6 +121,9 @@ TileShape complete_shape(int th, int tw, int k);
 // Clears counters and tile state; with wl.list, listed[] = -1 and counts 0.
 hipError_t launch_init_state(hipStream_t stream, ImgCnt* cnt, int nimg, int32_t* tile_last,
                              int ntiles, int32_t* hist_round, WorkList wl);
+// Clears the counters and tile state of the images marked fresh.
+hipError_t launch_serve_init(hipStream_t stream, const ImgDev* imgs, int nimg, ImgCnt* cnt,
+                             int32_t* tile_state);
 // The launch's round is `round`, plus *round_base when round_base is not
 // null (graph replays: the same launches serve every chunk of rounds).
 // Launch flags of the round kernels.

@@ -225,6 +225,23 @@ __global__ void k_init_state(ImgCnt* cnt, int nimg, int32_t* tile_last, int ntil
     if (tile_last && i < 2 * ntiles) tile_last[i] = -1;
 }
 
+// One block per image.
+__global__ void k_serve_init(const ImgDev* __restrict__ imgs, ImgCnt* cnt, int32_t* tile_state)
+{
+    const ImgDev* d = imgs + blockIdx.x;
+    if (d->fresh == 0) return;
+    if (threadIdx.x == 0) {
+        ImgCnt* c = cnt + d->slot;
+        c->lowerings = 0ull;
+        c->tile_rounds = 0ull;
+        c->last_step = -1;
+        c->pad = -1;
+        c->examinations = 0ull;
+    }
+    const int n = 2 * d->tiles_x * d->tiles_y;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) tile_state[2 * d->state0 + i] = -1;
+}
+
 __global__ void k_set_desc(ImgDev* dst, ImgDev d)
 {
     if (threadIdx.x == 0) *dst = d;
@@ -2573,6 +2590,13 @@ hipError_t launch_init_state(hipStream_t stream, ImgCnt* cnt, int nimg, int32_t*
     const int n = max(max(nimg, 2 * ntiles), 3);
     hipLaunchKernelGGL(k_init_state, dim3((n + kThreads - 1) / kThreads), dim3(kThreads), 0,
                        stream, cnt, nimg, tile_last, ntiles, hist_round, wl);
+    return hipGetLastError();
+}
+
+hipError_t launch_serve_init(hipStream_t stream, const ImgDev* imgs, int nimg, ImgCnt* cnt,
+                             int32_t* tile_state)
+{
+    hipLaunchKernelGGL(k_serve_init, dim3(nimg), dim3(kThreads), 0, stream, imgs, cnt, tile_state);
     return hipGetLastError();
 }
 

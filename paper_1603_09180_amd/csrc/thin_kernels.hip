@@ -691,6 +691,12 @@ struct Tile {
     static_assert(TH % 2 == 0 && TW % 2 == 0 && K % 2 == 0, "tile sides and halo must be even");
 
 
+    // The change bitmap run() leaves for the tail of the visit.
+    static __device__ __forceinline__ const uint32_t* changed(uint8_t*, const uint32_t* s_bits)
+    {
+        return s_bits;
+    }
+
     // Tile and halo from src into s_img (no barrier).
     // Work a residency can start before the block knows whether the tile
     // runs (none for this type).
@@ -973,6 +979,12 @@ struct RTile {
                 }
             }
         }
+    }
+
+    // The change bitmap run() leaves for the tail of the visit.
+    static __device__ __forceinline__ const uint32_t* changed(uint8_t*, const uint32_t* s_bits)
+    {
+        return s_bits;
     }
 
     // Tile and halo from src into s_img, spare rows and columns zeroed (they
@@ -1263,24 +1275,28 @@ struct RTile {
     }
 };
 
-// Residency with bit flags and dense work lists.  Two sets of bitmaps, one
-// bit per lattice cell and parity class (4 x LAT_H rows of LWW words each):
-// "pending" holds the candidates to examine from the residency's start (all
-// ones, or with SEED from the previous round's change bitmaps), "lowered"
-// holds, per class, the cells lowered by that class's latest step.  A step
-// of class c needs the candidates whose 3x3 changed since their examination
-// 4 steps earlier (section 2.2 re-examination rule): the cell itself if it
-// was lowered then, and any pixel of its 3x3 lowered by the 3 steps since,
-// one class each; the owner of each bitmap word gathers those from the
-// lowered bitmaps with word shifts (pull), so a lowering costs one LDS
-// atomic.  Every wave takes the candidates of its run of words (one word per
-// lane) and writes them into a run of the step's list that it reserves with
-// one LDS atomic, at offsets from a wave prefix sum; after one barrier the
-// block examines the list densely, so clean candidates cost nothing beyond
-// their share of one word.
+// Residency with bit flags and dense work lists.  "Lowered" bitmaps hold, one
+// bit per lattice cell and parity class (4 x LAT_H rows of LWW words), the
+// cells lowered by that class's latest step; the candidates to examine from
+// the residency's start (all of them, or with SEED those next to the previous
+// round's change bitmaps) stay in the registers of the lanes that own their
+// words.  A step of class c needs the candidates whose 3x3 changed since
+// their examination 4 steps earlier (section 2.2 re-examination rule): the
+// cell itself if it was lowered then, and any pixel of its 3x3 lowered by the
+// 3 steps since, one class each; the owner of each bitmap word gathers those
+// from the lowered bitmaps with word shifts (pull), so a lowering costs one
+// LDS atomic.  Every wave takes the candidates of its run of words and writes
+// them into a run of the step's list that it reserves with one LDS atomic, at
+// offsets from a wave prefix sum; after one barrier the block examines the
+// list densely, so clean candidates cost nothing beyond their share of one
+// word.
 // The seeded start: a candidate whose 3x3 saw none of the pixels lowered
 // during the last 4 steps of round r - 1 (dilated by the 3x3) was examined 4
 // steps earlier at the same values.
+//
+// What bounds it: in the dense first round the vector units (97 % of their
+// issue slots; per 64 examinations 76 instructions, per wave and step about
+// 300 for gather and list), later the chain of a tile's few busy steps.
 template <int TH, int TW, int K, int NT, bool SEED, typename E>
 struct BTile {
     using Elem = E;  // LDS pixel type: the image's own
@@ -1295,42 +1311,65 @@ struct BTile {
     static constexpr int CLASS_WORDS = LAT_H * LWW;   // bitmap words per class
     static constexpr int NWAVE = NT / 64;
     // Bitmap words of a class are dealt to the waves in runs of WAVE_WORDS
-    // (one per lane, whole lattice rows), so each wave's run of the list is
-    // in raster order and neighbouring lanes examine neighbouring cells.
+    // (whole lattice rows), so each wave's run of the list is in raster order
+    // and neighbouring lanes examine neighbouring cells.  Where the run leaves
+    // half the lanes idle, two lanes share a word, half of its bits each: a
+    // lane's part of the list is written bit by bit.
     static constexpr int WAVE_ROWS = (LAT_H + NWAVE - 1) / NWAVE;
     static constexpr int WAVE_WORDS = WAVE_ROWS * LWW;
+    static constexpr int SPLIT = WAVE_WORDS <= 32 ? 2 : 1;  // lanes to a word
     static constexpr int LIST_ELEMS = (NCELL + 1) & ~1;
-    // LDS bytes behind the flag pointer: 4 pending bitmaps, 4 lowered
-    // bitmaps, a ring of 8 list lengths and 8 "lowered" flags (by step),
-    // 4 "has seeds" flags (by class), the step's list
-    static constexpr int DIRTY_ELEMS = 32 * CLASS_WORDS + 32 + 16 + 2 * LIST_ELEMS;
     static constexpr int WPR = TW >= 32 ? TW / 32 : 1;
     static constexpr int RWW = (RW + 31) / 32;
-    static constexpr int BITS_WORDS = SEED ? TH * WPR : 1;
-    static constexpr int CW_WORDS = SEED ? RH * RWW : 1;
+    // LDS words behind the flag pointer: a pad (reads one row and word before
+    // the bitmaps), 4 lowered bitmaps, a ring of 8 list lengths and 8
+    // "lowered" flags (by step), 4 "has seeds" flags (by class), the step's
+    // list.  Outside the steps the list's space holds the change bitmap
+    // handed to the next round and, behind it, the previous round's change
+    // map of the next tile (whose staging may overlap this tile's tail).
+    static constexpr int PAD_WORDS = LWW + 1;
+    static constexpr int LIST_AT = PAD_WORDS + 4 * CLASS_WORDS + 8 + 4;
+    static constexpr int CHANGED_WORDS = SEED ? TH * WPR : 0;
+    static constexpr int MAP_WORDS = SEED ? RH * RWW : 0;
+    static constexpr int LIST_WORDS = LIST_ELEMS / 2 > CHANGED_WORDS + MAP_WORDS
+                                          ? LIST_ELEMS / 2 : CHANGED_WORDS + MAP_WORDS;
+    static constexpr int DIRTY_ELEMS = 4 * (LIST_AT + LIST_WORDS);
+    static constexpr int BITS_WORDS = 1, CW_WORDS = 1;
     static_assert(K % 4 == 0, "a residency must start at parity class 0");
     static_assert(K <= TH && K <= TW, "halo must not exceed the tile side");
     static_assert(TH % 4 == 0 && TW % 4 == 0, "tile sides must be multiples of 4");
     static_assert(NT % 64 == 0 && CLASS_WORDS <= NT, "one bitmap word per thread");
-    static_assert(WAVE_WORDS <= 64, "one bitmap word per lane");
+    static_assert(WAVE_WORDS <= 64, "at most one bitmap word per lane");
     static_assert(LWW + 1 <= 8, "reads one row and word past the lowered bitmaps stay in the ring");
-    static_assert(LIST_ELEMS >= NT, "every thread may read the first list entry");
     static_assert(LAT_H <= 256 && LAT_W <= 256, "list entries hold a row and a column byte");
     static_assert(!SEED || TW % 32 == 0, "history bitmaps need a tile width multiple of 32");
     static_assert(!SEED || 2 * K <= TH, "history seeding needs the region inside the 3x3 tile block");
 
 
+    // The flag area's parts.
+    static __device__ __forceinline__ uint32_t* lowered_maps(uint8_t* s_flags)
+    {
+        return reinterpret_cast<uint32_t*>(s_flags) + PAD_WORDS;
+    }
+    static __device__ __forceinline__ uint32_t* list_words(uint8_t* s_flags)
+    {
+        return reinterpret_cast<uint32_t*>(s_flags) + LIST_AT;
+    }
+    // The change bitmap run() leaves for the tail of the visit.
+    static __device__ __forceinline__ const uint32_t* changed(uint8_t* s_flags, const uint32_t*)
+    {
+        return list_words(s_flags);
+    }
+
     // Everything a residency can start before the block knows whether the
     // tile runs, so that it overlaps the staging loads instead of following
     // them: the ring slots and flags, the cleared lowered bitmaps and, when
-    // seeded, the previous round's change map of the region in 32-pixel
-    // words (two dependent global reads per word).  None of it is read by the
-    // previous tile's tail (which reads only the change bitmap s_bits and the
-    // block counters, both set up after the decision).
+    // seeded, the previous round's change map of the region in 32-pixel words.
+    // None of it is read by the previous tile's tail.
     static __device__ __forceinline__ void prefetch(const View& d, int gy0, int gx0, const Seed* sd,
-                                                    uint8_t* s_flags, uint32_t* s_cw, int tid)
+                                                    uint8_t* s_flags, uint32_t*, int tid)
     {
-        uint32_t* s_dl = reinterpret_cast<uint32_t*>(s_flags) + 4 * CLASS_WORDS;
+        uint32_t* s_dl = lowered_maps(s_flags);
         int* s_total = reinterpret_cast<int*>(s_dl + 4 * CLASS_WORDS);
         uint8_t* s_low = reinterpret_cast<uint8_t*>(s_total + 8);
         uint8_t* s_seeds = s_low + 8;
@@ -1339,10 +1378,11 @@ struct BTile {
         if (tid < 8) {
             s_total[tid] = 0;
             s_low[tid] = 0;
-            s_seeds[tid] = seeded ? 0 : 1;
+            if (tid < 4) s_seeds[tid] = seeded ? 0 : 1;
         }
         if constexpr (SEED) {
             if (seeded) {
+                uint32_t* map = list_words(s_flags) + CHANGED_WORDS;
                 const int ry0 = gy0 - K, rx0 = gx0 - K;
                 for (int it = tid; it < RH * RWW; it += NT) {
                     const int y = it / RWW, j = it - y * RWW;
@@ -1356,7 +1396,7 @@ struct BTile {
                         const uint32_t hi = history_word_t<TH, TW>(sd, gi, a + 1);
                         word = sh ? ((lo >> sh) | (hi << (32 - sh))) : lo;
                     }
-                    s_cw[it] = word;
+                    map[it] = word;
                 }
             }
         }
@@ -1392,20 +1432,29 @@ struct BTile {
         return x;
     }
 
+    // The low 16 bits of x at the even bits of the result.
+    static __device__ __forceinline__ uint32_t spread_bits(uint32_t x)
+    {
+        x &= 0xFFFFu;
+        x = (x | (x << 8)) & 0x00FF00FFu;
+        x = (x | (x << 4)) & 0x0F0F0F0Fu;
+        x = (x | (x << 2)) & 0x33333333u;
+        return (x | (x << 1)) & 0x55555555u;
+    }
+
     // Same contract as Tile::run.
     static __device__ __forceinline__ int run(const View d, int gy0, int gx0, int t0, int nsteps,
                                               const void* src, void* dst, E* s_img,
-                                              uint8_t* s_flags, uint32_t* s_bits, uint32_t* s_cw,
+                                              uint8_t* s_flags, uint32_t*, uint32_t*,
                                               const Seed* sd, const DecEntry* lut, int* s_count,
                                               int* s_last, int* s_exam, int tid, int& last_tau)
     {
         (void)t0;  // a multiple of 4: step tau has class tau mod 4
-        uint32_t* s_db = reinterpret_cast<uint32_t*>(s_flags);           // [4][LAT_H][LWW]
-        uint32_t* s_dl = s_db + 4 * CLASS_WORDS;                         // [4][LAT_H][LWW]
+        uint32_t* s_dl = lowered_maps(s_flags);                          // [4][LAT_H][LWW]
         int* s_total = reinterpret_cast<int*>(s_dl + 4 * CLASS_WORDS);   // [8]: step tau & 7
         uint8_t* s_low = reinterpret_cast<uint8_t*>(s_total + 8);        // [8]: step tau & 7
         uint8_t* s_seeds = s_low + 8;                                    // [4]: class
-        uint16_t* s_list = reinterpret_cast<uint16_t*>(s_seeds + 8);
+        uint16_t* s_list = reinterpret_cast<uint16_t*>(list_words(s_flags));
         const int ry0 = gy0 - K, rx0 = gx0 - K;
         const bool seeded = SEED && sd != nullptr && sd->r > 0;
         if (tid == 0) {
@@ -1413,61 +1462,67 @@ struct BTile {
             *s_last = -1;
             *s_exam = 0;
         }
-        if constexpr (SEED)
-            for (int i = tid; i < TH * WPR; i += NT) s_bits[i] = 0u;
-        if (!seeded)
-            for (int i = tid; i < 4 * CLASS_WORDS; i += NT) s_db[i] = valid_bits(i % LWW);
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+        // The bitmap word this lane owns, and its bits of it; lanes without
+        // one read a valid word (the last) and take nothing.  Every read of a
+        // step is unconditional, so a step's reads go out together: a word of
+        // a neighbouring row or column outside the lattice reads some other
+        // word of the flag area (they all lie inside it) and is masked to zero.
+        const int part = lane % SPLIT;
+        const bool has_word =
+            lane / SPLIT < WAVE_WORDS && wave * WAVE_WORDS + lane / SPLIT < CLASS_WORDS;
+        const int myw = has_word ? wave * WAVE_WORDS + lane / SPLIT : CLASS_WORDS - 1;
+        const int wa = myw / LWW, wj = myw - (myw / LWW) * LWW;
+        const bool up_ok = wa > 0, dn_ok = wa + 1 < LAT_H, lt_ok = wj > 0, rt_ok = wj + 1 < LWW;
+        const uint32_t mine = !has_word ? 0u
+                              : SPLIT == 1 ? valid_bits(wj)
+                                           : valid_bits(wj) & (part ? 0xFFFF0000u : 0x0000FFFFu);
+        uint32_t seeds[4] = {mine, mine, mine, mine};  // by class, pending since the start
         if constexpr (SEED) if (seeded) {
-            // Flag word j of class (si, sj) at lattice row a covers region
-            // row 2a + si, columns 64j + sj + 2t (t < 32): the 3x3-dilated
-            // changed map there, odd or even columns packed.
-            for (int i = tid; i < 4 * CLASS_WORDS; i += NT) {
-                const int c = i / CLASS_WORDS, rem = i - c * CLASS_WORDS;
-                const int a = rem / LWW, j = rem - a * LWW;
-                const int y = 2 * a + (c >> 1), sj = c & 1;
-                // every read is unconditional (clamped into the map, the
-                // value masked), so all of them go out together
-                uint32_t half[2];
+            // Bits 16h .. 16h + 15 of word j of class (si, sj) cover region
+            // row 2a + si, columns 64j + 32h + sj + 2t: the 3x3-dilated change
+            // map there (its word 2j + h), odd or even columns packed.  Every
+            // read is unconditional (clamped into the map, the value masked),
+            // so all of them go out together.
+            const uint32_t* map = list_words(s_flags) + CHANGED_WORDS;
 #pragma unroll
-                for (int hw = 0; hw < 2; ++hw) {
-                    const int w = 2 * j + hw;
-                    const int wc = w < RWW ? w : RWW - 1;
-                    const int wl = wc > 0 ? wc - 1 : 0, wr = wc + 1 < RWW ? wc + 1 : wc;
-                    uint32_t m = 0u;
+            for (int c = 0; c < 4; ++c) seeds[c] = 0u;
 #pragma unroll
-                    for (int dy = -1; dy <= 1; ++dy) {
-                        const int yy = y + dy;
-                        const int yc = yy < 0 ? 0 : (yy >= RH ? RH - 1 : yy);
-                        const uint32_t cc = s_cw[yc * RWW + wc];
-                        const uint32_t l = s_cw[yc * RWW + wl];
-                        const uint32_t r = s_cw[yc * RWW + wr];
-                        const uint32_t row = cc | (cc << 1) | (cc >> 1) | (wc > 0 ? l >> 31 : 0u) |
-                                             (wc + 1 < RWW ? r << 31 : 0u);
-                        m |= (yy >= 0 && yy < RH) ? row : 0u;
-                    }
-                    half[hw] = w < RWW ? even_bits(m >> sj) : 0u;
+            for (int h = 0; h < 2; ++h) {
+                if (SPLIT == 2 && h > 0) break;
+                const int half = SPLIT == 2 ? part : h;
+                const int w = 2 * wj + half;
+                const int wc = w < RWW ? w : RWW - 1;
+                const int wl = wc > 0 ? wc - 1 : 0, wr = wc + 1 < RWW ? wc + 1 : wc;
+                uint32_t row[4];  // dilated along the row: region rows 2a - 1 .. 2a + 2
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int yy = 2 * wa - 1 + e;
+                    const int yc = yy < 0 ? 0 : (yy >= RH ? RH - 1 : yy);
+                    const uint32_t cc = map[yc * RWW + wc];
+                    const uint32_t l = map[yc * RWW + wl], r = map[yc * RWW + wr];
+                    const uint32_t m = cc | (cc << 1) | (cc >> 1) | (wc > 0 ? l >> 31 : 0u) |
+                                       (wc + 1 < RWW ? r << 31 : 0u);
+                    row[e] = (yy >= 0 && yy < RH && w < RWW) ? m : 0u;
                 }
-                const uint32_t word = (half[0] | (half[1] << 16)) & valid_bits(j);
-                s_db[i] = word;
-                if (word) s_seeds[c] = 1;
+                const uint32_t m0 = row[0] | row[1] | row[2], m1 = row[1] | row[2] | row[3];
+                seeds[0] |= even_bits(m0) << (16 * half);
+                seeds[1] |= even_bits(m0 >> 1) << (16 * half);
+                seeds[2] |= even_bits(m1) << (16 * half);
+                seeds[3] |= even_bits(m1 >> 1) << (16 * half);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                seeds[c] &= mine;
+                if (seeds[c]) s_seeds[c] = 1;
             }
         }
         __syncthreads();
 
         const Lambda lambda = lambda_of(d.lambda);
-        const int wave = tid >> 6, lane = tid & 63;
-        // The bitmap word this lane owns; lanes without one read a valid word
-        // (the last) and take nothing.  Every read below is unconditional, so
-        // a step's reads go out together: a word of a neighbouring row or
-        // column outside the lattice reads some other word of the flag area
-        // (they all lie inside it) and is masked to zero.
-        const bool has_word = lane < WAVE_WORDS && wave * WAVE_WORDS + lane < CLASS_WORDS;
-        const int myw = has_word ? wave * WAVE_WORDS + lane : CLASS_WORDS - 1;
-        const int wa = myw / LWW, wj = myw - (myw / LWW) * LWW;
-        const bool up_ok = wa > 0, dn_ok = wa + 1 < LAT_H, lt_ok = wj > 0, rt_ok = wj + 1 < LWW;
         const uint32_t* own_dl = s_dl + myw;  // word (wa, wj) of class 0's lowered bitmap
-        int my_count = 0, my_last = -1;  // interior lowerings, last step with one
-        int my_exams = 0;                // candidates characterised (thread 0 counts the lists)
+        int my_count = 0, my_last = -1;  // the wave's interior lowerings, last step with one
+        int my_exams = 0;                // candidates characterised (the block's)
         bool done = false;               // block-uniform: no later step can lower anything
 
         // One step of class C = tau mod 4.  A step's candidates come from the
@@ -1481,15 +1536,15 @@ struct BTile {
         // at step tau - 4).
         auto step = [&](auto cls, int tau) __attribute__((always_inline)) {
             constexpr int c = decltype(cls)::value, si = c >> 1, sj = c & 1;
-            const uint64_t lw = *reinterpret_cast<const uint64_t*>(s_low);
-            const bool seeds_c = s_seeds[c] != 0;
+            const uint32_t* flags = reinterpret_cast<const uint32_t*>(s_low);
+            const uint32_t lw0 = flags[0], lw1 = flags[1], lws = flags[2];
             // Candidates of this word: still pending from the residency's
             // start, lowered themselves 4 steps ago, or next to a pixel
             // lowered during the last 3 steps (the lowered bitmap of each
             // other class, spread over the cells whose 3x3 holds it: rows a
             // or a+-1 and columns b or b+-1 by parity).  Read before the quiet
             // test; in a quiet step every one of these words is zero.
-            uint32_t want = s_db[c * CLASS_WORDS + myw] | own_dl[c * CLASS_WORDS];
+            uint32_t want = seeds[c] | own_dl[c * CLASS_WORDS];
 #pragma unroll
             for (int k = 1; k < 4; ++k) {
                 const int o = (c + k) & 3, oi = o >> 1, oj = o & 1;
@@ -1518,10 +1573,15 @@ struct BTile {
                 }
             }
             {
-                const int sh = 8 * ((tau + 4) & 7);  // slots tau-4 .. tau-1, in ring order
-                const uint64_t rot = sh ? ((lw >> sh) | (lw << (64 - sh))) : lw;
-                const uint64_t recent = rot & 0xFFFFFFFFull;
-                if (recent == 0ull && !(tau < 4 && seeds_c)) {
+                // "lowered" flags of steps tau - 4 .. tau - 1: the ring's half
+                // that holds the group of 4 steps before, and the steps of
+                // this group in the other
+                const uint32_t half0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)lw0);
+                const uint32_t half1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)lw1);
+                const bool seeds_c = ((uint32_t)__builtin_amdgcn_readfirstlane((int)lws) >> (8 * c) & 0xFFu) != 0;
+                const uint32_t now = tau & 4 ? half1 : half0, before = tau & 4 ? half0 : half1;
+                const uint32_t recent = (now & ((1u << (8 * c)) - 1u)) | (before >> (8 * c));
+                if (recent == 0u && !(tau < 4 && seeds_c)) {
                     if (tau >= 4) {
                         done = true;
                         return;
@@ -1534,10 +1594,8 @@ struct BTile {
                 }
             }
             if (tid == 0) s_low[tau & 7] = 0;
-            if (has_word) {
-                s_db[c * CLASS_WORDS + myw] = 0u;
-                s_dl[c * CLASS_WORDS + myw] = 0u;
-            }
+            seeds[c] = 0u;
+            if (has_word) s_dl[c * CLASS_WORDS + myw] = 0u;
             // Exact region after tau steps, clipped to the image interior,
             // as lattice rows a (region row 2a + si) and columns b (2b + sj).
             const int r_lo = max(tau + 1, 1 - ry0), r_hi = min(RH - 2 - tau, d.h - 2 - ry0);
@@ -1547,9 +1605,9 @@ struct BTile {
             uint32_t take = 0u;
             {
                 const int lo = max(b_lo - 32 * wj, 0), hi = min(b_hi - 32 * wj, 31);
-                if (has_word && wa >= a_lo && wa <= a_hi && lo <= hi) {
+                if (wa >= a_lo && wa <= a_hi && lo <= hi) {
                     const uint32_t mask = (hi == 31 ? ~0u : ((2u << hi) - 1u)) & ~((1u << lo) - 1u);
-                    take = want & mask;
+                    take = want & mask & mine;
                 }
             }
             // Each wave reserves a run of the step's list with one LDS atomic
@@ -1571,59 +1629,60 @@ struct BTile {
                 }
             }
             __syncthreads();
-            // the first entry is read with the length (it is in the list
-            // whenever tid < total)
-            const int total = s_total[tau & 7];
-            int next_cell = s_list[tid];
-            if (tid == 0) {
-                s_total[(tau + 4) & 7] = 0;
-                my_exams += total;
-            }
-            bool inner = false, lowered = false;
-            for (int i = tid; i < total; i += NT) {
+            // Every wave takes 64 entries at a time; past the end of the list
+            // its lanes repeat the last entry and are masked.  The loop, the
+            // verdicts and the counts are the wave's (scalar), so a lane's
+            // work is the decision and its own writes.
+            const int total = __builtin_amdgcn_readfirstlane(s_total[tau & 7]);
+            if (tid == 0) s_total[(tau + 4) & 7] = 0;
+            bool lowered = false;
+            int i = tid;
+            int next_cell = s_list[min(i, max(total - 1, 0))];
+            for (int i0 = 64 * wave; i0 < total; i0 += NT, i += NT) {
                 const int cell = next_cell;
-                if (i + NT < total) next_cell = s_list[i + NT];
+                next_cell = s_list[min(i + NT, total - 1)];
                 const int a = cell >> 8, b = cell & 0xFF;
-                const int lr = 2 * a + si, lc = 2 * b + sj;
-                E* p = s_img + lr * RWP + lc;
+                const int o = (2 * a + si) * RWP + 2 * b + sj;
+                // the words around W, centre, E of the three rows, all read
+                // before the first is used (left to itself the compiler,
+                // short of registers, waits for each row in turn)
+                uint32_t w[6];
                 Ring q;
                 if constexpr (sizeof(E) == 1) {
-                    // the two aligned words around W, centre, E (unaligned
-                    // LDS reads cost more than the funnel shift)
-                    const int x0 = lr * RWP + lc - 1;
-                    const uint32_t* w = reinterpret_cast<const uint32_t*>(s_img) + (x0 >> 2);
-                    uint32_t row[3];
+                    const int x0 = o - 1;
+                    const uint32_t* row = reinterpret_cast<const uint32_t*>(s_img) + (x0 >> 2);
 #pragma unroll
-                    for (int y = 0; y < 3; ++y)
-                        row[y] = __builtin_amdgcn_alignbyte(w[(y - 1) * (RWP / 4) + 1],
-                                                            w[(y - 1) * (RWP / 4)], x0 & 3);
-                    q = ring_of_bytes(row[0], row[1], row[2]);
+                    for (int y = 0; y < 6; ++y) w[y] = row[(y / 2 - 1) * (RWP / 4) + (y & 1)];
+                    asm("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]));
+                    // (unaligned LDS reads cost more than the funnel shift)
+                    q = ring_of_bytes(__builtin_amdgcn_alignbyte(w[1], w[0], x0 & 3),
+                                      __builtin_amdgcn_alignbyte(w[3], w[2], x0 & 3),
+                                      __builtin_amdgcn_alignbyte(w[5], w[4], x0 & 3));
                 } else {
-                    // aligned words: an even column is the third of its four pixels
-                    const uint32_t* w = reinterpret_cast<const uint32_t*>(p - (sj ? 1 : 2));
-                    q = ring_of_words<sj == 0>(w[-RWP / 2], w[-RWP / 2 + 1], w[0], w[1],
-                                               w[RWP / 2], w[RWP / 2 + 1]);
+                    // an even column is the third of its four pixels
+                    const uint32_t* row = reinterpret_cast<const uint32_t*>(s_img + o - (sj ? 1 : 2));
+#pragma unroll
+                    for (int y = 0; y < 6; ++y) w[y] = row[(y / 2 - 1) * (RWP / 2) + (y & 1)];
+                    asm("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]));
+                    q = ring_of_words<sj == 0>(w[0], w[1], w[2], w[3], w[4], w[5]);
                 }
-                uint32_t alpha;
-                if (decide(q, lut, lambda, alpha)) {
-                    p[0] = (E)alpha;
-                    lowered = true;
+                const Verdict v = weigh(q, lut, lambda);
+                const uint64_t low =
+                    __ballot(i < total) & __ballot(v.near >= v.need) & __ballot(v.contrast1 < v.reach);
+                if (low == 0) continue;
+                lowered = true;
+                // in the tile's interior, as one compare per axis
+                const uint64_t in = low & __ballot((uint32_t)(a - K / 2) < (uint32_t)(TH / 2)) &
+                                    __ballot((uint32_t)(b - K / 2) < (uint32_t)(TW / 2));
+                if (__builtin_amdgcn_inverse_ballot_w64(low)) {
+                    s_img[o] = (E)v.alpha;
                     atomicOr(&s_dl[c * CLASS_WORDS + a * LWW + (b >> 5)], 1u << (b & 31));
-                    if (lr >= K && lr < K + TH && lc >= K && lc < K + TW) {
-                        ++my_count;
-                        inner = true;
-                        if constexpr (SEED) {
-                            if (tau >= nsteps - 4) {
-                                const int y = lr - K, x = lc - K;
-                                atomicOr(&s_bits[y * WPR + (x >> 5)], 1u << (x & 31));
-                            }
-                        }
-                    }
                 }
+                my_count += __popcll(in);
+                my_last = in != 0 ? tau : my_last;
             }
-            // one store per wave (the lanes would all write the same byte)
-            if (__ballot(lowered) != 0ull && lane == 0) s_low[tau & 7] = 1;
-            if (inner) my_last = tau;
+            my_exams += total;
+            if (lowered && lane == 0) s_low[tau & 7] = 1;
             __syncthreads();
         };
         using C0 = std::integral_constant<int, 0>;
@@ -1638,15 +1697,34 @@ struct BTile {
         }
 
         store(d, gy0, gx0, src, dst, s_img, tid);
-        block_counts(my_count, my_last, my_exams, s_count, s_last, s_exam, tid);
-        __syncthreads();
-        if constexpr (SEED) {
-            if (sd != nullptr) {
-                for (int i = tid; i < TH * WPR; i += NT)
-                    sd->cur_bits[(int64_t)sd->g * TH * WPR + i] = s_bits[i];
-                if (tid == 0) sd->cur_round[sd->g] = sd->r;
+        if (lane == 0) {
+            if (my_count) {
+                atomicAdd(s_count, my_count);
+                atomicMax(s_last, my_last);
             }
+            if (wave == 0) *s_exam = my_exams;
         }
+        if constexpr (SEED) {
+            // The interior pixels lowered during the last 4 steps, in pixel
+            // order: exactly what the lowered bitmaps hold now (one step of
+            // each class; a skipped step's class lowered nothing in its last
+            // one).  Word w of interior row y: 16 cells from column K/2 + 16w.
+            uint32_t* out = list_words(s_flags);
+            for (int i = tid; i < TH * WPR; i += NT) {
+                const int y = i / WPR, w = i - y * WPR;
+                const int a = (K + y) >> 1, b0 = K / 2 + 16 * w, j = b0 >> 5, sh = b0 & 31;
+                const uint32_t* even = s_dl + (2 * (y & 1)) * CLASS_WORDS + a * LWW + j;
+                const uint32_t* odd = even + CLASS_WORDS;
+                // 16 bits from bit sh of word j (and its successor)
+                const uint32_t e = (uint32_t)((((uint64_t)even[1] << 32) | even[0]) >> sh);
+                const uint32_t o = (uint32_t)((((uint64_t)odd[1] << 32) | odd[0]) >> sh);
+                const uint32_t bits = spread_bits(e) | spread_bits(o) << 1;
+                out[i] = bits;
+                if (sd != nullptr) sd->cur_bits[(int64_t)sd->g * TH * WPR + i] = bits;
+            }
+            if (sd != nullptr && tid == 0) sd->cur_round[sd->g] = sd->r;
+        }
+        __syncthreads();
         last_tau = *s_last;
         return *s_count;
     }
@@ -1817,9 +1895,10 @@ __device__ __forceinline__ int round_tile(const ImgDev* __restrict__ imgs, ImgCn
             uint32_t ask = 0x1FFu;  // bit 3 (dy + 1) + (dx + 1)
             if constexpr (var_seeded(VAR)) {
                 if (nsteps >= 4) {
+                    const uint32_t* bits = T::changed(s_dirty, s_bits);
                     int rmin = TH, rmax = -1, cmin = TW, cmax = -1;
                     for (int i = tid; i < TH * T::WPR; i += 64) {
-                        const uint32_t w = s_bits[i];
+                        const uint32_t w = bits[i];
                         if (!w) continue;
                         const int row = i / T::WPR, c0 = 32 * (i - row * T::WPR);
                         rmin = min(rmin, row);
@@ -2763,8 +2842,7 @@ static int lds_bytes(TileShape s)
                          : 8;
     if (s.var == kVarBits || s.var == kVarBitsSeeded) {
         const int lat_h = (s.th + 2 * s.k) / 2, lat_w = (s.tw + 2 * s.k) / 2;
-        const int flags = 16 * lat_h * ((lat_w + 31) / 32) + 2 * lat_h * lat_w + 64;
-        return region * 2 + flags + hist + 2048 + 64;
+        return region * 2 + 16 * lat_h * ((lat_w + 31) / 32) + 2 * lat_h * lat_w + 128 + 2048 + 64;
     }
     return region * 3 + hist + 2048 + 64;
 }

@@ -494,6 +494,31 @@ int chunk_graph(thin_ctx* ctx, const std::vector<uint64_t>& key, F record, hipGr
 
 int launch_worklists(thin_ctx* ctx, std::vector<thin::WlImg>& wl, std::vector<int32_t>& steps,
                      ImgCnt* d_cnt);
+int choose_flow(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work, double waves);
+int run_flow(thin_ctx* ctx, int which, const thin_image* ims, const std::vector<int>& work,
+             thin_stats* stats, std::vector<int>& rest);
+
+// Several images go to the small-image engine when their tiles are at most
+// this many times what is resident at once: at the start of a call, or (the
+// images still unstable) after some rounds.  Small images have long tails,
+// which cost the rounds of launches 40 us and more per 16 steps for a handful
+// of tiles and cost the engine 10.  96 mixed images of sides 64..640 (6
+// Mpixel, up to 580 passes), in ms with the bound 0, 1, 2, 4, 8: 12.3, 3.4,
+// 3.9, 3.0, 2.9; the same sizes all u8 leveling (up to 76 passes): 1.74, 1.53,
+// 1.53, 1.22, 1.44; 30 of sides 64..1500: 1.45, 1.29, 1.30, 1.30, 1.54; 150
+// mixed of sides 64..1500 (29 Mpixel): 7.5, 4.9, 4.7, 4.7, 4.9.
+constexpr double kFlowWaves = 4.0;
+
+// Images a tiled run leaves to the small-image engine: not yet stable after an
+// even number of rounds (so their states are in the callers' buffers), few
+// enough of them that their tiles are resident together or nearly so.
+struct Handover {
+    const thin_image* ims;     // the caller's images
+    const int* src_index;      // image i of the run is ims[src_index[i]]
+    std::vector<int> images;   // handed over (indices into ims); empty: none
+    std::vector<ImgCnt> cnt;   // their counters so far
+    int steps = 0;             // steps they have run (a multiple of 4)
+};
 
 // Longest chunk of rounds launched between two counter reads.  A run stops
 // at most one chunk past stability, so long chunks cost extra rounds; short
@@ -544,9 +569,11 @@ struct TiledBufs {
 // or at its step cap, brings every image's state home into its own buffer
 // and fills the statistics (stats[src_index[i]] for image i; src_index may
 // be null for the identity).  allocate: graphs and profiling events may be
-// created (the no-allocation entry point passes false).
+// created (the no-allocation entry point passes false).  hand (nullable): may
+// leave the last images to the small-image engine.
 int drive_tiled(thin_ctx* ctx, TileShape shape, const ImgDev* h_imgs, int nimg, int ntiles,
-                const TiledBufs& b, const int* src_index, thin_stats* stats, bool allocate)
+                const TiledBufs& b, const int* src_index, thin_stats* stats, bool allocate,
+                Handover* hand)
 {
     const int K = shape.k;
     int max_steps_all = 0;
@@ -580,6 +607,14 @@ int drive_tiled(thin_ctx* ctx, TileShape shape, const ImgDev* h_imgs, int nimg, 
         }
         return true;
     };
+    // the caller's images not stable after `rounds` rounds
+    auto unstable = [&](const ImgCnt* snap, int rounds) {
+        std::vector<int> out;
+        for (int i = 0; i < nimg; ++i)
+            if (snap[i].last_step >= rounds * K - 4) out.push_back(hand->src_index[i]);
+        return out;
+    };
+    bool to_flow = false;
     const int kflags = thin::kStateIsTile | (nimg == 1 ? thin::kOneImage : 0);
     int dtypes = 0;
     for (int i = 0; i < nimg; ++i) dtypes |= h_imgs[i].dtype == THIN_U8 ? 1 : 2;
@@ -660,6 +695,11 @@ int drive_tiled(thin_ctx* ctx, TileShape shape, const ImgDev* h_imgs, int nimg, 
         if (pending >= 0) {
             HIP_TRY(ctx, hipEventSynchronize(ctx->ev[pending]));
             if (all_done(ctx->h_snap[pending], pending_rounds)) {
+                done = true;
+            } else if (hand && launched % 2 == 0 &&
+                       choose_flow(ctx, hand->ims, unstable(ctx->h_snap[pending], pending_rounds),
+                                   kFlowWaves) >= 0) {
+                to_flow = true;
                 done = true;
             } else if (tail_ok) {
                 const unsigned long long low = ctx->h_snap[pending][0].lowerings;
@@ -747,8 +787,14 @@ int drive_tiled(thin_ctx* ctx, TileShape shape, const ImgDev* h_imgs, int nimg, 
     ctx->last_launches = launched;
 
     bool limited = false;
+    if (to_flow) hand->steps = launched * K;
     for (int i = 0; i < nimg; ++i) {
         const ImgDev& d = h_imgs[i];
+        if (to_flow && fin[i].last_step >= launched * K - 4) {
+            hand->images.push_back(hand->src_index[i]);
+            hand->cnt.push_back(fin[i]);
+            continue;
+        }
         thin_stats st;
         fill_stats(&st, fin[i], steps_done[i], d.max_steps, false);
         if (!st.converged) limited = true;
@@ -781,7 +827,8 @@ ImgDev describe_tiled(const thin_image& im, TileShape shape, void* twin, int32_t
     return d;
 }
 
-int run_tiled(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work, thin_stats* stats)
+int run_tiled(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work, thin_stats* stats,
+              bool hand_over = false)
 {
     int64_t total_px = 0;
     for (int i : work) total_px += ims[i].h * ims[i].w;
@@ -844,8 +891,32 @@ int run_tiled(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work
                                 hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(ctx, hipMemcpyAsync(b.tile_img, plan.tile_img.data(), sizeof(int32_t) * ntiles,
                                 hipMemcpyHostToDevice, ctx->stream));
-    return drive_tiled(ctx, shape, plan.imgs.data(), nimg, ntiles, b, plan.src_index.data(), stats,
-                       true);
+    Handover hand{ims, plan.src_index.data(), {}, {}, 0};
+    rc = drive_tiled(ctx, shape, plan.imgs.data(), nimg, ntiles, b, plan.src_index.data(), stats,
+                     true, hand_over ? &hand : nullptr);
+    if (rc || hand.images.empty()) return rc;
+    // The last images, from their states in the callers' buffers; what the
+    // small-image engine cannot take goes on in rounds.
+    const int launches = ctx->last_launches;
+    std::vector<thin_stats> late(*std::max_element(hand.images.begin(), hand.images.end()) + 1);
+    std::vector<int> rest;
+    const int flow = choose_flow(ctx, ims, hand.images, kFlowWaves);
+    rc = flow >= 0 ? run_flow(ctx, flow, ims, hand.images, late.data(), rest) : THIN_ENOMEM;
+    if (rc == THIN_ENOMEM) rest = hand.images;
+    else if (rc) return rc;
+    if (!rest.empty() && (rc = run_tiled(ctx, ims, rest, late.data()))) return rc;
+    ctx->last_launches += launches;
+    for (size_t k = 0; stats && k < hand.images.size(); ++k) {
+        const ImgCnt& c = hand.cnt[k];
+        thin_stats st = late[hand.images[k]];
+        st.passes = st.lowerings ? st.passes + (uint64_t)(hand.steps / 4)
+                                 : (c.last_step < 0 ? 1 : (uint64_t)(c.last_step / 4) + 2);
+        st.lowerings += c.lowerings;
+        st.tile_rounds += c.tile_rounds;
+        st.examinations += c.examinations;
+        stats[hand.images[k]] = st;
+    }
+    return THIN_OK;
 }
 
 // --------------------------------------------------------- small-image engine
@@ -858,6 +929,7 @@ int run_tiled(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work
 // 512x512, four to a unit: 1675 against 1404).
 constexpr thin::FlowShape kFlowShapes[] = {
     {16, 16, 8, 256}, {24, 48, 8, 640}, {48, 48, 8, 1024}, {128, 48, 8, 768}, {176, 48, 8, 1024}};
+constexpr int kFlowQueued = 2;  // first shape used for more tiles than are resident at once
 
 int flow_tiles(const thin_image& im, thin::FlowShape s, int& tx, int& ty)
 {
@@ -867,16 +939,20 @@ int flow_tiles(const thin_image& im, thin::FlowShape s, int& tx, int& ty)
     return (int)std::min<int64_t>((int64_t)tx * ty, INT_MAX / 2);
 }
 
-// The small-image engine's shape (index) for these images, -1 for none.
-int choose_flow(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work)
+// The small-image engine's shape (index) for these images, -1 for none: the
+// first shape whose tiles are all resident at once, or with several images
+// one that each image fits and whose tiles are at most `waves` times what is
+// resident (blocks take the tiles of later images as earlier ones finish).
+int choose_flow(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work, double waves)
 {
     if (ctx->engine != THIN_ENGINE_TILED || ctx->forced.th || ctx->graph || ctx->tail ||
-        ctx->max_passes || ctx->flow_side == 0)
+        ctx->max_passes || ctx->flow_side == 0 || work.empty())
         return -1;
     int64_t total_px = 0;
     for (int i : work) total_px += ims[i].h * ims[i].w;
     const auto cls = size_class(total_px, (int64_t)work.size());
     if (ctx->tuned.count(cls) && !ctx->tuned_flow.count(cls)) return -1;
+    int several = -1;
     for (int k = 0; k < (int)std::size(kFlowShapes); ++k) {
         if (ctx->flow_side > 0 && k + 1 != ctx->flow_side) continue;
         const thin::FlowShape s = kFlowShapes[k];
@@ -884,14 +960,19 @@ int choose_flow(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& wo
         const int64_t fit = k == 0 && ctx->flow_side < 0 ? std::min(ctx->flow_cap[k], ctx->num_cus)
                                                         : ctx->flow_cap[k];
         int64_t tiles = 0;
+        bool each = true;
         for (int i : work) {
             int tx, ty;
-            tiles += flow_tiles(ims[i], s, tx, ty);
-            if (tiles > fit) break;
+            const int t = flow_tiles(ims[i], s, tx, ty);
+            each = each && t <= fit;
+            tiles += t;
         }
         if (tiles <= fit) return k;
+        // (from 48x48 on: the smaller tiles pay for their halos when blocks
+        // queue)
+        if (several < 0 && k >= kFlowQueued && each && (double)tiles <= waves * (double)fit) several = k;
     }
-    return -1;
+    return several;
 }
 
 // Device memory of a run of the small-image engine.
@@ -1316,7 +1397,7 @@ int run_images(thin_ctx* ctx, const thin_image* ims, int n, thin_stats* stats)
     if (ctx->engine == THIN_ENGINE_STEP) return run_step_engine(ctx, ims, work, stats);
     if (ctx->engine == THIN_ENGINE_WORKLIST) return run_worklist(ctx, ims, work, stats);
     if (ctx->engine == THIN_ENGINE_COOP) return run_coop(ctx, ims, work, stats);
-    const int flow = choose_flow(ctx, ims, work);
+    const int flow = choose_flow(ctx, ims, work, kFlowWaves);
     if (flow >= 0) {
         std::vector<int> rest;
         const int rc = run_flow(ctx, flow, ims, work, stats, rest);
@@ -1326,7 +1407,7 @@ int run_images(thin_ctx* ctx, const thin_image* ims, int n, thin_stats* stats)
         if (rc != THIN_OK && rc != THIN_ENOMEM) return rc;
         if (rc == THIN_OK) work.swap(rest);
     }
-    return run_tiled(ctx, ims, work, stats);
+    return run_tiled(ctx, ims, work, stats, true);
 }
 
 // One tiled run over `work` of ims with `shape` forced; wall time in ms
@@ -1449,7 +1530,7 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
             // the small-image engine stays the choice of these images where
             // it beats the best tile shape
             ctx->tuned_flow.insert(cls);
-            const int flow = choose_flow(ctx, work_img.data(), work);
+            const int flow = choose_flow(ctx, work_img.data(), work, kFlowWaves);
             bool faster = false;
             for (int k = 0; flow >= 0 && k < 2 && rc == THIN_OK; ++k) {
                 std::vector<int> rest;
@@ -1501,7 +1582,7 @@ int run_noalloc(thin_ctx* ctx, const thin_image& im, thin_stats* stats)
     if (!ctx->noalloc || ctx->h_snap_cap < 1)
         return fail(ctx, THIN_EDEVICE, "the static scratch array was not set up by thin_create");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    const int flow = choose_flow(ctx, &im, {0});
+    const int flow = choose_flow(ctx, &im, {0}, 1.0);
     if (flow >= 0) {
         std::vector<thin::FlowImg> imgs;
         std::vector<int32_t> tile_img;
@@ -1561,7 +1642,7 @@ int run_noalloc(thin_ctx* ctx, const thin_image& im, thin_stats* stats)
     b.small = reinterpret_cast<int32_t*>(base + o_small);
     const ImgDev d = describe_tiled(im, shape, base + o_twin, 0, 0, steps_cap(ctx));
     HIP_TRY(ctx, thin::launch_set_desc(ctx->stream, b.imgs, d));
-    return drive_tiled(ctx, shape, &d, 1, (int)ntiles, b, nullptr, stats, false);
+    return drive_tiled(ctx, shape, &d, 1, (int)ntiles, b, nullptr, stats, false, nullptr);
 }
 
 }  // namespace

@@ -113,3 +113,28 @@ def test_scratch_cap_and_noalloc():
                                      raw) == thin.THIN_OK
     torch.cuda.synchronize()
     assert_image(t, thin.Stats.of(raw), ref)
+
+
+@pytest.mark.parametrize("polls", ["", ",0"], ids=["taken", "given_up"])
+def test_last_images_handed_over(polls, monkeypatch):
+    """A batch too large for the engine starts on the rounds of launches and
+    leaves its last images to it (here 1092 tiles, 512 of them resident at
+    most), or goes on in rounds when the engine gives up."""
+    monkeypatch.setenv("THIN_FLOW", "2" + polls)
+    imgs, lams, adjs, ops = [], [], [], []
+    for i in range(12):
+        dt = np.uint8 if i % 3 else np.uint16
+        if i < 3:  # the long runs
+            imgs.append(synth.gen_ridges(300, 300, 40 + i, dt))
+        else:
+            imgs.append(image(300, 300 - i, 600 + i, dt))
+        lams.append((0, 12, 40)[i % 3] * (1 if i % 3 else 257))
+        adjs.append(["8,4", "4,8"][i % 2])
+        ops.append(["leveling", "skeleton"][(i // 2) % 2])
+    refs = [oracle.sweep_dirty(F, l, a, op=o) for F, l, a, o in zip(imgs, lams, adjs, ops)]
+    assert max(r.passes for r in refs) > 2 * min(r.passes for r in refs)
+    ts = [torch.from_numpy(F.copy()).cuda() for F in imgs]
+    print("case hand-over", polls, [r.passes for r in refs], flush=True)
+    with thin.Context() as ctx:
+        for t, st, ref in zip(ts, ctx.run_batch(ts, lams, adjs, ops=ops), refs):
+            assert_image(t, st, ref)

@@ -11,14 +11,15 @@
 // steady state of that constant extension.
 //
 // Each of the four recursions of a pass (causal and anticausal, smoothing
-// and derivative) runs in its own thread, one thread per column (coalesced
-// across a wave; columns of up to 1024 samples split into segments, below)
-// or per row, writing its own plane; the row pass adds the two halves of
-// its input as it reads them, and a last elementwise pass adds the halves
-// of gx and gy and stores the result.  Every product and sum is rounded on
-// its own, in the association order written below (no contraction into
-// fused multiply-adds), so the float32 result is reproducible bit for bit
-// on a given image size.
+// and derivative) is one lane's chain along its line.  A block holds whole
+// lines in LDS (k_grad_cols_lds, k_grad_rows_lds), adds the two halves of each
+// result there and, in the row pass, stores the final values; columns of up
+// to 1024 samples run split into segments instead (k_grad_cols_seg), and
+// lines too long for LDS run from global memory, one thread per recursion,
+// each writing its own plane (k_grad_cols, k_grad_rows, k_grad_out).  Every
+// product and sum is rounded on its own, in the association order written
+// below (no contraction into fused multiply-adds), so the float32 result is
+// reproducible bit for bit on a given image size.
 #include "thin_internal.h"
 
 #pragma clang fp contract(off)
@@ -75,10 +76,11 @@ struct ColLine {
     __device__ __forceinline__ float operator()(int n) const { return (float)col[(int64_t)n * pitch]; }
 };
 
+template <bool HALVES>
 struct SumLine {
-    const float* u;
-    const float* v;
-    __device__ __forceinline__ float operator()(int n) const { return u[n] + v[n]; }
+    const float* u;   // the sum, or with HALVES one half of it
+    const float* v;   // the other half
+    __device__ __forceinline__ float operator()(int n) const { return HALVES ? u[n] + v[n] : u[n]; }
 };
 
 // One recursion along a line of n samples: kind 0 smoothing causal, 1
@@ -142,8 +144,9 @@ __global__ __launch_bounds__(kGradThreads) void k_grad_cols(const T* __restrict_
 
 // Row pass: blockIdx.y picks gx+ (derivative causal of A), gx- (derivative
 // anticausal of A), gy+ (smoothing causal of B) or gy- (smoothing
-// anticausal of B), one thread per row.  Planes in: A+, A-, B+, B-; out:
-// gx+, gx-, gy+, gy-.
+// anticausal of B), one thread per row.  Planes in: A and B, or with HALVES A+,
+// A-, B+, B-; out: gx+, gx-, gy+, gy-.
+template <bool HALVES>
 __global__ __launch_bounds__(kGradThreads) void k_grad_rows(const float* __restrict__ in,
                                                             int h, int w, int64_t plane,
                                                             float* __restrict__ out, GradCoef co)
@@ -152,8 +155,8 @@ __global__ __launch_bounds__(kGradThreads) void k_grad_rows(const float* __restr
     if (i >= h || w <= 0) return;
     const int k = blockIdx.y;
     const int64_t row = (int64_t)i * w;
-    const float* u = in + (k < 2 ? 0 : 2 * plane) + row;
-    const SumLine line{u, u + plane};
+    const float* u = in + (k < 2 ? 0 : (HALVES ? 2 : 1) * plane) + row;
+    const SumLine<HALVES> line{u, u + plane};
     float* o = out + (int64_t)k * plane + row;
     switch (k) {
     case 0: run_line<2>(co, line, w, o, 1); break;
@@ -161,6 +164,228 @@ __global__ __launch_bounds__(kGradThreads) void k_grad_rows(const float* __restr
     case 2: run_line<0>(co, line, w, o, 1); break;
     default: run_line<1>(co, line, w, o, 1); break;
     }
+}
+
+// ------------------------------------------------------- lines held in LDS
+//
+// A recursion's chain runs on one wave, and a lone wave issues an instruction
+// about every 8 cycles, so what bounds a line is the instructions a sample
+// takes on its chain: 14 from global memory (load, conversion, addresses, the
+// input's products), with every 16 samples waiting for their loads. Here a
+// block's threads first compute the input terms of all four recursions of its
+// lines into LDS, coalesced and with many loads in flight, then the first wave
+// runs the chains, four lanes to a line, in place (two products, two sums and
+// half an LDS access a sample, 16 bytes at a time), then all threads add the
+// directions and store.  1601 x 1283 u8 in, u16 and float out: 184 to 89 us a
+// call (column pass 42, row pass with the output 32); 512 x 512: row pass and
+// output 28 to 14 us.  The bits are those of the passes from global memory.
+
+constexpr int kLdsThreads = 1024;
+constexpr size_t kLdsBytes = 160 * 1024 - 1024;   // dynamic LDS a block may ask for
+
+// Floats of one recursion's line in LDS: a multiple of 4, and an odd multiple,
+// so that the lanes' 16-byte accesses spread over the banks.
+__host__ __device__ inline int chain_floats(int n)
+{
+    const int quads = (n + 3) / 4;
+    return 4 * (quads | 1);
+}
+
+constexpr size_t kChainSlack = 128;  // bytes of LDS behind a block's last line
+
+// y = (t + b1 s1) + b2 s2 over the n terms at `line`, in place, in the
+// recursion's own order; s: the steady state of the edge.
+__device__ __forceinline__ void run_chain(const GradCoef& co, float4* line, int n, float s)
+{
+    const int quads = (n + 3) / 4;
+    float s1 = s, s2 = s;
+    auto step = [&](float t) __attribute__((always_inline)) {
+        const float y = (t + co.b1 * s1) + co.b2 * s2;
+        s2 = s1;
+        s1 = y;
+        return y;
+    };
+    // 4 quads a turn, the next ones read ahead (the lanes' common trip count,
+    // so nothing but the chain is in the loop); past the line's end the reads
+    // stay in the block's LDS (kChainSlack) and are not used
+    auto four = [&](float4 t) __attribute__((always_inline)) {
+        float4 y;
+        y.x = step(t.x);
+        y.y = step(t.y);
+        y.z = step(t.z);
+        y.w = step(t.w);
+        return y;
+    };
+    float4 t[4];
+    int k = 0;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) t[g] = line[g];
+    for (; k + 4 <= quads; k += 4) {
+        float4 next[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) next[g] = line[k + 4 + g];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) line[k + g] = four(t[g]);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) t[g] = next[g];
+    }
+    for (; k < quads; ++k) line[k] = four(line[k]);
+}
+
+// Floats of a column's four lines, and 4 more to spread the columns over the
+// banks.
+__host__ __device__ inline int column_floats(int h) { return 4 * chain_floats(h) + 4; }
+
+// Column pass: `per` columns a block, the lines of a column: smoothing
+// causal, smoothing anticausal (reversed), derivative causal, derivative
+// anticausal (reversed).  Planes: out (A), out + plane (B).
+template <typename T>
+__global__ __launch_bounds__(kLdsThreads) void k_grad_cols_lds(const T* __restrict__ src, int64_t pitch,
+                                                               int h, int w, int per,
+                                                               float* __restrict__ out, int64_t plane,
+                                                               GradCoef co)
+{
+    extern __shared__ float4 lds4[];
+    float* lds = reinterpret_cast<float*>(lds4);
+    const int tid = threadIdx.x;
+    const int j0 = blockIdx.x * per, n = min(per, w - j0);
+    const int len = chain_floats(h);
+    // neighbouring lanes take neighbouring columns (4, 8 or 16 lanes to a row)
+    const int shift = per <= 4 ? 2 : (per <= 8 ? 3 : 4);
+    const int c = tid & ((1 << shift) - 1), rows = kLdsThreads >> shift;
+    float* const mine = lds + c * column_floats(h);
+    if (c < n)
+        for (int i = 4 * (tid >> shift); i < h; i += 4 * rows) {
+            // samples i - 1 .. i + 5 of the column, edges repeated
+            const T* col = src + j0 + c;
+            float x[7];
+#pragma unroll
+            for (int k = 0; k < 7; ++k) x[k] = (float)col[(int64_t)min(max(i - 1 + k, 0), h - 1) * pitch];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (i + k >= h) break;
+                mine[i + k] = co.a0 * x[k + 1] + co.a1 * x[k];
+                mine[len + h - 1 - i - k] = co.a2 * x[k + 2] + co.a3 * x[k + 3];
+                mine[2 * len + i + k] = co.d1 * x[k];
+                mine[3 * len + h - 1 - i - k] = co.d2 * x[k + 2];
+            }
+        }
+    __syncthreads();
+    if (tid < 4 * n) {
+        const bool causal = (tid & 1) == 0, smooth = (tid & 2) == 0;
+        const float edge = (float)src[(int64_t)(causal ? 0 : h - 1) * pitch + j0 + (tid >> 2)];
+        const float st = causal ? (smooth ? co.s_plus : co.d_plus) : (smooth ? co.s_minus : co.d_minus);
+        run_chain(co, lds4 + ((tid >> 2) * column_floats(h) + (tid & 3) * len) / 4, h, edge * st);
+    }
+    __syncthreads();
+    if (c < n)
+        for (int i = tid >> shift; i < h; i += rows) {
+            float* a = out + (int64_t)i * w + j0 + c;
+            a[0] = mine[i] + mine[len + h - 1 - i];
+            a[plane] = mine[2 * len + i] + mine[3 * len + h - 1 - i];
+        }
+}
+
+// Row pass and output: `per` rows a block, the lines of row r at 4r:
+// derivative of A causal and anticausal, smoothing of B causal and
+// anticausal.  Planes in: A and B, or with HALVES A+, A-, B+, B-.
+template <typename T, bool HALVES>
+__global__ __launch_bounds__(kLdsThreads) void k_grad_rows_lds(const float* __restrict__ in, int h, int w,
+                                                               int per, int64_t plane,
+                                                               T* __restrict__ dst, int64_t dst_pitch,
+                                                               float* __restrict__ mag, float gain,
+                                                               float top, GradCoef co)
+{
+    extern __shared__ float4 lds4[];
+    float* lds = reinterpret_cast<float*>(lds4);
+    const int tid = threadIdx.x;
+    const int i0 = blockIdx.x * per, n = min(per, h - i0);
+    const int len = chain_floats(w);
+    auto at_a = [&](const float* row, int j) __attribute__((always_inline)) {
+        return HALVES ? row[j] + row[plane + j] : row[j];
+    };
+    auto at_b = [&](const float* row, int j) __attribute__((always_inline)) {
+        return HALVES ? row[2 * plane + j] + row[3 * plane + j] : row[plane + j];
+    };
+    for (int j = tid; j < w; j += kLdsThreads) {
+        const int jp = max(j - 1, 0), j1 = min(j + 1, w - 1), j2 = min(j + 2, w - 1);
+#pragma unroll 2
+        for (int r = 0; r < n; ++r) {
+            const float* row = in + (int64_t)(i0 + r) * w;
+            float* t = lds + 4 * r * len;
+            t[j] = co.d1 * at_a(row, jp);
+            t[len + w - 1 - j] = co.d2 * at_a(row, j1);
+            t[2 * len + j] = co.a0 * at_b(row, j) + co.a1 * at_b(row, jp);
+            t[3 * len + w - 1 - j] = co.a2 * at_b(row, j1) + co.a3 * at_b(row, j2);
+        }
+    }
+    __syncthreads();
+    if (tid < 4 * n) {
+        const bool causal = (tid & 1) == 0, smooth = (tid & 2) != 0;
+        const float* row = in + (int64_t)(i0 + (tid >> 2)) * w;
+        const int e = causal ? 0 : w - 1;
+        const float edge = smooth ? at_b(row, e) : at_a(row, e);
+        const float st = causal ? (smooth ? co.s_plus : co.d_plus) : (smooth ? co.s_minus : co.d_minus);
+        run_chain(co, lds4 + tid * (len / 4), w, edge * st);
+    }
+    __syncthreads();
+    for (int j = tid; j < w; j += kLdsThreads) {
+        for (int r = 0; r < n; ++r) {
+            const float* y = lds + 4 * r * len;
+            const float gx = y[j] + y[len + w - 1 - j];
+            const float gy = y[2 * len + j] + y[3 * len + w - 1 - j];
+            const float sq = gx * gx + gy * gy;
+            const float m = sqrtf(sq);
+            if (mag) mag[(int64_t)(i0 + r) * w + j] = m;
+            dst[(int64_t)(i0 + r) * dst_pitch + j] = (T)fminf(rintf(m * gain), top);
+        }
+    }
+}
+
+// Lines a block takes: as many blocks as compute units, or `waves` times that
+// many where LDS holds no more lines (0: even that leaves lines over, and the
+// passes from global memory, which run every line at once, are faster: at 4000
+// x 3000 six waves of column blocks and six of row blocks took 849 us, those
+// 493).
+int lines_per_block(int lines, int floats, int num_cus, int waves)
+{
+    const int most = min(16, (int)(kLdsBytes / (sizeof(float) * (size_t)floats)));
+    const int want = (lines + num_cus - 1) / num_cus;
+    if (most <= 0 || (int64_t)most * num_cus * waves < lines) return 0;
+    return min(want, most);
+}
+
+template <typename F>
+hipError_t allow_lds(F* kernel)
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)(kLdsBytes + kChainSlack));
+}
+
+template <typename T>
+hipError_t launch_cols_lds(hipStream_t stream, const void* src, int64_t pitch, int h, int w, int per,
+                           float* out, int64_t plane, const GradCoef& co)
+{
+    const hipError_t e = allow_lds(&k_grad_cols_lds<T>);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_grad_cols_lds<T>, dim3((w + per - 1) / per), dim3(kLdsThreads),
+                       kChainSlack + sizeof(float) * (size_t)per * column_floats(h), stream,
+                       static_cast<const T*>(src), pitch, h, w, per, out, plane, co);
+    return hipGetLastError();
+}
+
+template <typename T, bool HALVES>
+hipError_t launch_rows_lds(hipStream_t stream, const float* in, int h, int w, int per, int64_t plane,
+                           void* dst, int64_t dst_pitch, float* mag, float gain, float top,
+                           const GradCoef& co)
+{
+    const hipError_t e = allow_lds(&k_grad_rows_lds<T, HALVES>);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_grad_rows_lds<T, HALVES>), dim3((h + per - 1) / per), dim3(kLdsThreads),
+                       kChainSlack + sizeof(float) * (size_t)per * 4 * chain_floats(w), stream, in, h, w, per, plane,
+                       static_cast<T*>(dst), dst_pitch, mag, gain, top, co);
+    return hipGetLastError();
 }
 
 // Columns of at most kSegLen * kSegMax samples also run split into segments
@@ -299,47 +524,71 @@ __global__ __launch_bounds__(256) void k_grad_out(const float* __restrict__ g, i
 
 hipError_t launch_gradient(hipStream_t stream, const void* src, int64_t src_pitch, int src_dtype,
                            int h, int w, float* scratch, void* dst, int64_t dst_pitch,
-                           int dst_dtype, float* mag, GradCoef co, float gain)
+                           int dst_dtype, float* mag, GradCoef co, float gain, int num_cus)
 {
     const int64_t plane = (int64_t)h * w;
-    float* cols = scratch;              // A+, A-, B+, B-
+    float* cols = scratch;              // A+, A-, B+, B- (or A, B)
     float* rows = scratch + 4 * plane;  // gx+, gx-, gy+, gy-
     const dim3 block(kGradThreads);
-    const dim3 gc((w + kGradThreads - 1) / kGradThreads, 4);
-    const dim3 gr((h + kGradThreads - 1) / kGradThreads, 4);
-    // Segmented passes for lines of at most kSegLen * kSegMax samples (a
-    // pass has only 4 x (lines) chains, too few to fill the device); longer
-    // lines run one chain per thread.
+    hipError_t e;
+    // Columns: in segments up to kSegLen * kSegMax samples, else whole in LDS,
+    // else from global memory.
     const int seg_c = (h + kSegLen - 1) / kSegLen;
-    const dim3 sgc((w + 63) / 64, 4);
+    const int num = num_cus > 0 ? num_cus : 1;
+    const int per_c = lines_per_block(w, column_floats(h), num, 1);
+    bool halves = true;
     if (seg_c <= kSegMax) {
+        const dim3 sgc((w + 63) / 64, 4);
         if (src_dtype == 1)
             hipLaunchKernelGGL(k_grad_cols_seg<uint8_t>, sgc, dim3(64, seg_c), 0, stream,
                                static_cast<const uint8_t*>(src), src_pitch, h, w, cols, plane, co);
         else
             hipLaunchKernelGGL(k_grad_cols_seg<uint16_t>, sgc, dim3(64, seg_c), 0, stream,
                                static_cast<const uint16_t*>(src), src_pitch, h, w, cols, plane, co);
-    } else if (src_dtype == 1) {
-        hipLaunchKernelGGL(k_grad_cols<uint8_t>, gc, block, 0, stream,
-                           static_cast<const uint8_t*>(src), src_pitch, h, w, cols, plane, co);
+        e = hipGetLastError();
+    } else if (per_c > 0) {
+        halves = false;
+        e = src_dtype == 1
+                ? launch_cols_lds<uint8_t>(stream, src, src_pitch, h, w, per_c, cols, plane, co)
+                : launch_cols_lds<uint16_t>(stream, src, src_pitch, h, w, per_c, cols, plane, co);
     } else {
-        hipLaunchKernelGGL(k_grad_cols<uint16_t>, gc, block, 0, stream,
-                           static_cast<const uint16_t*>(src), src_pitch, h, w, cols, plane, co);
+        const dim3 gc((w + kGradThreads - 1) / kGradThreads, 4);
+        if (src_dtype == 1)
+            hipLaunchKernelGGL(k_grad_cols<uint8_t>, gc, block, 0, stream,
+                               static_cast<const uint8_t*>(src), src_pitch, h, w, cols, plane, co);
+        else
+            hipLaunchKernelGGL(k_grad_cols<uint16_t>, gc, block, 0, stream,
+                               static_cast<const uint16_t*>(src), src_pitch, h, w, cols, plane, co);
+        e = hipGetLastError();
     }
-    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // (The row pass stays one chain per row: its lanes walk different rows,
-    // and with segments eight times as many waves share each CU's cache
-    // for those scattered lines; measured 24 -> 50 us at 512 x 512.)
-    hipLaunchKernelGGL(k_grad_rows, gr, block, 0, stream, cols, h, w, plane, rows, co);
+    const float top = dst_dtype == 1 ? 255.0f : 65535.0f;
+    const int per_r = lines_per_block(h, 4 * chain_floats(w), num, 3);
+    if (per_r > 0) {
+        if (dst_dtype == 1)
+            return halves ? launch_rows_lds<uint8_t, true>(stream, cols, h, w, per_r, plane, dst,
+                                                           dst_pitch, mag, gain, top, co)
+                          : launch_rows_lds<uint8_t, false>(stream, cols, h, w, per_r, plane, dst,
+                                                            dst_pitch, mag, gain, top, co);
+        return halves ? launch_rows_lds<uint16_t, true>(stream, cols, h, w, per_r, plane, dst,
+                                                        dst_pitch, mag, gain, top, co)
+                      : launch_rows_lds<uint16_t, false>(stream, cols, h, w, per_r, plane, dst,
+                                                         dst_pitch, mag, gain, top, co);
+    }
+    // Rows too long for LDS.
+    const dim3 gr((h + kGradThreads - 1) / kGradThreads, 4);
+    if (halves)
+        hipLaunchKernelGGL(k_grad_rows<true>, gr, block, 0, stream, cols, h, w, plane, rows, co);
+    else
+        hipLaunchKernelGGL(k_grad_rows<false>, gr, block, 0, stream, cols, h, w, plane, rows, co);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const dim3 go((unsigned)((plane + 255) / 256));
     if (dst_dtype == 1)
         hipLaunchKernelGGL(k_grad_out<uint8_t>, go, dim3(256), 0, stream, rows, h, w, plane,
-                           static_cast<uint8_t*>(dst), dst_pitch, mag, gain, 255.0f);
+                           static_cast<uint8_t*>(dst), dst_pitch, mag, gain, top);
     else
         hipLaunchKernelGGL(k_grad_out<uint16_t>, go, dim3(256), 0, stream, rows, h, w, plane,
-                           static_cast<uint16_t*>(dst), dst_pitch, mag, gain, 65535.0f);
+                           static_cast<uint16_t*>(dst), dst_pitch, mag, gain, top);
     return hipGetLastError();
 }
 

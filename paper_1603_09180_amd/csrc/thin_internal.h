@@ -210,7 +210,7 @@ struct GradCoef {
 constexpr int kGradPlanes = 8;
 hipError_t launch_gradient(hipStream_t stream, const void* src, int64_t src_pitch, int src_dtype,
                            int h, int w, float* scratch, void* dst, int64_t dst_pitch,
-                           int dst_dtype, float* mag, GradCoef co, float gain);
+                           int dst_dtype, float* mag, GradCoef co, float gain, int num_cus);
 // Pixel work-list engine (k_worklist): one block per image runs parity
 // steps one after the other, examining only the candidates whose 3x3
 // changed since their last examination.

@@ -1924,7 +1924,8 @@ int thin_gradient(thin_ctx* ctx, const void* src, int64_t h, int64_t w, int64_t 
     if (rc) return rc;
     HIP_TRY(ctx, thin::launch_gradient(ctx->stream, src, src_pitch, src_dtype, (int)h, (int)w,
                                        static_cast<float*>(ctx->grad.ptr), dst, dst_pitch,
-                                       dst_dtype, magnitude, gradient_coef(alpha), gain));
+                                       dst_dtype, magnitude, gradient_coef(alpha), gain,
+                                       ctx->num_cus));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     return THIN_OK;
 }

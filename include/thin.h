@@ -86,8 +86,10 @@ enum {
     THIN_ENGINE_TILED = 1,    /* one launch per round of LDS tiles (several parity steps per
                                  residency, stable tiles skipped); the host checks convergence.
                                  Images whose tiles all fit the device at once run in one
-                                 cooperative launch instead (no pass cap, tile shape, graph
-                                 or tail flag set), tiles exchanging their halos on the device */
+                                 launch instead (no pass cap, tile shape, graph or tail flag
+                                 set), tiles exchanging their halos on the device; such
+                                 launches wait for room on the device, first come first
+                                 served */
     THIN_ENGINE_STEP = 2,     /* one parity step per launch over global memory (simple, slow) */
     /* 3 is not used (permanently unavailable: thin_create refuses it) */
     THIN_ENGINE_COOP = 4,     /* one cooperative launch for the whole run: the tiled engine's

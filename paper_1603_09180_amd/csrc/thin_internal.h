@@ -151,8 +151,8 @@ hipError_t launch_coop(hipStream_t stream, TileShape shape, const ImgDev* imgs, 
                        int kflags);
 bool tile_shape_supported(TileShape s);
 
-// Small-image engine (k_flow): all steps of its images in one cooperative
-// launch, tiles exchanging halos through tagged words.
+// Small-image engine (k_flow): all steps of its images in one launch, tiles
+// exchanging halos through tagged words.
 struct FlowImg {
     void* image;
     int64_t pitch;       // row pitch in elements
@@ -179,11 +179,11 @@ struct FlowRun {
     int32_t* ctl;
     uint64_t* exch;
     int max_polls, max_rounds;
+    int vote_every;           // rounds between votes (a power of two)
 };
 constexpr int kFlowNext = 0, kFlowAbort = 16;  // control words
 constexpr int kFlowCtl = 32;                   // first vote ring
 constexpr int kFlowRing = 1024;
-constexpr int kFlowVote = 4;                   // rounds between votes (a power of two)
 constexpr int kFlowMaxSide = 500;              // tiles across or down an image
 constexpr int kFlowRunning = 0, kFlowStable = 1, kFlowGivenUp = 2;  // marks
 // Exchange words of an image: two copies of one (u8) or two (u16) per 2x2 cell.

@@ -2048,7 +2048,7 @@ void k_coop(const ImgDev* __restrict__ imgs, ImgCnt* cnt,
 
 // ------------------------------------------------------------------ k_flow
 //
-// Small images: the whole run in one cooperative launch, every tile of an
+// Small images: the whole run in one launch, every tile of an
 // image held by a block of its own from its first step to its last, windows
 // in registers and region in LDS.  Nothing is staged between rounds: after K
 // steps a block publishes its interior cells and takes its halo cells from
@@ -2079,7 +2079,7 @@ void k_coop(const ImgDev* __restrict__ imgs, ImgCnt* cnt,
 // after the exchange each window is compared with the region's new values and
 // every candidate next to a difference becomes pending.
 //
-// Convergence.  After every kFlowVote-th round a tile adds one to that round's
+// Convergence.  After every vote_every-th round a tile adds one to that round's
 // votes, and one in the high half when it lowered an interior pixel during
 // the round's last 4 steps (one word, so that neither is seen without the
 // other).  The first tile reads one vote word a round; when all tiles have
@@ -2092,14 +2092,15 @@ void k_coop(const ImgDev* __restrict__ imgs, ImgCnt* cnt,
 //
 // Progress.  Blocks take tiles in order.  Every image before the oldest
 // unfinished one is finished, so its blocks come back for tiles; the oldest
-// unfinished one has at most gridDim.x tiles and all blocks are resident
-// (cooperative launch), so all its tiles get a block and none waits for a
-// tile without one.  Every wait and the number of rounds are bounded all the
-// same: a block that runs out marks its image given up, sets the abort word
-// and leaves, as do all that see either, and the host runs the images that
-// are not stable on the rounds of launches.  An image's mark changes once
-// (compare and swap), and its tiles are stored when it says stable only, so
-// images given up are untouched.
+// unfinished one has at most gridDim.x tiles and all blocks become resident
+// (the grid is no larger than the device holds, other kernels end, and the
+// host lets this process's waiting kernels run together only where all fit),
+// so all its tiles get a block and none waits for a tile without one.  Every
+// wait and the number of rounds are bounded all the same: a block that runs
+// out marks its image given up, sets the abort word and leaves, as do all that
+// see either, and the host runs the images that are not stable on the rounds
+// of launches.  An image's mark changes once (compare and swap), and its tiles
+// are stored when it says stable only, so images given up are untouched.
 
 __device__ __forceinline__ uint64_t flow_load(const uint64_t* p)
 {
@@ -2135,7 +2136,7 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
                                              const int32_t* __restrict__ tile_img, int ntiles,
                                              ImgCnt* cnt, const DecEntry* __restrict__ lut_g,
                                              int32_t* ctl, uint64_t* exch, int max_polls,
-                                             int max_rounds)
+                                             int max_rounds, int vote_every)
 {
     using T = RTile<TH, TW, K, NT, false>;
     constexpr int PPT = T::PPT, RWP = T::RWP;
@@ -2145,6 +2146,7 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
     __shared__ int s_tile, s_act, s_mark, s_count, s_last, s_exam;
     const int tid = threadIdx.x;
     int lut_adj = -1;
+    const int vote_shift = 31 - __clz(vote_every);
     for (;;) {
         if (tid == 0) s_tile = flow_load(&ctl[kFlowAbort]) ? ntiles : atomicAdd(&ctl[kFlowNext], 1);
         __syncthreads();
@@ -2227,8 +2229,8 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
             }
             lds_barrier();  // s_act complete; every read of this round's flags done
             if (tid == 0) {
-                if ((r & (kFlowVote - 1)) == kFlowVote - 1) {
-                    const int v = r / kFlowVote;
+                if ((r & (vote_every - 1)) == vote_every - 1) {
+                    const int v = r >> vote_shift;
                     (void)__hip_atomic_fetch_add(&ring[v & (kFlowRing - 1)], 1 + (s_act << 16),
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     // the word used half a ring ago: every tile is past it
@@ -2247,7 +2249,7 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
                 // words all blocks share are read as seldom as will do)
                 int32_t m = kFlowRunning, votes = 0;
                 if (polls == 0 ? tid < 64 : (polls & 3) == 3) m = flow_load(image_mark);
-                if (counts && polls == 0 && vote * kFlowVote + kFlowVote <= r)
+                if (counts && polls == 0 && (vote + 1) << vote_shift <= r)
                     votes = flow_load(&ring[vote & (kFlowRing - 1)]);
 #pragma unroll
                 for (int k = 0; k < PPT; ++k) {
@@ -2262,7 +2264,7 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
                         // every tile is through that round
                         if (votes >> 16 == 0 && mark == kFlowRunning)
                             mark = flow_mark(image_mark, kFlowStable);
-                        vote = max(vote + 1, r / kFlowVote - 1);
+                        vote = max(vote + 1, (r >> vote_shift) - 1);
                     }
                 }
                 bool wait = false;
@@ -2654,11 +2656,9 @@ int flow_capacity_t(int num_cus)
 template <int TH, int TW, int K, int NT>
 hipError_t launch_flow_t(hipStream_t stream, const FlowRun& r)
 {
-    int ntiles = r.ntiles, max_polls = r.max_polls, max_rounds = r.max_rounds;
-    void* args[] = {(void*)&r.imgs, (void*)&r.tile_img, (void*)&ntiles, (void*)&r.cnt, (void*)&r.lut,
-                    (void*)&r.ctl,  (void*)&r.exch,     (void*)&max_polls, (void*)&max_rounds};
-    return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_flow<TH, TW, K, NT>),
-                                      dim3(r.grid), dim3(NT), args, 0, stream);
+    hipLaunchKernelGGL((k_flow<TH, TW, K, NT>), dim3(r.grid), dim3(NT), 0, stream, r.imgs, r.tile_img,
+                       r.ntiles, r.cnt, r.lut, r.ctl, r.exch, r.max_polls, r.max_rounds, r.vote_every);
+    return hipGetLastError();
 }
 
 }  // namespace

@@ -138,3 +138,39 @@ def test_last_images_handed_over(polls, monkeypatch):
     with thin.Context() as ctx:
         for t, st, ref in zip(ts, ctx.run_batch(ts, lams, adjs, ops=ops), refs):
             assert_image(t, st, ref)
+
+
+def test_several_threads_and_streams():
+    """Each thread runs images of its own on a stream of its own: launches that
+    fit the device together (16x16 tiles), one that fills it (512x512 by 16x16
+    tiles, alone) and a cooperative run."""
+    import threading
+
+    jobs = []
+    for i in range(6):
+        h, w = [(33, 60), (300, 290), (129, 120), (70, 33), (512, 512), (100, 90)][i]
+        F = image(h, w, 900 + i, np.uint8 if i % 2 else np.uint16)
+        lam = 5 if i % 2 else 700
+        jobs.append((F, lam, ["8,4", "4,8"][i % 2], oracle.sweep_dirty(F, lam, ["8,4", "4,8"][i % 2])))
+    wrong = []
+
+    def work(i):
+        F, lam, adj, ref = jobs[i]
+        stream = torch.cuda.Stream()
+        engine = thin.THIN_ENGINE_COOP if i == 5 else thin.THIN_ENGINE_AUTO
+        with torch.cuda.stream(stream), thin.Context(stream=stream, engine=engine) as ctx:
+            src = torch.from_numpy(F).cuda()
+            for rep in range(8):
+                t = src.clone()
+                st = ctx.run(t, lam, adj)
+                if not (np.array_equal(t.cpu().numpy(), ref.image) and
+                        (st.passes, st.lowerings) == (ref.passes, ref.lowerings)):
+                    wrong.append((i, rep))
+
+    print("case flow threads", flush=True)
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(jobs))]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert wrong == []

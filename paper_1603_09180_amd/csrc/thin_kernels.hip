@@ -141,19 +141,39 @@ __device__ __forceinline__ Ring ring_of_words(uint32_t u0, uint32_t u1, uint32_t
 __device__ __forceinline__ uint32_t mask_of(u16x2 b0, u16x2 b1, u16x2 b2, u16x2 b3,
                                             unsigned short scale)
 {
-    const uint32_t m = as_word(b0) | as_word(b1) << 1 | as_word(b2) << 2 | as_word(b3) << 3;
+    const uint32_t m = (as_word(b0) | as_word(b1) << 1) | (as_word(b2) | as_word(b3) << 1) << 2;
     const u16x2 w = {scale, (unsigned short)(16 * scale)};
     return __builtin_amdgcn_udot2(as_pair(m), w, 0u, false);
 }
 
 // A candidate's test in numbers (see DecEntry): it is lowered to alpha (its
-// alpha-) when near >= need and contrast1 < reach.  lut points at the 256
-// entries of the image's adjacency and operator.
+// alpha-) when near >= need and, where its own contrast must be within lambda,
+// contrast1 < reach.  lut points at the 256 entries of the image's adjacency
+// and operator.
 struct Verdict {
     uint32_t near, need;        // counted components within lambda's reach: present, needed
-    uint32_t contrast1, reach;  // v - alpha- - 1, and its bound
+    int32_t own;                // negative: its own contrast must be within lambda too
+    uint32_t contrast1, reach;  // v - alpha- - 1, and its bound (lambda); or
+                                // both subtracted from 65535, the other way round
     uint32_t alpha;
+
+    __device__ __forceinline__ bool lower() const
+    {
+        return near >= need && (own >= 0 || contrast1 < reach);
+    }
+    // The wave's lanes that lower (whole-wave compares and scalar logic: asked
+    // for lower() in one ballot the compiler goes through a register of 0 and 1).
+    __device__ __forceinline__ uint64_t lanes() const
+    {
+        return __ballot(near >= need) & (__ballot(own >= 0) | __ballot(contrast1 < reach));
+    }
 };
+// How many of the components hold a pixel that is not in far.
+__device__ __forceinline__ uint32_t components_near(uint32_t comps, uint32_t far)
+{
+    const uint32_t hit = comps & ~__builtin_amdgcn_perm(0u, far, 0u);
+    return (uint32_t)__popc((((hit & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | hit) & 0x80808080u);
+}
 __device__ __forceinline__ Verdict weigh(const Ring& q, const DecEntry* lut, const Lambda& lam)
 {
     const u16x2 one = pair_of_ones();
@@ -172,15 +192,47 @@ __device__ __forceinline__ Verdict weigh(const Ring& q, const DecEntry* lut, con
     const uint32_t far = mask_of(beyond(d0), beyond(d1), beyond(d2), beyond(d3), 1);
     const u16x2 c = __builtin_elementwise_min(__builtin_elementwise_min(d0 - one, d1 - one),
                                               __builtin_elementwise_min(d2 - one, d3 - one));
-    // counted components that hold a pixel within lambda's reach
-    const uint32_t hit = comps & ~__builtin_amdgcn_perm(0u, far, 0u);
-    const uint32_t nonzero = (((hit & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | hit) & 0x80808080u;
     Verdict v;
-    v.near = (uint32_t)__popc(nonzero);
+    v.near = components_near(comps, far);
     v.need = need & 0xFFu;
     v.contrast1 = min(as_word(c) & 0xFFFFu, as_word(c) >> 16);
-    v.reach = (int32_t)need < 0 ? lam.one : 0x10000u;
+    v.reach = lam.one;
+    v.own = (int32_t)need;
     v.alpha = (as_word(q.v) & 0xFFFFu) - 1u - v.contrast1;
+    return v;
+}
+// The same for pixels and lambda of at most 255.  The differences fit 16 bits
+// with their sign, so one subtraction a pair serves all: its signs are L, the
+// signs after adding lambda the pixels out of reach, and its largest value as
+// an unsigned number is that of the highest lower neighbour.  A permute turns
+// four signs into bytes of 0 or -1, and dot products with the negative powers
+// of two make a mask of them: 32 instructions where weigh() takes 43.  Only the
+// bit-flag tiles hold one pixel type a kernel; the register windows, whose
+// steps are chains of latencies, decide both types by weigh().
+__device__ __forceinline__ Verdict weigh_small(const Ring& q, const DecEntry* lut, const Lambda& lam)
+{
+    const u16x2 x0 = q.p0 - q.v, x1 = q.p1 - q.v, x2 = q.p2 - q.v, x3 = q.p3 - q.v;
+    auto signs = [](u16x2 a, u16x2 b, u16x2 c, u16x2 d) __attribute__((always_inline)) {
+        constexpr uint32_t of_halves = 0x0B0A0908u;  // the sign of each half of both operands
+        const int ab = (int)__builtin_amdgcn_perm(as_word(b), as_word(a), of_halves);
+        const int cd = (int)__builtin_amdgcn_perm(as_word(d), as_word(c), of_halves);
+        // -1 times -1, -16, -2, -32 and -4, -64, -8, -128
+        return (uint32_t)__builtin_amdgcn_sdot4(
+            cd, (int)0x80F8C0FCu, __builtin_amdgcn_sdot4(ab, (int)0xE0FEF0FFu, 0, false), false);
+    };
+    const uint32_t at = signs(x0, x1, x2, x3) * (uint32_t)sizeof(DecEntry);
+    const uint64_t raw = *reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(lut) + at);
+    const uint32_t need = (uint32_t)raw, comps = (uint32_t)(raw >> 32);
+    const u16x2 top2 = __builtin_elementwise_max(__builtin_elementwise_max(x0, x1),
+                                                 __builtin_elementwise_max(x2, x3));
+    const uint32_t top = max(as_word(top2) & 0xFFFFu, as_word(top2) >> 16);
+    Verdict v;
+    v.near = components_near(comps, signs(x0 + lam.two, x1 + lam.two, x2 + lam.two, x3 + lam.two));
+    v.need = need & 0xFFu;
+    v.own = (int32_t)need;
+    v.contrast1 = 0xFFFFu - lam.one;
+    v.reach = top;
+    v.alpha = ((as_word(q.v) & 0xFFFFu) + top) & 0xFFFFu;
     return v;
 }
 __device__ __forceinline__ bool decide(const Ring& q, const DecEntry* lut, const Lambda& lam,
@@ -188,7 +240,7 @@ __device__ __forceinline__ bool decide(const Ring& q, const DecEntry* lut, const
 {
     const Verdict v = weigh(q, lut, lam);
     alpha = v.alpha;
-    return v.near >= v.need && v.contrast1 < v.reach;
+    return v.lower();
 }
 
 __device__ __forceinline__ uint32_t load_px(const void* base, int dtype, int64_t idx)
@@ -1037,7 +1089,7 @@ struct RTile {
             weigh(ring_of_words<sj != 0>(w[2 * ci - 2], w[2 * ci - 1], w[2 * ci], w[2 * ci + 1],
                                          w[2 * ci + 2], w[2 * ci + 3]),
                   lut, lambda);
-        const uint64_t low = act & __ballot(v.near >= v.need) & __ballot(v.contrast1 < v.reach);
+        const uint64_t low = act & v.lanes();
         n.exams += __popcll(act);
         if (low == 0) return 0;
         const bool mine = __builtin_amdgcn_inverse_ballot_w64(low);
@@ -1295,8 +1347,11 @@ struct RTile {
 // steps earlier at the same values.
 //
 // What bounds it: in the dense first round the vector units (97 % of their
-// issue slots; per 64 examinations 76 instructions, per wave and step about
-// 300 for gather and list), later the chain of a tile's few busy steps.
+// issue slots; per 64 examinations 58 instructions in 16 bits and 51 in 8, per
+// wave and step about 170 for gather and list), later the chain of a tile's
+// few busy steps.  (63 and 67 with the 16-bit decision for both and lanes'
+// verdicts joined in registers: 512 images, 162 Mpx in all, in 8 bits 6.72 ms,
+// now 6.35; 8192x8192 in 16 bits 1.554, now 1.518.)
 template <int TH, int TW, int K, int NT, bool SEED, typename E>
 struct BTile {
     using Elem = E;  // LDS pixel type: the image's own
@@ -1519,7 +1574,7 @@ struct BTile {
         }
         __syncthreads();
 
-        const Lambda lambda = lambda_of(d.lambda);
+        const Lambda lambda = lambda_of(sizeof(E) == 1 ? min(d.lambda, 255u) : d.lambda);
         const uint32_t* own_dl = s_dl + myw;  // word (wa, wj) of class 0's lowered bitmap
         int my_count = 0, my_last = -1;  // the wave's interior lowerings, last step with one
         int my_exams = 0;                // candidates characterised (the block's)
@@ -1636,11 +1691,13 @@ struct BTile {
             const int total = __builtin_amdgcn_readfirstlane(s_total[tau & 7]);
             if (tid == 0) s_total[(tau + 4) & 7] = 0;
             bool lowered = false;
-            int i = tid;
-            int next_cell = s_list[min(i, max(total - 1, 0))];
-            for (int i0 = 64 * wave; i0 < total; i0 += NT, i += NT) {
+            const uint8_t* list = reinterpret_cast<const uint8_t*>(s_list);
+            auto entry = [&](int byte) { return (int)*reinterpret_cast<const uint16_t*>(list + byte); };
+            int at = 2 * tid;  // this lane's entry, in bytes
+            int next_cell = entry(min(at, max(2 * total - 2, 0)));
+            for (int i0 = 64 * wave; i0 < total; i0 += NT, at += 2 * NT) {
                 const int cell = next_cell;
-                next_cell = s_list[min(i + NT, total - 1)];
+                next_cell = entry(min(at + 2 * NT, 2 * total - 2));
                 const int a = cell >> 8, b = cell & 0xFF;
                 const int o = (2 * a + si) * RWP + 2 * b + sj;
                 // the words around W, centre, E of the three rows, all read
@@ -1649,10 +1706,10 @@ struct BTile {
                 uint32_t w[6];
                 Ring q;
                 if constexpr (sizeof(E) == 1) {
-                    const int x0 = o - 1;
+                    const int x0 = o - RWP - 1;  // (addressed from the row above: no negative offset)
                     const uint32_t* row = reinterpret_cast<const uint32_t*>(s_img) + (x0 >> 2);
 #pragma unroll
-                    for (int y = 0; y < 6; ++y) w[y] = row[(y / 2 - 1) * (RWP / 4) + (y & 1)];
+                    for (int y = 0; y < 6; ++y) w[y] = row[(y / 2) * (RWP / 4) + (y & 1)];
                     asm("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]));
                     // (unaligned LDS reads cost more than the funnel shift)
                     q = ring_of_bytes(__builtin_amdgcn_alignbyte(w[1], w[0], x0 & 3),
@@ -1660,15 +1717,15 @@ struct BTile {
                                       __builtin_amdgcn_alignbyte(w[5], w[4], x0 & 3));
                 } else {
                     // an even column is the third of its four pixels
-                    const uint32_t* row = reinterpret_cast<const uint32_t*>(s_img + o - (sj ? 1 : 2));
+                    const uint32_t* row =
+                        reinterpret_cast<const uint32_t*>(s_img + o - RWP - (sj ? 1 : 2));
 #pragma unroll
-                    for (int y = 0; y < 6; ++y) w[y] = row[(y / 2 - 1) * (RWP / 2) + (y & 1)];
+                    for (int y = 0; y < 6; ++y) w[y] = row[(y / 2) * (RWP / 2) + (y & 1)];
                     asm("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]));
                     q = ring_of_words<sj == 0>(w[0], w[1], w[2], w[3], w[4], w[5]);
                 }
-                const Verdict v = weigh(q, lut, lambda);
-                const uint64_t low =
-                    __ballot(i < total) & __ballot(v.near >= v.need) & __ballot(v.contrast1 < v.reach);
+                const Verdict v = sizeof(E) == 1 ? weigh_small(q, lut, lambda) : weigh(q, lut, lambda);
+                const uint64_t low = __ballot(at < 2 * total) & v.lanes();
                 if (low == 0) continue;
                 lowered = true;
                 // in the tile's interior, as one compare per axis

@@ -55,7 +55,8 @@ ALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 OPS_PER_EXAMINATION = 40
 
 
-def _roofline(px_passes, alg_bytes, launches, kernel_ms, traffic, x_method, timing, steps=1):
+def _roofline(px_passes, alg_bytes, launches, kernel_ms, traffic, x_method, timing, steps=1,
+              kernel="k_round"):
     """The round kernel's roofline: ALU-bound in streaming-equivalent units
     (OPS_PER_EXAMINATION integer ops per pixel-pass), the HBM figure and the
     method-work fraction (the oracle's examinations only) beside it."""
@@ -67,7 +68,7 @@ def _roofline(px_passes, alg_bytes, launches, kernel_ms, traffic, x_method, timi
     gbs = alg_bytes / launches / avg_s / 1e9 if ok else None
     method = OPS_PER_EXAMINATION * x_method / (kernel_ms / 1e3) / 1e12 if ok else None
     return {
-        "bound": "alu", "kernel": "k_round",
+        "bound": "alu", "kernel": kernel,
         "achieved": round(tops, 3) if tops else None,
         "peak": round(ALU_PEAK_TOPS, 2), "unit": "Tops/s",
         "frac": round(tops / ALU_PEAK_TOPS, 4) if tops else None,
@@ -229,7 +230,9 @@ def bench_single(job, name, steps, warmup, cpu_s, tile, k, engine=0, graph=False
     elapsed = t1 - t0
     mpx = h * w * steps / elapsed / 1e6
     alg_bytes = 2 * b * h * w * ref.passes * steps
-    traffic = _traffic_for("k_round", name)
+    # small images run in one launch (k_flow), a run in rounds takes several
+    kernel = "k_flow" if launches == steps and engine in (0, 1) else "k_round"
+    traffic = _traffic_for(kernel, name)
     out = {
         "metric": METRIC,
         "value": round(mpx, 3),
@@ -260,7 +263,7 @@ def bench_single(job, name, steps, warmup, cpu_s, tile, k, engine=0, graph=False
         "roofline": _roofline(h * w * ref.passes * steps, alg_bytes, launches, kernel_ms,
                               traffic, ref.examinations * steps,
                               "kernel durations from HIP events in a second pass over the "
-                              "same runs", steps),
+                              "same runs", steps, kernel),
         # the method's own work (oracle dirty-pixel sweep): examinations X
         # against the streaming H*W*P pixel-passes
         "method_work": {"examinations": int(ref.examinations), "pixel_passes": h * w * ref.passes,

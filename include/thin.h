@@ -241,7 +241,7 @@ typedef struct thin_tune_result {
     int32_t tile_h, tile_w;     /* tile interior */
     int32_t steps_per_round;    /* parity steps per residency (halo width) */
     int32_t threads;            /* threads per tile */
-    int32_t variant;            /* residency variant (0..4) */
+    int32_t variant;            /* residency variant (0..5) */
     int32_t candidates;         /* shapes timed */
     double ms;                  /* best wall time of one run over the images, chosen shape */
     double default_ms;          /* the same with the untuned choice */

@@ -33,7 +33,10 @@
 //            across the ping-pong pair when it changed during the previous
 //            round.  Residency variants (Tile, RTile, BTile) differ only in
 //            how a step finds and examines its candidates;
-//   k_coop   the rounds of k_round in one cooperative launch.
+//   k_coop   the rounds of k_round in one cooperative launch;
+//   k_flow   small images in one launch: every tile resident from its first
+//            step to its last, halos exchanged between running blocks;
+//   k_worklist  one block per image, device-side pixel work lists.
 #include "thin_internal.h"
 
 #include <climits>
@@ -1346,8 +1349,8 @@ struct RTile {
 // during the last 4 steps of round r - 1 (dilated by the 3x3) was examined 4
 // steps earlier at the same values.
 //
-// What bounds it: in the dense first round the vector units (97 % of their
-// issue slots; per 64 examinations 58 instructions in 16 bits and 51 in 8, per
+// What bounds it: in the dense first round the vector units (85 % of their
+// issue slots in 8 bits; per 64 examinations 58 instructions in 16 bits and 51 in 8, per
 // wave and step about 170 for gather and list), later the chain of a tile's
 // few busy steps.  (63 and 67 with the 16-bit decision for both and lanes'
 // verdicts joined in registers: 512 images, 162 Mpx in all, in 8 bits 6.72 ms,

@@ -129,7 +129,11 @@ struct thin_ctx {
     DevBuf wl_imgs, wl_bits;       // pixel work-list engine: descriptors, global pending bitmaps
     DevBuf flow_imgs, flow_ctl, flow_exch;  // small-image engine
     int flow_side = -1;            // small-image engine: -1 by size, 0 off, k its k-th shape
-    int flow_polls = 1 << 22;      // polls of a wait before it gives up
+    // Polls of a wait before it gives up, about 1 us each.  A block waits for a
+    // step of its neighbours (microseconds), or for tiles queued behind an older
+    // image (milliseconds); what waits longer is half resident beside another
+    // process's kernel, and the bound is what that call loses.
+    int flow_polls = thin::kFlowPolls;
     int flow_cap[8] = {-1, -1, -1, -1, -1, -1, -1, -1};  // resident blocks by shape (-1: not asked)
     DevBuf grad;                   // gradient front-end scratch (8 floats per pixel)
     ImgCnt* h_snap[2] = {nullptr, nullptr};   // pinned snapshots of the counters
@@ -374,6 +378,11 @@ std::pair<int, int> size_class(int64_t total_pixels, int64_t images)
 //   <arch> <log2 total pixels> <log2 pixels per image> <th> <tw> <k> <threads> <variant> <ms>
 // Lines of other architectures, or naming shapes this build does not have,
 // are ignored when reading and kept when writing.
+// A second line of a class whose architecture name ends in this says that the
+// small-image engine beat the class's shape (files without such lines, and
+// readers that do not know the name, keep to the shapes).
+constexpr char kFlowMark[] = "+flow";
+
 void load_tune_cache(thin_ctx* ctx)
 {
     if (ctx->tune_cache.empty()) return;
@@ -386,10 +395,11 @@ void load_tune_cache(thin_ctx* ctx)
     while (fscanf(f, "%63s %d %d %d %d %d %d %d %lf", arch, &a, &b, &sh.th, &sh.tw, &sh.k, &sh.nt,
                   &sh.var, &ms) == 9)
         if (ctx->arch == arch && thin::tile_shape_supported(sh)) ctx->tuned[{a, b}] = sh;
+        else if (ctx->arch + kFlowMark == arch) ctx->tuned_flow.insert({a, b});
     fclose(f);
 }
 
-void save_tune_cache(const thin_ctx* ctx, std::pair<int, int> cls, TileShape sh, double ms)
+void save_tune_cache(const thin_ctx* ctx, std::pair<int, int> cls, TileShape sh, double ms, bool flow)
 {
     if (ctx->tune_cache.empty()) return;
     std::vector<std::string> keep;
@@ -398,8 +408,9 @@ void save_tune_cache(const thin_ctx* ctx, std::pair<int, int> cls, TileShape sh,
         while (fgets(line, sizeof line, f)) {
             char arch[64];
             int a, b;
-            if (sscanf(line, "%63s %d %d", arch, &a, &b) == 3 && ctx->arch == arch &&
-                a == cls.first && b == cls.second)
+            if (sscanf(line, "%63s %d %d", arch, &a, &b) == 3 &&
+                (ctx->arch == arch || ctx->arch + kFlowMark == arch) && a == cls.first &&
+                b == cls.second)
                 continue;  // replaced below
             keep.push_back(line);
         }
@@ -409,8 +420,9 @@ void save_tune_cache(const thin_ctx* ctx, std::pair<int, int> cls, TileShape sh,
     FILE* f = fopen(tmp.c_str(), "w");
     if (!f) return;
     for (const std::string& l : keep) fputs(l.c_str(), f);
-    fprintf(f, "%s %d %d %d %d %d %d %d %.4f\n", ctx->arch.c_str(), cls.first, cls.second, sh.th,
-            sh.tw, sh.k, sh.nt, sh.var, ms);
+    for (int mark = 0; mark <= (flow ? 1 : 0); ++mark)
+        fprintf(f, "%s%s %d %d %d %d %d %d %d %.4f\n", ctx->arch.c_str(), mark ? kFlowMark : "",
+                cls.first, cls.second, sh.th, sh.tw, sh.k, sh.nt, sh.var, ms);
     fclose(f);
     std::rename(tmp.c_str(), ctx->tune_cache.c_str());
 }
@@ -421,9 +433,13 @@ TileShape choose_shape(const thin_ctx* ctx, int64_t total_pixels, int64_t images
     auto it = ctx->tuned.find(size_class(total_pixels, images));
     if (it != ctx->tuned.end()) return it->second;
     // Small work lists are bound by the latency of each round: small tiles
-    // with one cell per thread and register windows.  Large ones are bound by
+    // with one cell per thread and register windows, seeded (512x512 crests in
+    // rounds of launches: 2.57 ms, 3.01 unseeded).  Large ones are bound by
     // throughput: dense per-step work lists with seeded flags in 128x128
-    // tiles (less halo work per pixel).
+    // tiles (less halo work per pixel).  Between, it is the content that
+    // decides (1400x1500 crests 14.9 ms in 32x32 tiles, 24.2 in 128x128;
+    // 2048x2048 blobs 693 us and 610), so the line stays where only a few
+    // hundred of the small tiles are left to a launch.
     (void)images;
     if (total_pixels <= (int64_t)1 << 20) return TileShape{32, 32, 16, 1024, thin::kVarRegsSeeded};
     return TileShape{128, 128, 16, 512, thin::kVarBitsSeeded};
@@ -984,7 +1000,7 @@ int choose_flow(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& wo
 // more blocks than the device has compute units (a block not yet resident then
 // finds a unit without any of them, and takes it when whatever else runs there
 // ends), or, all of one kernel, no more than the device holds of it.  First
-// come, first served.  (128x128 from 8 threads, one image each: 30 us an
+// come, first served.  (128x128 from 8 threads, one image each: 25 us an
 // image, 100 if launches run one by one.)
 class Room {
 public:
@@ -1591,7 +1607,6 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
             res.ms = timed[b].first;
             res.candidates = (int32_t)timed.size();
             ctx->tuned[cls] = best;
-            save_tune_cache(ctx, cls, best, res.ms);
             // the small-image engine stays the choice of these images where
             // it beats the best tile shape
             ctx->tuned_flow.insert(cls);
@@ -1613,6 +1628,7 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
                 faster = std::chrono::duration<double, std::milli>(t1 - t0).count() < res.ms;
             }
             if (!faster) ctx->tuned_flow.erase(cls);
+            save_tune_cache(ctx, cls, best, res.ms, faster);
         } else if (prev_shape.th) {
             ctx->tuned[cls] = prev_shape;
         }
@@ -1741,7 +1757,7 @@ int thin_create(thin_ctx** out, const thin_config* cfg)
     }
     // THIN_FLOW="shape[,polls]" picks the small-image engine's shape (1 on; 0:
     // off; -1: by size) and the bound of its waits (tuning, tests).
-    int flow_side = -1, flow_polls = 1 << 22;
+    int flow_side = -1, flow_polls = thin::kFlowPolls;
     if (const char* env = getenv("THIN_FLOW")) (void)sscanf(env, "%d,%d", &flow_side, &flow_polls);
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0) {

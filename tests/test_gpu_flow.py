@@ -174,3 +174,31 @@ def test_several_threads_and_streams():
     for th in threads:
         th.join()
     assert wrong == []
+
+
+def test_tune_cache_keeps_the_engine(tmp_path):
+    """A recorded class whose second line says that the small-image engine beat
+    its shape runs in one launch; without that line it runs the shape's rounds.
+    Tuning leaves one line of the class's shape either way."""
+    arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
+    F = image(300, 200, 4321, np.uint8)
+    ref = oracle.sweep_dirty(F, 5, "8,4")
+    path = tmp_path / "tune.txt"
+
+    def launches():
+        t = torch.from_numpy(F.copy()).cuda()
+        with thin.Context(tune_cache=str(path), profile=True) as ctx:
+            assert_image(t, ctx.run(t, 5, "8,4"), ref)
+            return int(ctx.profile().launches)
+
+    print("case flow tune cache", flush=True)
+    shape = " 15 15 64 64 16 256 3 1.0\n"
+    path.write_text(arch + shape)
+    assert launches() > 1
+    path.write_text(arch + shape + arch + "+flow" + shape)
+    assert launches() == 1
+    with thin.Context(tune_cache=str(path)) as ctx:
+        ctx.autotune([torch.from_numpy(F.copy()).cuda()], [5], [0], reps=1)
+    lines = path.read_text().splitlines()
+    assert [l.startswith(arch + " 15 15 ") for l in lines].count(True) == 1
+    assert (launches() == 1) == any(l.startswith(arch + "+flow 15 15 ") for l in lines)

@@ -20,6 +20,7 @@
 // product and sum is rounded on its own, in the association order written
 // below (no contraction into fused multiply-adds), so the float32 result is
 // reproducible bit for bit on a given image size.
+#include "gradient_plan.h"
 #include "thin_internal.h"
 
 #pragma clang fp contract(off)
@@ -181,16 +182,6 @@ __global__ __launch_bounds__(kGradThreads) void k_grad_rows(const float* __restr
 // output 28 to 14 us.  The bits are those of the passes from global memory.
 
 constexpr int kLdsThreads = 1024;
-constexpr size_t kLdsBytes = 160 * 1024 - 1024;   // dynamic LDS a block may ask for
-
-// Floats of one recursion's line in LDS: a multiple of 4, and an odd multiple,
-// so that the lanes' 16-byte accesses spread over the banks.
-__host__ __device__ inline int chain_floats(int n)
-{
-    const int quads = (n + 3) / 4;
-    return 4 * (quads | 1);
-}
-
 constexpr size_t kChainSlack = 128;  // bytes of LDS behind a block's last line
 
 // y = (t + b1 s1) + b2 s2 over the n terms at `line`, in place, in the
@@ -231,10 +222,6 @@ __device__ __forceinline__ void run_chain(const GradCoef& co, float4* line, int 
     }
     for (; k < quads; ++k) line[k] = four(line[k]);
 }
-
-// Floats of a column's four lines, and 4 more to spread the columns over the
-// banks.
-__host__ __device__ inline int column_floats(int h) { return 4 * chain_floats(h) + 4; }
 
 // Column pass: `per` columns a block, the lines of a column: smoothing
 // causal, smoothing anticausal (reversed), derivative causal, derivative
@@ -340,19 +327,6 @@ __global__ __launch_bounds__(kLdsThreads) void k_grad_rows_lds(const float* __re
             dst[(int64_t)(i0 + r) * dst_pitch + j] = (T)fminf(rintf(m * gain), top);
         }
     }
-}
-
-// Lines a block takes: as many blocks as compute units, or `waves` times that
-// many where LDS holds no more lines (0: even that leaves lines over, and the
-// passes from global memory, which run every line at once, are faster: at 4000
-// x 3000 six waves of column blocks and six of row blocks took 849 us, those
-// 493).
-int lines_per_block(int lines, int floats, int num_cus, int waves)
-{
-    const int most = min(16, (int)(kLdsBytes / (sizeof(float) * (size_t)floats)));
-    const int want = (lines + num_cus - 1) / num_cus;
-    if (most <= 0 || (int64_t)most * num_cus * waves < lines) return 0;
-    return min(want, most);
 }
 
 template <typename F>
@@ -535,7 +509,7 @@ hipError_t launch_gradient(hipStream_t stream, const void* src, int64_t src_pitc
     // else from global memory.
     const int seg_c = (h + kSegLen - 1) / kSegLen;
     const int num = num_cus > 0 ? num_cus : 1;
-    const int per_c = lines_per_block(w, column_floats(h), num, 1);
+    const int per_c = columns_per_block(h, w, num);
     bool halves = true;
     if (seg_c <= kSegMax) {
         const dim3 sgc((w + 63) / 64, 4);
@@ -563,7 +537,7 @@ hipError_t launch_gradient(hipStream_t stream, const void* src, int64_t src_pitc
     }
     if (e != hipSuccess) return e;
     const float top = dst_dtype == 1 ? 255.0f : 65535.0f;
-    const int per_r = lines_per_block(h, 4 * chain_floats(w), num, 3);
+    const int per_r = rows_per_block(h, w, num);
     if (per_r > 0) {
         if (dst_dtype == 1)
             return halves ? launch_rows_lds<uint8_t, true>(stream, cols, h, w, per_r, plane, dst,

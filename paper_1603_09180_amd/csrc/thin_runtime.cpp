@@ -127,7 +127,8 @@ struct thin_ctx {
     uint64_t allocated = 0;        // bytes of scratch currently held
     DevBuf twin, imgs, cnt, tile_img, tile_last, small, hist_bits, hist_round, wl_list, wl_meta;
     DevBuf wl_imgs, wl_bits;       // pixel work-list engine: descriptors, global pending bitmaps
-    DevBuf flow_imgs, flow_ctl, flow_exch;  // small-image engine
+    DevBuf flow_imgs, flow_ctl, flow_exch;  // small-image engine (descriptors and tile map first)
+    bool flow_held = false;        // a call is using them
     int flow_side = -1;            // small-image engine: -1 by size, 0 off, k its k-th shape
     // Polls of a wait before it gives up, about 1 us each.  A block waits for a
     // step of its neighbours (microseconds), or for tiles queued behind an older
@@ -203,19 +204,39 @@ int fail(thin_ctx* ctx, int code, const char* fmt, ...)
             return fail((ctx), THIN_EDEVICE, "%s failed: %s", #expr, hipGetErrorString(e_)); \
     } while (0)
 
+// Frees the scratch that a call can do without: the small-image engine's,
+// unless the call is using it.  Held between calls for speed alone, so a call
+// that does not fit beside it takes its place.  Whether anything was freed.
+bool shed(thin_ctx* ctx)
+{
+    bool freed = false;
+    auto drop = [&](DevBuf& b) {
+        if (!b.ptr) return;
+        if (!freed) (void)hipStreamSynchronize(ctx->stream);
+        (void)hipFree(b.ptr);
+        ctx->allocated -= b.bytes;
+        b = DevBuf{};
+        freed = true;
+    };
+    if (!ctx->flow_held)
+        for (DevBuf* b : {&ctx->flow_imgs, &ctx->flow_ctl, &ctx->flow_exch}) drop(*b);
+    return freed;
+}
+
+size_t rounded(size_t bytes) { return (bytes + 255) & ~size_t(255); }
+
 // Grows `b` to at least `need` bytes (contents not kept).
 int ensure(thin_ctx* ctx, DevBuf& b, size_t need)
 {
     if (b.bytes >= need) return THIN_OK;
-    size_t want = std::max(need, b.bytes + b.bytes / 2);
-    want = (want + 255) & ~size_t(255);
-    const uint64_t after = ctx->allocated - b.bytes + want;
-    if (ctx->max_device_bytes && after > ctx->max_device_bytes) {
-        want = (need + 255) & ~size_t(255);
-        if (ctx->allocated - b.bytes + want > ctx->max_device_bytes)
-            return fail(ctx, THIN_ENOMEM, "scratch of %zu bytes exceeds max_device_bytes %llu",
-                        want, (unsigned long long)ctx->max_device_bytes);
-    }
+    auto fits = [&](size_t want) {
+        return !ctx->max_device_bytes || ctx->allocated - b.bytes + want <= ctx->max_device_bytes;
+    };
+    size_t want = rounded(std::max(need, b.bytes + b.bytes / 2));
+    if (!fits(want)) want = rounded(need);
+    if (!fits(want) && !(shed(ctx) && fits(want)))
+        return fail(ctx, THIN_ENOMEM, "scratch of %zu bytes exceeds max_device_bytes %llu", want,
+                    (unsigned long long)ctx->max_device_bytes);
     if (b.ptr) {
         HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         HIP_TRY(ctx, hipFree(b.ptr));
@@ -226,7 +247,11 @@ int ensure(thin_ctx* ctx, DevBuf& b, size_t need)
     if (hipMalloc(&b.ptr, want) != hipSuccess) {
         (void)hipGetLastError();
         b.ptr = nullptr;
-        return fail(ctx, THIN_ENOMEM, "hipMalloc(%zu) failed", want);
+        if (!shed(ctx) || hipMalloc(&b.ptr, want) != hipSuccess) {
+            (void)hipGetLastError();
+            b.ptr = nullptr;
+            return fail(ctx, THIN_ENOMEM, "hipMalloc(%zu) failed", want);
+        }
     }
     b.bytes = want;
     ctx->allocated += want;
@@ -1151,6 +1176,8 @@ int64_t plan_flow(int which, const thin_image* ims, const std::vector<int>& work
     return words;
 }
 
+// THIN_ENOMEM, with nothing more allocated than before, where the engine's
+// scratch does not fit beside what the context holds.
 int run_flow(thin_ctx* ctx, int which, const thin_image* ims, const std::vector<int>& work,
              thin_stats* stats, std::vector<int>& rest)
 {
@@ -1158,18 +1185,33 @@ int run_flow(thin_ctx* ctx, int which, const thin_image* ims, const std::vector<
     std::vector<thin::FlowImg> imgs;
     std::vector<int32_t> tile_img;
     const int64_t words = plan_flow(which, ims, work, imgs, tile_img);
-    int rc;
-    if ((rc = ensure(ctx, ctx->flow_imgs, sizeof(thin::FlowImg) * nimg))) return rc;
-    if ((rc = ensure(ctx, ctx->cnt, sizeof(ImgCnt) * nimg))) return rc;
-    if ((rc = ensure(ctx, ctx->flow_ctl, sizeof(int32_t) * flow_control_words(nimg)))) return rc;
-    if ((rc = ensure(ctx, ctx->flow_exch, sizeof(uint64_t) * words))) return rc;
-    if (nimg > 1 && (rc = ensure(ctx, ctx->tile_img, sizeof(int32_t) * tile_img.size()))) return rc;
-    if ((rc = ensure_snap(ctx, nimg))) return rc;
-    const FlowBufs b{static_cast<thin::FlowImg*>(ctx->flow_imgs.ptr),
-                     static_cast<int32_t*>(ctx->tile_img.ptr), static_cast<ImgCnt*>(ctx->cnt.ptr),
-                     static_cast<int32_t*>(ctx->flow_ctl.ptr),
-                     static_cast<uint64_t*>(ctx->flow_exch.ptr)};
-    return drive_flow(ctx, which, imgs, tile_img, words, b, work, stats, rest, true);
+    const size_t o_map = rounded(sizeof(thin::FlowImg) * nimg);
+    const struct {
+        DevBuf& buf;
+        size_t bytes;
+    } needs[] = {{ctx->cnt, sizeof(ImgCnt) * nimg},
+                 {ctx->flow_imgs, o_map + (nimg > 1 ? sizeof(int32_t) * tile_img.size() : 0)},
+                 {ctx->flow_ctl, sizeof(int32_t) * flow_control_words(nimg)},
+                 {ctx->flow_exch, sizeof(uint64_t) * words}};
+    uint64_t after = ctx->allocated;
+    for (const auto& n : needs)
+        if (n.bytes > n.buf.bytes) after += rounded(n.bytes) - n.buf.bytes;
+    if (ctx->max_device_bytes && after > ctx->max_device_bytes) return THIN_ENOMEM;
+    ctx->flow_held = true;
+    int rc = THIN_OK;
+    for (const auto& n : needs)
+        if (rc == THIN_OK) rc = ensure(ctx, n.buf, n.bytes);
+    if (rc == THIN_OK) rc = ensure_snap(ctx, nimg);
+    if (rc == THIN_OK) {
+        char* head = static_cast<char*>(ctx->flow_imgs.ptr);
+        const FlowBufs b{reinterpret_cast<thin::FlowImg*>(head), reinterpret_cast<int32_t*>(head + o_map),
+                         static_cast<ImgCnt*>(ctx->cnt.ptr), static_cast<int32_t*>(ctx->flow_ctl.ptr),
+                         static_cast<uint64_t*>(ctx->flow_exch.ptr)};
+        rc = drive_flow(ctx, which, imgs, tile_img, words, b, work, stats, rest, true);
+    }
+    ctx->flow_held = false;
+    if (rc == THIN_ENOMEM) (void)shed(ctx);
+    return rc;
 }
 
 // ---------------------------------------------------------- cooperative engine
@@ -1530,6 +1572,7 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
     }
     if (work_img.empty()) return fail(ctx, THIN_EINVAL, "no image of at least 3x3 to tune on");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
+    (void)shed(ctx);
     void *pristine = nullptr, *scratch = nullptr;
     if (hipMalloc(&pristine, bytes) != hipSuccess || hipMalloc(&scratch, bytes) != hipSuccess) {
         (void)hipGetLastError();

@@ -48,6 +48,23 @@ def test_many_small_images():
                 assert (st.passes, st.lowerings) == (ref.passes, ref.lowerings)
 
 
+@pytest.mark.parametrize("kw", [dict(), dict(max_passes=1000), dict(engine=thin.THIN_ENGINE_COOP)],
+                         ids=["auto", "rounds", "coop"])
+def test_rounds_without_change_bitmaps(kw):
+    """A 512x512 image takes 273408 bytes of twin, tile state and queues; the
+    change bitmaps of the default shape (64 KB) do not fit beside them."""
+    with thin.Context(max_device_bytes=274_000, **kw) as ctx:
+        check(ctx, image(512, 512, 5), 5, "8,4")
+
+
+def test_change_bitmaps_give_way():
+    """Under 400 kB the first image has its change bitmaps, and the second one's
+    larger twin takes their place."""
+    with thin.Context(max_device_bytes=400_000, max_passes=1000) as ctx:
+        for h, w in [(512, 512), (600, 560), (512, 512)]:
+            check(ctx, image(h, w, h), 5, "8,4")
+
+
 def test_gradient_after_a_small_image():
     """The gradient's 32 bytes a pixel of 400x500 under a cap that holds them and
     the image's twin, not the exchange words of the image before."""

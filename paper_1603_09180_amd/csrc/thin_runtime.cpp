@@ -134,7 +134,8 @@ struct thin_ctx {
     // Polls of a wait before it gives up, about 1 us each.  A block waits for a
     // step of its neighbours (microseconds), or for tiles queued behind an older
     // image (milliseconds); what waits longer is half resident beside another
-    // process's kernel, and the bound is what that call loses.
+    // process's kernel, and the bound is what that call loses (it goes on in
+    // rounds and does not try again).
     int flow_polls = thin::kFlowPolls;
     int flow_cap[8] = {-1, -1, -1, -1, -1, -1, -1, -1};  // resident blocks by shape (-1: not asked)
     DevBuf grad;                   // gradient front-end scratch (8 floats per pixel)
@@ -1550,16 +1551,17 @@ int run_images(thin_ctx* ctx, const thin_image* ims, int n, thin_stats* stats)
     if (ctx->engine == THIN_ENGINE_WORKLIST) return run_worklist(ctx, ims, work, stats);
     if (ctx->engine == THIN_ENGINE_COOP) return run_coop(ctx, ims, work, stats);
     const int flow = choose_flow(ctx, ims, work, kFlowWaves);
+    std::vector<int> rest;
     if (flow >= 0) {
-        std::vector<int> rest;
         const int rc = run_flow(ctx, flow, ims, work, stats, rest);
         if (rc == THIN_OK && rest.empty()) return rc;
-        // Over the scratch cap (its exchange words take more than a twin), or
-        // images it gave up on: the rounds of launches.
+        // Over the scratch cap (its exchange words take more than a twin): the
+        // rounds of launches.  Images it gave up on stay there: what kept its
+        // blocks from running together would do so again.
         if (rc != THIN_OK && rc != THIN_ENOMEM) return rc;
-        if (rc == THIN_OK) work.swap(rest);
+        if (rc == THIN_OK) work = rest;
     }
-    return run_tiled(ctx, ims, work, stats, true);
+    return run_tiled(ctx, ims, work, stats, rest.empty());
 }
 
 // One tiled run over `work` of ims with `shape` forced; wall time in ms

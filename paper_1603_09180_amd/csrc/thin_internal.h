@@ -185,6 +185,10 @@ constexpr int kFlowNext = 0, kFlowAbort = 16;  // control words
 constexpr int kFlowCtl = 32;                   // first vote ring
 constexpr int kFlowRing = 1024;
 constexpr int kFlowPolls = 1 << 17;            // of a wait, unless set
+// Rounds of an image, far beyond what one takes (every round but the last
+// lowers something; a spiral corridor through n x n pixels takes n * n / 16),
+// and within what the kernel's round tags and step numbers count.
+constexpr int kFlowMaxRounds = 1 << 24;
 constexpr int kFlowMaxSide = 500;              // tiles across or down an image
 constexpr int kFlowRunning = 0, kFlowStable = 1, kFlowGivenUp = 2;  // marks
 // Exchange words of an image: two copies of one (u8) or two (u16) per 2x2 cell.

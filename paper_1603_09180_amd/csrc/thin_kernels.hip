@@ -2156,7 +2156,7 @@ void k_coop(const ImgDev* __restrict__ imgs, ImgCnt* cnt,
 // (the grid is no larger than the device holds, other kernels end, and the
 // host lets this process's waiting kernels run together only where all fit),
 // so all its tiles get a block and none waits for a tile without one.  Every
-// wait and the number of rounds are bounded all the same: a block that runs
+// wait and the number of rounds (kFlowMaxRounds) are bounded all the same: a block that runs
 // out marks its image given up, sets the abort word and leaves, as do all that
 // see either, and the host runs the images that are not stable on the rounds
 // of launches.  An image's mark changes once (compare and swap), and its tiles
@@ -2203,7 +2203,8 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
     __shared__ __align__(16) uint16_t s_img[T::IMG_ELEMS];
     __shared__ __align__(16) uint8_t s_flags[T::DIRTY_ELEMS];
     __shared__ DecEntry s_lut[256];
-    __shared__ int s_tile, s_act, s_mark, s_count, s_last, s_exam;
+    __shared__ int s_tile, s_act, s_mark, s_count, s_last;
+    __shared__ unsigned long long s_exam;
     const int tid = threadIdx.x;
     int lut_adj = -1;
     const int vote_shift = 31 - __clz(vote_every);
@@ -2230,7 +2231,7 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
             s_mark = kFlowRunning;
             s_count = 0;
             s_last = -1;
-            s_exam = 0;
+            s_exam = 0ull;
         }
         if (tid < T::DIRTY_ELEMS / 4) reinterpret_cast<uint32_t*>(s_flags)[tid] = 0u;
         T::stage(d, gy0, gx0, im.image, im.image, s_img, tid);
@@ -2257,7 +2258,8 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
 
         uint64_t* const ex = exch + im.word0;
         const Lambda lambda = lambda_of(im.lambda);
-        int lowered = 0, exams = 0, last = -1;  // of the wave, over all rounds
+        int lowered = 0, last = -1;  // of the wave, over all rounds
+        unsigned long long exams = 0;
         int32_t* const image_mark = &cnt[im.slot].pad;
         int32_t* const ring = ctl + im.ctl0;
         const bool counts = lt == 0 && tid < 64;  // the wave that counts the image's votes
@@ -2268,7 +2270,7 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
             typename T::Counts n;
             T::steps(q, s_img, s_flags, nullptr, K, tid, s_lut, lambda, n);
             lowered += n.lowered;
-            exams += n.exams;
+            exams += (unsigned)n.exams;
             if (n.last >= 0) last = r * K + n.last;
             if (n.last >= K - 4 && (tid & 63) == 0) s_act = 1;
             const uint32_t tag = (uint32_t)r + 1u;
@@ -2378,7 +2380,7 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
         if (tid == 0) {
             ImgCnt* c = cnt + im.slot;
             atomicAdd(&c->tile_rounds, (unsigned long long)(r + 1));
-            atomicAdd(&c->examinations, (unsigned long long)(uint32_t)s_exam);
+            atomicAdd(&c->examinations, s_exam);
             if (s_count) {
                 atomicAdd(&c->lowerings, (unsigned long long)(uint32_t)s_count);
                 atomicMax(&c->last_step, s_last);

@@ -1134,7 +1134,7 @@ int drive_flow(thin_ctx* ctx, int which, const std::vector<thin::FlowImg>& imgs,
     run.ctl = b.ctl;
     run.exch = b.exch;
     run.max_polls = ctx->flow_polls;
-    run.max_rounds = 1 << 16;
+    run.max_rounds = thin::kFlowMaxRounds;
     // A vote is one atomic of every tile on one word (512x512, four 16x16
     // tiles to a unit: 3119 us voting every round, 1675 every fourth); up to 64
     // tiles it costs less than the rounds an image waits for the next vote.

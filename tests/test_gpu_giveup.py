@@ -38,3 +38,25 @@ def test_an_image_given_up_is_not_handed_back(monkeypatch):
     assert launches(F, 20, "8,4") == 1
     monkeypatch.setenv("THIN_FLOW", "1,0")
     assert launches(F, 20, "8,4") == rounds + 1
+
+
+def test_a_run_of_more_than_100000_passes():
+    """A spiral corridor, consumed from its ends a pixel or two a pass: the
+    engine stays with it to the end."""
+    n, r, c, d, turns = 741, 2, 2, 0, 0
+    F = np.full((n, n), 255, np.uint8)
+    F[r, c] = 55
+    step = [(0, 1), (1, 0), (0, -1), (-1, 0)]
+    while turns < 2:
+        y, x = r + step[d][0], c + step[d][1]
+        yy, xx = y + step[d][0], x + step[d][1]
+        if not (2 <= y < n - 2 and 2 <= x < n - 2) or (2 <= yy < n - 2 and 2 <= xx < n - 2
+                                                       and F[yy, xx] == 55):
+            d, turns = (d + 1) % 4, turns + 1
+            continue
+        r, c, turns = y, x, 0
+        F[r, c] = 55
+    ref = oracle.sweep_dirty(F, 0, "4,8")
+    assert ref.passes > 131072
+    print("case long spiral", ref.passes, flush=True)
+    assert launches(F, 0, "4,8", ref) == 1

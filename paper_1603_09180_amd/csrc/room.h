@@ -1,0 +1,70 @@
+// room.h -- admission of kernels whose blocks wait for each other.  Host code
+// that needs no GPU to run.
+#pragma once
+
+#include <condition_variable>
+#include <cstdint>
+#include <mutex>
+
+namespace thin {
+
+// Room on a device for such kernels (k_flow, k_coop), held from before the
+// launch until the kernel has ended: two that are each partly resident would
+// keep one another waiting.  Kernels run together if all their blocks become
+// resident wherever each one goes: with no more blocks than the device has
+// compute units (a block not yet resident then finds a unit without any of
+// them, and takes it when whatever else runs there ends), or, all of one
+// kernel, no more than the device holds of it.  The dispatcher deals a
+// kernel's blocks to the XCDs in turn, so what counts is the fullest XCD: a
+// kernel's blocks are rounded up to a whole turn (three kernels of 85 blocks
+// leave 33 to one XCD's 32 units).  First come, first served.  (128x128 from 8
+// threads, one image each: 25 us an image, 100 if launches run one by one.)
+class Room {
+public:
+    // which: the kernel; holds: how many of its blocks the device holds
+    Room(int device, int which, int blocks, int holds, int num_cus)
+        : gate_(gate_of(device)), blocks_((blocks + kXcds - 1) / kXcds * kXcds)
+    {
+        std::unique_lock<std::mutex> lock(gate_.m);
+        const uint64_t mine = gate_.tickets++;
+        gate_.freed.wait(lock, [&] {
+            const int all = gate_.used + blocks_;
+            return mine == gate_.serving &&
+                   (gate_.used == 0 || all <= num_cus || (gate_.which == which && all <= holds));
+        });
+        gate_.which = gate_.used == 0 || gate_.which == which ? which : kMixed;
+        gate_.used += blocks_;
+        ++gate_.serving;
+        if (gate_.tickets != gate_.serving) gate_.freed.notify_all();
+    }
+    ~Room()
+    {
+        const std::lock_guard<std::mutex> lock(gate_.m);
+        gate_.used -= blocks_;
+        if (gate_.tickets != gate_.serving) gate_.freed.notify_all();
+    }
+    Room(const Room&) = delete;
+    Room& operator=(const Room&) = delete;
+
+    static constexpr int kCoop = -1;  // which: k_coop; k_flow's are its shapes from 0 on
+    static constexpr int kXcds = 8;
+
+private:
+    static constexpr int kMixed = -2;
+    struct Gate {
+        std::mutex m;
+        std::condition_variable freed;
+        uint64_t tickets = 0, serving = 0;
+        int used = 0;        // blocks of all that hold room
+        int which = kMixed;  // the kernel they all are
+    };
+    static Gate& gate_of(int device)
+    {
+        static Gate gates[64];
+        return gates[device & 63];
+    }
+    Gate& gate_;
+    const int blocks_;
+};
+
+}  // namespace thin

@@ -16,14 +16,12 @@
 #include <chrono>
 #include <climits>
 #include <cmath>
-#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <iterator>
 #include <map>
-#include <mutex>
 #include <set>
 #include <new>
 #include <optional>
@@ -31,6 +29,7 @@
 #include <vector>
 
 #include "thin.h"
+#include "room.h"
 #include "thin_internal.h"
 
 using thin::ImgCnt;
@@ -1049,62 +1048,6 @@ int choose_flow(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& wo
     return several;
 }
 
-// Room on a device for kernels whose blocks wait for each other (k_flow,
-// k_coop), held from before the launch until the kernel has ended: two that
-// are each partly resident would keep one another waiting.  Kernels run
-// together if all their blocks become resident wherever each one goes: with no
-// more blocks than the device has compute units (a block not yet resident then
-// finds a unit without any of them, and takes it when whatever else runs there
-// ends), or, all of one kernel, no more than the device holds of it.  First
-// come, first served.  (128x128 from 8 threads, one image each: 25 us an
-// image, 100 if launches run one by one.)
-class Room {
-public:
-    // which: the kernel; holds: how many of its blocks the device holds
-    Room(int device, int which, int blocks, int holds, int num_cus)
-        : gate_(gate_of(device)), blocks_(blocks)
-    {
-        std::unique_lock<std::mutex> lock(gate_.m);
-        const uint64_t mine = gate_.tickets++;
-        gate_.freed.wait(lock, [&] {
-            const int all = gate_.used + blocks;
-            return mine == gate_.serving &&
-                   (gate_.used == 0 || all <= num_cus || (gate_.which == which && all <= holds));
-        });
-        gate_.which = gate_.used == 0 || gate_.which == which ? which : kMixed;
-        gate_.used += blocks;
-        ++gate_.serving;
-        if (gate_.tickets != gate_.serving) gate_.freed.notify_all();
-    }
-    ~Room()
-    {
-        const std::lock_guard<std::mutex> lock(gate_.m);
-        gate_.used -= blocks_;
-        if (gate_.tickets != gate_.serving) gate_.freed.notify_all();
-    }
-    Room(const Room&) = delete;
-    Room& operator=(const Room&) = delete;
-
-    static constexpr int kCoop = -1;  // which: k_coop; k_flow's are its shapes from 0 on
-
-private:
-    static constexpr int kMixed = -2;
-    struct Gate {
-        std::mutex m;
-        std::condition_variable freed;
-        uint64_t tickets = 0, serving = 0;
-        int used = 0;        // blocks of all that hold room
-        int which = kMixed;  // the kernel they all are
-    };
-    static Gate& gate_of(int device)
-    {
-        static Gate gates[64];
-        return gates[device & 63];
-    }
-    Gate& gate_;
-    const int blocks_;
-};
-
 // Device memory of a run of the small-image engine.
 struct FlowBufs {
     thin::FlowImg* imgs;
@@ -1147,7 +1090,7 @@ int drive_flow(thin_ctx* ctx, int which, const std::vector<thin::FlowImg>& imgs,
                                     hipMemcpyHostToDevice, ctx->stream));
     }
     // (A cooperative launch keeps such kernels apart too, at 18 us a call.)
-    const Room room(ctx->device, which, run.grid, ctx->flow_cap[which], ctx->num_cus);
+    const thin::Room room(ctx->device, which, run.grid, ctx->flow_cap[which], ctx->num_cus);
     HIP_TRY(ctx, thin::launch_flow_init(ctx->stream, run, nimg, flow_control_words(nimg), words,
                                         nimg == 1 ? &imgs[0] : nullptr));
     const bool profile = ctx->profile && allocate;
@@ -1337,7 +1280,7 @@ int run_coop(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work,
         }
         HIP_TRY(ctx, hipEventRecord(ctx->prof_ev[0], ctx->stream));
     }
-    const Room room(ctx->device, Room::kCoop, ctx->num_cus, 0, ctx->num_cus);
+    const thin::Room room(ctx->device, thin::Room::kCoop, ctx->num_cus, 0, ctx->num_cus);
     HIP_TRY(ctx, thin::launch_coop(ctx->stream, shape, d_imgs, d_cnt, d_tile_img, d_tile_last,
                                    ntiles, ctx->d_lut, d_small, d_small + 3, rounds_cap,
                                    ctx->num_cus, static_cast<uint32_t*>(ctx->hist_bits.ptr),

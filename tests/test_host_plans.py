@@ -1,6 +1,7 @@
 """The library's host-side decisions that need no GPU, compiled on their own
 from its headers with the host compiler: the gradient's lines per block at
-every accepted side, against the same rule in Python's integers."""
+every accepted side, against the same rule in Python's integers, and the
+admission to a device of kernels whose blocks wait for each other."""
 import ctypes
 import os
 import subprocess
@@ -56,3 +57,67 @@ extern "C" int rows(int h, int w, int cus) { return thin::rows_per_block(h, w, c
                     assert want_c == want_r == 0
                 fits += want_c > 0
     assert fits > 50
+
+
+@pytest.fixture(scope="module")
+def room(tmp_path_factory):
+    """enter(device, which, blocks, holds) starts a thread that asks for room on
+    a device of 256 units; inside(i) says whether thread i has it (waiting up
+    to 20 s where it should), leave(i) lets it go."""
+    lib = compiled(tmp_path_factory.mktemp("room"), "room", """
+#include "room.h"
+#include <atomic>
+#include <chrono>
+#include <thread>
+namespace {
+struct Job {
+    std::thread th;
+    std::atomic<int> state{0}, go{0};
+};
+Job jobs[512];
+int n = 0;
+}
+extern "C" int enter(int device, int which, int blocks, int holds)
+{
+    Job& j = jobs[n];
+    j.th = std::thread([=, &j] {
+        const thin::Room room(device, which, blocks, holds, 256);
+        j.state = 1;
+        while (!j.go) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    });
+    // until it has room or waits for it
+    for (int k = 0; k < 50 && !j.state; ++k) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    return n++;
+}
+extern "C" int inside(int i, int should)
+{
+    for (int k = 0; k < 20000 && should && !jobs[i].state; ++k)
+        std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    return jobs[i].state;
+}
+extern "C" void leave(int i)
+{
+    jobs[i].go = 1;
+    jobs[i].th.join();
+}
+""", "-pthread")
+    return lib
+
+
+@pytest.mark.parametrize("blocks,held,fit", [(85, 0, 2), (64, 0, 4), (57, 0, 4), (1, 0, 32),
+                                             (170, 512, 2), (168, 512, 3), (300, 512, 1)])
+def test_room_counts_the_fullest_xcd(room, blocks, held, fit):
+    """As many kernels of `blocks` blocks as every XCD has units for (or, all of
+    one kernel, holds blocks of it: `held` in all) run together, and one more
+    waits for one of them to end."""
+    device = 1 + (blocks * 7 + held) % 60
+    holds = held or 256
+    # the fullest XCD takes a block of every turn a kernel deals
+    assert fit * -(-blocks // 8) <= holds // 8 < (fit + 1) * -(-blocks // 8)
+    ids = [room.enter(device, 1, blocks, holds) for _ in range(fit + 1)]
+    assert [room.inside(i, 1) for i in ids[:-1]] == [1] * fit
+    assert room.inside(ids[-1], 0) == 0
+    room.leave(ids[0])
+    assert room.inside(ids[-1], 1) == 1
+    for i in ids[1:]:
+        room.leave(i)

@@ -3,7 +3,6 @@
 #pragma once
 
 #include <condition_variable>
-#include <cstdint>
 #include <mutex>
 
 namespace thin {
@@ -17,8 +16,10 @@ namespace thin {
 // kernel, no more than the device holds of it.  The dispatcher deals a
 // kernel's blocks to the XCDs in turn, so what counts is the fullest XCD: a
 // kernel's blocks are rounded up to a whole turn (three kernels of 85 blocks
-// leave 33 to one XCD's 32 units).  First come, first served.  (128x128 from 8
-// threads, one image each: 25 us an image, 100 if launches run one by one.)
+// leave 33 to one XCD's 32 units).  First come, first served, but a kernel that
+// fits goes past those that wait for more room, each of which lets kPasses
+// pass (128x128 from 8 threads, one image each: 25 us an image, 100 if launches
+// run one by one).
 class Room {
 public:
     // which: the kernel; holds: how many of its blocks the device holds
@@ -26,35 +27,46 @@ public:
         : gate_(gate_of(device)), blocks_((blocks + kXcds - 1) / kXcds * kXcds)
     {
         std::unique_lock<std::mutex> lock(gate_.m);
-        const uint64_t mine = gate_.tickets++;
+        Waiter me;
+        Waiter** at = &gate_.first;
+        while (*at) at = &(*at)->next;
+        *at = &me;
         gate_.freed.wait(lock, [&] {
             const int all = gate_.used + blocks_;
-            return mine == gate_.serving &&
-                   (gate_.used == 0 || all <= num_cus || (gate_.which == which && all <= holds));
+            if (gate_.used != 0 && all > num_cus && !(gate_.which == which && all <= holds)) return false;
+            for (const Waiter* w = gate_.first; w != &me; w = w->next)
+                if (w->passed >= kPasses) return false;
+            return true;
         });
+        for (at = &gate_.first; *at != &me; at = &(*at)->next) ++(*at)->passed;
+        *at = me.next;
         gate_.which = gate_.used == 0 || gate_.which == which ? which : kMixed;
         gate_.used += blocks_;
-        ++gate_.serving;
-        if (gate_.tickets != gate_.serving) gate_.freed.notify_all();
+        if (gate_.first) gate_.freed.notify_all();
     }
     ~Room()
     {
         const std::lock_guard<std::mutex> lock(gate_.m);
         gate_.used -= blocks_;
-        if (gate_.tickets != gate_.serving) gate_.freed.notify_all();
+        if (gate_.first) gate_.freed.notify_all();
     }
     Room(const Room&) = delete;
     Room& operator=(const Room&) = delete;
 
     static constexpr int kCoop = -1;  // which: k_coop; k_flow's are its shapes from 0 on
     static constexpr int kXcds = 8;
+    static constexpr int kPasses = 8;
 
 private:
     static constexpr int kMixed = -2;
+    struct Waiter {
+        Waiter* next = nullptr;
+        int passed = 0;      // later ones that went in before it
+    };
     struct Gate {
         std::mutex m;
         std::condition_variable freed;
-        uint64_t tickets = 0, serving = 0;
+        Waiter* first = nullptr;  // those that wait, in the order they came
         int used = 0;        // blocks of all that hold room
         int which = kMixed;  // the kernel they all are
     };

@@ -121,3 +121,23 @@ def test_room_counts_the_fullest_xcd(room, blocks, held, fit):
     assert room.inside(ids[-1], 1) == 1
     for i in ids[1:]:
         room.leave(i)
+
+
+def test_room_lets_what_fits_past_what_waits(room):
+    """A kernel of 242 blocks waits for one of 64; eight that fit beside that one
+    go past it, the ninth waits behind it, and all get their turn."""
+    first = room.enter(61, 0, 64, 2048)
+    big = room.enter(61, 1, 242, 512)
+    assert (room.inside(first, 1), room.inside(big, 0)) == (1, 0)
+    for _ in range(8):
+        i = room.enter(61, 2, 8, 512)
+        assert room.inside(i, 1) == 1
+        room.leave(i)
+    ninth = room.enter(61, 2, 16, 512)
+    assert room.inside(ninth, 0) == 0
+    room.leave(first)
+    assert room.inside(big, 1) == 1
+    assert room.inside(ninth, 0) == 0     # 248 + 16 blocks are more than 256
+    room.leave(big)
+    assert room.inside(ninth, 1) == 1
+    room.leave(ninth)

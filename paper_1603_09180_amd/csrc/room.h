@@ -2,7 +2,9 @@
 // that needs no GPU to run.
 #pragma once
 
+#include <chrono>
 #include <condition_variable>
+#include <cstdint>
 #include <mutex>
 
 namespace thin {
@@ -19,11 +21,15 @@ namespace thin {
 // leave 33 to one XCD's 32 units).  First come, first served, but a kernel that
 // fits goes past those that wait for more room, each of which lets kPasses
 // pass (128x128 from 8 threads, one image each: 25 us an image, 100 if launches
-// run one by one).
+// run one by one).  A kernel that could run another way waits only while room
+// is being given back: it leaves without when nobody has left for `patience`
+// microseconds (a cooperative run of seconds, or a stream that has not come to
+// its kernel yet).
 class Room {
 public:
-    // which: the kernel; holds: how many of its blocks the device holds
-    Room(int device, int which, int blocks, int holds, int num_cus)
+    // which: the kernel; holds: how many of its blocks the device holds;
+    // patience: < 0 without end
+    Room(int device, int which, int blocks, int holds, int num_cus, int64_t patience)
         : gate_(gate_of(device)), blocks_((blocks + kXcds - 1) / kXcds * kXcds)
     {
         std::unique_lock<std::mutex> lock(gate_.m);
@@ -31,27 +37,42 @@ public:
         Waiter** at = &gate_.first;
         while (*at) at = &(*at)->next;
         *at = &me;
-        gate_.freed.wait(lock, [&] {
+        auto may = [&] {
             const int all = gate_.used + blocks_;
             if (gate_.used != 0 && all > num_cus && !(gate_.which == which && all <= holds)) return false;
             for (const Waiter* w = gate_.first; w != &me; w = w->next)
                 if (w->passed >= kPasses) return false;
             return true;
-        });
-        for (at = &gate_.first; *at != &me; at = &(*at)->next) ++(*at)->passed;
+        };
+        while (!(held_ = may())) {
+            if (patience < 0) {
+                gate_.freed.wait(lock);
+                continue;
+            }
+            const uint64_t left = gate_.left;
+            const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(patience);
+            if (!gate_.freed.wait_until(lock, until, [&] { return gate_.left != left || may(); })) break;
+        }
+        for (at = &gate_.first; *at != &me; at = &(*at)->next)
+            if (held_) ++(*at)->passed;
         *at = me.next;
+        if (gate_.first) gate_.freed.notify_all();
+        if (!held_) return;
         gate_.which = gate_.used == 0 || gate_.which == which ? which : kMixed;
         gate_.used += blocks_;
-        if (gate_.first) gate_.freed.notify_all();
     }
     ~Room()
     {
+        if (!held_) return;
         const std::lock_guard<std::mutex> lock(gate_.m);
         gate_.used -= blocks_;
+        ++gate_.left;
         if (gate_.first) gate_.freed.notify_all();
     }
     Room(const Room&) = delete;
     Room& operator=(const Room&) = delete;
+
+    bool held() const { return held_; }
 
     static constexpr int kCoop = -1;  // which: k_coop; k_flow's are its shapes from 0 on
     static constexpr int kXcds = 8;
@@ -67,6 +88,7 @@ private:
         std::mutex m;
         std::condition_variable freed;
         Waiter* first = nullptr;  // those that wait, in the order they came
+        uint64_t left = 0;   // how many have given room back
         int used = 0;        // blocks of all that hold room
         int which = kMixed;  // the kernel they all are
     };
@@ -77,6 +99,7 @@ private:
     }
     Gate& gate_;
     const int blocks_;
+    bool held_ = false;
 };
 
 }  // namespace thin

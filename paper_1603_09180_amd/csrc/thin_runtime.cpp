@@ -1061,7 +1061,8 @@ int flow_control_words(int nimg) { return thin::kFlowCtl + nimg * thin::kFlowRin
 
 // Launches the small-image engine on `imgs` (tile map tile_img, exchange
 // words in all) and fills the statistics of images src[i]; rest receives
-// those it gave up on (untouched).  allocate: profiling events may be created.
+// those it gave up on (untouched), all of them when it finds no room on the
+// device.  allocate: profiling events may be created.
 int drive_flow(thin_ctx* ctx, int which, const std::vector<thin::FlowImg>& imgs,
                const std::vector<int32_t>& tile_img, int64_t words, const FlowBufs& b,
                const std::vector<int>& src, thin_stats* stats, std::vector<int>& rest, bool allocate)
@@ -1083,14 +1084,23 @@ int drive_flow(thin_ctx* ctx, int which, const std::vector<thin::FlowImg>& imgs,
     // tiles it costs less than the rounds an image waits for the next vote.
     run.vote_every = run.ntiles <= 64 ? 1 : 4;
     int rc;
+    // (A cooperative launch keeps such kernels apart too, at 18 us a call.)
+    // An image waits for room no longer than it would take in rounds, which
+    // need none (512x512 crests 3 ms, 128x128 blobs 0.25).
+    int64_t pixels = 0;
+    for (const thin::FlowImg& f : imgs) pixels += (int64_t)f.h * f.w;
+    const thin::Room room(ctx->device, which, run.grid, ctx->flow_cap[which], ctx->num_cus,
+                          300 + pixels / 100);
+    if (!room.held()) {
+        rest = src;
+        return THIN_OK;
+    }
     if (nimg > 1) {
         HIP_TRY(ctx, hipMemcpyAsync(b.imgs, imgs.data(), sizeof(thin::FlowImg) * nimg,
                                     hipMemcpyHostToDevice, ctx->stream));
         HIP_TRY(ctx, hipMemcpyAsync(b.tile_img, tile_img.data(), sizeof(int32_t) * run.ntiles,
                                     hipMemcpyHostToDevice, ctx->stream));
     }
-    // (A cooperative launch keeps such kernels apart too, at 18 us a call.)
-    const thin::Room room(ctx->device, which, run.grid, ctx->flow_cap[which], ctx->num_cus);
     HIP_TRY(ctx, thin::launch_flow_init(ctx->stream, run, nimg, flow_control_words(nimg), words,
                                         nimg == 1 ? &imgs[0] : nullptr));
     const bool profile = ctx->profile && allocate;
@@ -1280,7 +1290,7 @@ int run_coop(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work,
         }
         HIP_TRY(ctx, hipEventRecord(ctx->prof_ev[0], ctx->stream));
     }
-    const thin::Room room(ctx->device, thin::Room::kCoop, ctx->num_cus, 0, ctx->num_cus);
+    const thin::Room room(ctx->device, thin::Room::kCoop, ctx->num_cus, 0, ctx->num_cus, -1);
     HIP_TRY(ctx, thin::launch_coop(ctx->stream, shape, d_imgs, d_cnt, d_tile_img, d_tile_last,
                                    ntiles, ctx->d_lut, d_small, d_small + 3, rounds_cap,
                                    ctx->num_cus, static_cast<uint32_t*>(ctx->hist_bits.ptr),
@@ -1499,8 +1509,8 @@ int run_images(thin_ctx* ctx, const thin_image* ims, int n, thin_stats* stats)
         const int rc = run_flow(ctx, flow, ims, work, stats, rest);
         if (rc == THIN_OK && rest.empty()) return rc;
         // Over the scratch cap (its exchange words take more than a twin): the
-        // rounds of launches.  Images it gave up on stay there: what kept its
-        // blocks from running together would do so again.
+        // rounds of launches.  Images it gave up on or found no room for stay
+        // there: what kept its blocks from running together would do so again.
         if (rc != THIN_OK && rc != THIN_ENOMEM) return rc;
         if (rc == THIN_OK) work = rest;
     }

@@ -1,5 +1,9 @@
-"""What a call does when the small-image engine cannot finish its images: the
-path taken, by the launches it takes, and the result against the oracle."""
+"""What a call does when the small-image engine cannot finish its images or
+finds no room: the path taken, by the launches it takes, how long others keep it
+waiting, and the result against the oracle."""
+import threading
+import time
+
 import numpy as np
 import pytest
 
@@ -60,3 +64,79 @@ def test_a_run_of_more_than_100000_passes():
     assert ref.passes > 131072
     print("case long spiral", ref.passes, flush=True)
     assert launches(F, 0, "4,8", ref) == 1
+
+
+def sleep_cycles(ms):
+    """The argument of torch.cuda._sleep for about `ms`."""
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    torch.cuda._sleep(100_000)
+    a.record()
+    torch.cuda._sleep(1_000_000)
+    b.record()
+    b.synchronize()
+    return int(1_000_000 * ms / a.elapsed_time(b))
+
+
+def independent_streams(cycles):
+    """Two streams of which the second does not wait for the first's work (the
+    device has few hardware queues, and streams may share one)."""
+    first = torch.cuda.Stream()
+    for _ in range(16):
+        other = torch.cuda.Stream()
+        with torch.cuda.stream(first):
+            torch.cuda._sleep(cycles)
+        t0 = time.perf_counter()
+        with torch.cuda.stream(other):
+            torch.zeros(8, device="cuda")
+        other.synchronize()
+        quick = time.perf_counter() - t0 < 0.05
+        first.synchronize()
+        if quick:
+            return first, other
+    pytest.skip("every stream shares the first one's queue")
+
+
+def test_calls_do_not_wait_for_a_stream_that_is_not_there_yet():
+    """One thread's stream has 150 ms of other work before its 512x512 image; the
+    128x128 images of another thread, which do not fit beside that one, take
+    their usual time."""
+    cycles = sleep_cycles(150)
+    streams = independent_streams(cycles)
+    F, G = synth.gen_blobs(512, 512, 1), synth.gen_blobs(128, 128, 2)
+    refF, refG = oracle.sweep_dirty(F, 5, "8,4"), oracle.sweep_dirty(G, 5, "8,4")
+    wrong, times, stop = [], [], threading.Event()
+
+    def slow():
+        stream = streams[0]
+        with torch.cuda.stream(stream), thin.Context(stream=stream) as ctx:
+            src = torch.from_numpy(F).cuda()
+            while not stop.is_set():
+                t = src.clone()
+                torch.cuda._sleep(cycles)
+                ctx.run(t, 5, "8,4")
+                if not np.array_equal(t.cpu().numpy(), refF.image):
+                    wrong.append("slow")
+
+    def quick():
+        stream = streams[1]
+        with torch.cuda.stream(stream), thin.Context(stream=stream) as ctx:
+            src = torch.from_numpy(G).cuda()
+            for rep in range(40):
+                t = src.clone()
+                t0 = time.perf_counter()
+                st = ctx.run(t, 5, "8,4")
+                times.append(time.perf_counter() - t0)
+                if not (np.array_equal(t.cpu().numpy(), refG.image) and st.passes == refG.passes):
+                    wrong.append(rep)
+                time.sleep(0.02)
+        stop.set()
+
+    print("case other work in a stream", flush=True)
+    threads = [threading.Thread(target=f) for f in (slow, quick)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    print("ms:", [round(1e3 * x, 2) for x in sorted(times)], flush=True)
+    assert wrong == []
+    assert sorted(times[4:])[-2] < 0.03

@@ -5,6 +5,7 @@ admission to a device of kernels whose blocks wait for each other."""
 import ctypes
 import os
 import subprocess
+import time
 
 import pytest
 
@@ -62,8 +63,9 @@ extern "C" int rows(int h, int w, int cus) { return thin::rows_per_block(h, w, c
 @pytest.fixture(scope="module")
 def room(tmp_path_factory):
     """enter(device, which, blocks, holds) starts a thread that asks for room on
-    a device of 256 units; inside(i) says whether thread i has it (waiting up
-    to 20 s where it should), leave(i) lets it go."""
+    a device of 256 units, patient(..., microseconds) one that does so for a
+    while; inside(i, should) says whether thread i has room (1), waits (0) or
+    went without (2), waiting up to 20 s for `should`; leave(i) lets it go."""
     lib = compiled(tmp_path_factory.mktemp("room"), "room", """
 #include "room.h"
 #include <atomic>
@@ -77,21 +79,25 @@ struct Job {
 Job jobs[512];
 int n = 0;
 }
-extern "C" int enter(int device, int which, int blocks, int holds)
+extern "C" int patient(int device, int which, int blocks, int holds, int patience)
 {
     Job& j = jobs[n];
     j.th = std::thread([=, &j] {
-        const thin::Room room(device, which, blocks, holds, 256);
-        j.state = 1;
+        const thin::Room room(device, which, blocks, holds, 256, patience);
+        j.state = room.held() ? 1 : 2;
         while (!j.go) std::this_thread::sleep_for(std::chrono::milliseconds(1));
     });
     // until it has room or waits for it
     for (int k = 0; k < 50 && !j.state; ++k) std::this_thread::sleep_for(std::chrono::milliseconds(1));
     return n++;
 }
+extern "C" int enter(int device, int which, int blocks, int holds)
+{
+    return patient(device, which, blocks, holds, -1);
+}
 extern "C" int inside(int i, int should)
 {
-    for (int k = 0; k < 20000 && should && !jobs[i].state; ++k)
+    for (int k = 0; k < 20000 && should != jobs[i].state && should; ++k)
         std::this_thread::sleep_for(std::chrono::milliseconds(1));
     return jobs[i].state;
 }
@@ -141,3 +147,24 @@ def test_room_lets_what_fits_past_what_waits(room):
     room.leave(big)
     assert room.inside(ninth, 1) == 1
     room.leave(ninth)
+
+
+def test_room_is_waited_for_while_it_is_given_back(room):
+    """A kernel that could run another way leaves when no room has been given
+    back for its patience, counted anew each time some has; one that waits
+    behind it then has its turn."""
+    first = room.enter(62, 0, 64, 2048)
+    big = room.patient(62, 1, 242, 512, 600_000)
+    for _ in range(8):
+        i = room.enter(62, 2, 8, 512)
+        assert (room.inside(i, 1), room.inside(big, 0)) == (1, 0)
+        time.sleep(0.2)
+        room.leave(i)
+    ninth = room.enter(62, 2, 8, 512)
+    assert (room.inside(ninth, 0), room.inside(big, 0)) == (0, 0)
+    assert (room.inside(big, 2), room.inside(ninth, 1)) == (2, 1)
+    for i in (first, big, ninth):
+        room.leave(i)
+    alone = room.patient(62, 1, 242, 512, 0)
+    assert room.inside(alone, 1) == 1
+    room.leave(alone)

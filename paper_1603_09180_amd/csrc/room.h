@@ -45,6 +45,7 @@ public:
             return true;
         };
         while (!(held_ = may())) {
+            gate_.sought = std::chrono::steady_clock::now();
             if (patience < 0) {
                 gate_.freed.wait(lock);
                 continue;
@@ -74,6 +75,17 @@ public:
 
     bool held() const { return held_; }
 
+    // Whether somebody found no room within the last 10 seconds: then a caller
+    // asks for room only once its stream has come to the kernel (some
+    // microseconds more of a call), so that nobody waits for what the stream has
+    // to do before.
+    static bool sought(int device)
+    {
+        Gate& gate = gate_of(device);
+        const std::lock_guard<std::mutex> lock(gate.m);
+        return std::chrono::steady_clock::now() - gate.sought < std::chrono::seconds(10);
+    }
+
     static constexpr int kCoop = -1;  // which: k_coop; k_flow's are its shapes from 0 on
     static constexpr int kXcds = 8;
     static constexpr int kPasses = 8;
@@ -89,6 +101,7 @@ private:
         std::condition_variable freed;
         Waiter* first = nullptr;  // those that wait, in the order they came
         uint64_t left = 0;   // how many have given room back
+        std::chrono::steady_clock::time_point sought{};  // somebody waited last (or never)
         int used = 0;        // blocks of all that hold room
         int which = kMixed;  // the kernel they all are
     };

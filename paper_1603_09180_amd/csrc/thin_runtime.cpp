@@ -1057,6 +1057,22 @@ struct FlowBufs {
     uint64_t* exch;
 };
 
+// Before room is asked for: while others seek it, the stream's earlier work is
+// waited for (through an event, which on the null stream also follows the
+// streams that the null stream waits for).
+int come_to_kernel(thin_ctx* ctx)
+{
+    if (!thin::Room::sought(ctx->device)) return THIN_OK;
+    if (ctx->stream) {
+        const hipError_t e = hipStreamQuery(ctx->stream);
+        (void)hipGetLastError();
+        if (e == hipSuccess) return THIN_OK;
+    }
+    HIP_TRY(ctx, hipEventRecord(ctx->ev[0], ctx->stream));
+    HIP_TRY(ctx, hipEventSynchronize(ctx->ev[0]));
+    return THIN_OK;
+}
+
 int flow_control_words(int nimg) { return thin::kFlowCtl + nimg * thin::kFlowRing; }
 
 // Launches the small-image engine on `imgs` (tile map tile_img, exchange
@@ -1089,6 +1105,7 @@ int drive_flow(thin_ctx* ctx, int which, const std::vector<thin::FlowImg>& imgs,
     // need none (512x512 crests 3 ms, 128x128 blobs 0.25).
     int64_t pixels = 0;
     for (const thin::FlowImg& f : imgs) pixels += (int64_t)f.h * f.w;
+    if ((rc = come_to_kernel(ctx))) return rc;
     const thin::Room room(ctx->device, which, run.grid, ctx->flow_cap[which], ctx->num_cus,
                           300 + pixels / 100);
     if (!room.held()) {
@@ -1290,6 +1307,7 @@ int run_coop(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work,
         }
         HIP_TRY(ctx, hipEventRecord(ctx->prof_ev[0], ctx->stream));
     }
+    if ((rc = come_to_kernel(ctx))) return rc;
     const thin::Room room(ctx->device, thin::Room::kCoop, ctx->num_cus, 0, ctx->num_cus, -1);
     HIP_TRY(ctx, thin::launch_coop(ctx->stream, shape, d_imgs, d_cnt, d_tile_img, d_tile_last,
                                    ntiles, ctx->d_lut, d_small, d_small + 3, rounds_cap,

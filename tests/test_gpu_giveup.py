@@ -99,12 +99,13 @@ def independent_streams(cycles):
 def test_calls_do_not_wait_for_a_stream_that_is_not_there_yet():
     """One thread's stream has 150 ms of other work before its 512x512 image; the
     128x128 images of another thread, which do not fit beside that one, take
-    their usual time."""
+    their usual time: in one launch, but for those that come before the first
+    thread knows that room is sought."""
     cycles = sleep_cycles(150)
     streams = independent_streams(cycles)
     F, G = synth.gen_blobs(512, 512, 1), synth.gen_blobs(128, 128, 2)
     refF, refG = oracle.sweep_dirty(F, 5, "8,4"), oracle.sweep_dirty(G, 5, "8,4")
-    wrong, times, stop = [], [], threading.Event()
+    wrong, times, stop, launches = [], [], threading.Event(), []
 
     def slow():
         stream = streams[0]
@@ -119,16 +120,17 @@ def test_calls_do_not_wait_for_a_stream_that_is_not_there_yet():
 
     def quick():
         stream = streams[1]
-        with torch.cuda.stream(stream), thin.Context(stream=stream) as ctx:
+        with torch.cuda.stream(stream), thin.Context(stream=stream, profile=True) as ctx:
             src = torch.from_numpy(G).cuda()
-            for rep in range(40):
+            for rep in range(50):
                 t = src.clone()
                 t0 = time.perf_counter()
                 st = ctx.run(t, 5, "8,4")
                 times.append(time.perf_counter() - t0)
+                launches.append(int(ctx.profile(reset=True).launches))
                 if not (np.array_equal(t.cpu().numpy(), refG.image) and st.passes == refG.passes):
                     wrong.append(rep)
-                time.sleep(0.02)
+                time.sleep(0.01)
         stop.set()
 
     print("case other work in a stream", flush=True)
@@ -140,3 +142,4 @@ def test_calls_do_not_wait_for_a_stream_that_is_not_there_yet():
     print("ms:", [round(1e3 * x, 2) for x in sorted(times)], flush=True)
     assert wrong == []
     assert sorted(times[4:])[-2] < 0.03
+    assert sum(n == 1 for n in launches[20:]) >= 26, launches

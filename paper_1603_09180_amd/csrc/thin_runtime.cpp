@@ -134,8 +134,13 @@ struct thin_ctx {
     // step of its neighbours (microseconds), or for tiles queued behind an older
     // image (milliseconds); what waits longer is half resident beside another
     // process's kernel, and the bound is what that call loses (it goes on in
-    // rounds and does not try again).
+    // rounds and does not try again).  What left it half resident often stays
+    // (another process, a stream of few compute units), so the context's calls
+    // keep to rounds for a second after it, and twice as long each time it
+    // happens again, up to 64: a stay on a shared device loses 0.15 s a minute.
     int flow_polls = thin::kFlowPolls;
+    int flow_off_s = 0;
+    std::chrono::steady_clock::time_point flow_off_until{};
     int flow_cap[8] = {-1, -1, -1, -1, -1, -1, -1, -1};  // resident blocks by shape (-1: not asked)
     DevBuf grad;                   // gradient front-end scratch (8 floats per pixel)
     ImgCnt* h_snap[2] = {nullptr, nullptr};   // pinned snapshots of the counters
@@ -1021,6 +1026,7 @@ int choose_flow(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& wo
     if (ctx->engine != THIN_ENGINE_TILED || ctx->forced.th || ctx->graph || ctx->tail ||
         ctx->max_passes || ctx->flow_side == 0 || work.empty())
         return -1;
+    if (ctx->flow_off_s && std::chrono::steady_clock::now() < ctx->flow_off_until) return -1;
     int64_t total_px = 0;
     for (int i : work) total_px += ims[i].h * ims[i].w;
     const auto cls = size_class(total_px, (int64_t)work.size());
@@ -1145,6 +1151,12 @@ int drive_flow(thin_ctx* ctx, int which, const std::vector<thin::FlowImg>& imgs,
         thin_stats st;
         fill_stats(&st, c, c.last_step + 5, INT_MAX, false);
         if (stats) stats[src[n]] = st;
+    }
+    if (rest.empty()) {
+        ctx->flow_off_s = 0;
+    } else {
+        ctx->flow_off_s = std::min(64, std::max(1, 2 * ctx->flow_off_s));
+        ctx->flow_off_until = std::chrono::steady_clock::now() + std::chrono::seconds(ctx->flow_off_s);
     }
     ctx->last_launches = 1;
     ctx->last_tail_steps = 0;

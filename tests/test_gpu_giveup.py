@@ -44,6 +44,28 @@ def test_an_image_given_up_is_not_handed_back(monkeypatch):
     assert launches(F, 20, "8,4") == rounds + 1
 
 
+def test_a_give_up_is_remembered_for_a_while(monkeypatch):
+    """The calls of a context go straight to rounds for a second after a give-up,
+    then try the engine again; a context that did not give up uses it."""
+    F = ridges()
+    ref = oracle.sweep_dirty(F, 20, "8,4")
+    monkeypatch.setenv("THIN_FLOW", "0")
+    rounds = launches(F, 20, "8,4", ref)
+    monkeypatch.setenv("THIN_FLOW", "1,0")
+    print("case give-up remembered", flush=True)
+    seen = []
+    with thin.Context(profile=True) as ctx:
+        for pause in (0, 0, 0, 1.2, 0):
+            time.sleep(pause)
+            t = torch.from_numpy(F.copy()).cuda()
+            st = ctx.run(t, 20, "8,4")
+            assert np.array_equal(t.cpu().numpy(), ref.image) and st.passes == ref.passes
+            seen.append(int(ctx.profile(reset=True).launches))
+    assert seen == [rounds + 1, rounds, rounds, rounds + 1, rounds]
+    monkeypatch.setenv("THIN_FLOW", "1")
+    assert launches(F, 20, "8,4", ref) == 1
+
+
 def test_a_run_of_more_than_100000_passes():
     """A spiral corridor, consumed from its ends a pixel or two a pass: the
     engine stays with it to the end."""

@@ -86,10 +86,10 @@ enum {
     THIN_ENGINE_TILED = 1,    /* one launch per round of LDS tiles (several parity steps per
                                  residency, stable tiles skipped); the host checks convergence.
                                  Images whose tiles all fit the device at once run in one
-                                 launch instead (no pass cap, tile shape, graph or tail flag
-                                 set), tiles exchanging their halos on the device; such
-                                 launches wait for room on the device, first come first
-                                 served */
+                                 launch instead (no pass cap, tile shape, graph, tail or
+                                 rounds flag set), tiles exchanging their halos on the
+                                 device; such launches wait for room on the device while
+                                 others give room back, and run in rounds without */
     THIN_ENGINE_STEP = 2,     /* one parity step per launch over global memory (simple, slow) */
     /* 3 is not used (permanently unavailable: thin_create refuses it) */
     THIN_ENGINE_COOP = 4,     /* one cooperative launch for the whole run: the tiled engine's
@@ -127,11 +127,16 @@ enum {
     THIN_FLAG_PROFILE = 1,      /* time every round kernel with HIP events (see thin_profile) */
     THIN_FLAG_GRAPH = 2,        /* tiled engine: replay chunks of rounds as HIP graphs
                                    (ignored while THIN_FLAG_PROFILE is set) */
-    THIN_FLAG_TAIL = 4          /* tiled engine: hand a single image's convergence tail to the
+    THIN_FLAG_TAIL = 4,         /* tiled engine: hand a single image's convergence tail to the
                                    pixel work-list kernel once the image (at most 512x512
                                    pixels) lowers fewer than 2048 pixels per round; results are
                                    identical, and on MI355X it is measured slower than staying
                                    on the tiles, so it is off by default */
+    THIN_FLAG_ROUNDS = 8        /* tiled engine: rounds of launches for small images too.  For
+                                   callers whose stream has few compute units, or who share the
+                                   device with other processes: one launch holds a block for
+                                   every tile, and where they cannot all run at once it gives
+                                   up after about 0.15 s (results are identical) */
 };
 
 typedef struct thin_profile_info {

@@ -129,7 +129,8 @@ struct thin_ctx {
     DevBuf wl_imgs, wl_bits;       // pixel work-list engine: descriptors, global pending bitmaps
     DevBuf flow_imgs, flow_ctl, flow_exch;  // small-image engine (descriptors and tile map first)
     bool flow_held = false, hist_held = false;  // a call is using them; hist_bits
-    int flow_side = -1;            // small-image engine: -1 by size, 0 off, k its k-th shape
+    int flow_side = -1;            // small-image engine: -1 by size, 0 off (THIN_FLAG_ROUNDS),
+                                   // k its k-th shape
     // Polls of a wait before it gives up, about 1 us each.  A block waits for a
     // step of its neighbours (microseconds), or for tiles queued behind an older
     // image (milliseconds); what waits longer is half resident beside another
@@ -1830,7 +1831,7 @@ int thin_create(thin_ctx** out, const thin_config* cfg)
     ctx->max_device_bytes = c.max_device_bytes;
     ctx->max_passes = c.max_passes;
     ctx->forced = forced;
-    ctx->flow_side = flow_side;
+    ctx->flow_side = c.flags & THIN_FLAG_ROUNDS ? 0 : flow_side;
     ctx->flow_polls = flow_polls;
     ctx->profile = (c.flags & THIN_FLAG_PROFILE) != 0;
     ctx->tail = (c.flags & THIN_FLAG_TAIL) != 0;

@@ -23,6 +23,7 @@ THIN_ENGINE_WORKLIST = 5
 THIN_FLAG_PROFILE = 1
 THIN_FLAG_GRAPH = 2
 THIN_FLAG_TAIL = 4
+THIN_FLAG_ROUNDS = 8
 
 EXPORTED = [
     "thin_create", "thin_run", "thin_run_noalloc", "thin_skeleton", "thin_run_batch", "thin_serve_admit",
@@ -370,7 +371,7 @@ class Context:
                  max_device_bytes: int = 0, max_passes: int = 0, tile: int = 0,
                  steps_per_round: int = 0, profile: bool = False, graph: bool = False,
                  threads: int = 0, variant: int = 0, tune_cache: str | None = None,
-                 tail: bool = False):
+                 tail: bool = False, rounds: bool = False):
         import torch
 
         if stream is None:
@@ -386,7 +387,7 @@ class Context:
         cfg.threads = threads
         cfg.variant = variant
         cfg.flags = ((THIN_FLAG_PROFILE if profile else 0) | (THIN_FLAG_GRAPH if graph else 0)
-                     | (THIN_FLAG_TAIL if tail else 0))
+                     | (THIN_FLAG_TAIL if tail else 0) | (THIN_FLAG_ROUNDS if rounds else 0))
         cfg.tune_cache = tune_cache.encode() if tune_cache else None
         self.device = device
         self.stream = stream

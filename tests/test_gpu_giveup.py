@@ -66,6 +66,19 @@ def test_a_give_up_is_remembered_for_a_while(monkeypatch):
     assert launches(F, 20, "8,4", ref) == 1
 
 
+@pytest.mark.parametrize("env", ["", "1", "1,0"])
+def test_rounds_by_the_flag(env, monkeypatch):
+    """The flag keeps small images to rounds, whatever shape is asked for."""
+    F = ridges()
+    ref = oracle.sweep_dirty(F, 20, "8,4")
+    if env:
+        monkeypatch.setenv("THIN_FLOW", env)
+    print("case rounds flag", env, flush=True)
+    n = launches(F, 20, "8,4", ref, rounds=True)
+    monkeypatch.setenv("THIN_FLOW", "0")
+    assert n == launches(F, 20, "8,4", ref)
+
+
 def test_a_run_of_more_than_100000_passes():
     """A spiral corridor, consumed from its ends a pixel or two a pass: the
     engine stays with it to the end."""

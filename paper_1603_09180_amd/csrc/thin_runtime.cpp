@@ -442,7 +442,9 @@ void load_tune_cache(thin_ctx* ctx)
     fclose(f);
 }
 
-void save_tune_cache(const thin_ctx* ctx, std::pair<int, int> cls, TileShape sh, double ms, bool flow)
+// Writes the class's line; flow: what to record of the small-image engine (0 it
+// was slower, 1 faster, -1 not measured: the file keeps what it says).
+void save_tune_cache(const thin_ctx* ctx, std::pair<int, int> cls, TileShape sh, double ms, int flow)
 {
     if (ctx->tune_cache.empty()) return;
     std::vector<std::string> keep;
@@ -452,8 +454,8 @@ void save_tune_cache(const thin_ctx* ctx, std::pair<int, int> cls, TileShape sh,
             char arch[64];
             int a, b;
             if (sscanf(line, "%63s %d %d", arch, &a, &b) == 3 &&
-                (ctx->arch == arch || ctx->arch + kFlowMark == arch) && a == cls.first &&
-                b == cls.second)
+                (ctx->arch == arch || (flow >= 0 && ctx->arch + kFlowMark == arch)) &&
+                a == cls.first && b == cls.second)
                 continue;  // replaced below
             keep.push_back(line);
         }
@@ -463,7 +465,7 @@ void save_tune_cache(const thin_ctx* ctx, std::pair<int, int> cls, TileShape sh,
     FILE* f = fopen(tmp.c_str(), "w");
     if (!f) return;
     for (const std::string& l : keep) fputs(l.c_str(), f);
-    for (int mark = 0; mark <= (flow ? 1 : 0); ++mark)
+    for (int mark = 0; mark <= (flow == 1 ? 1 : 0); ++mark)
         fprintf(f, "%s%s %d %d %d %d %d %d %d %.4f\n", ctx->arch.c_str(), mark ? kFlowMark : "",
                 cls.first, cls.second, sh.th, sh.tw, sh.k, sh.nt, sh.var, ms);
     fclose(f);
@@ -1624,6 +1626,7 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
         // Untuned choice first (also warms the context's buffers).
         const auto cls = size_class(total_px, (int64_t)work_img.size());
         const auto prev = ctx->tuned.find(cls);
+        const bool prev_flow = ctx->tuned_flow.count(cls) != 0;
         TileShape prev_shape{0, 0, 0, 0, 0};
         if (prev != ctx->tuned.end()) {
             prev_shape = prev->second;
@@ -1666,12 +1669,14 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
             res.candidates = (int32_t)timed.size();
             ctx->tuned[cls] = best;
             // the small-image engine stays the choice of these images where
-            // it beats the best tile shape
+            // it beats the best tile shape; where this context may not use it,
+            // or could not finish, what was known of it stays
             ctx->tuned_flow.insert(cls);
             const int flow = choose_flow(ctx, work_img.data(), work, kFlowWaves);
-            bool faster = false;
+            int faster = -1;
             for (int k = 0; flow >= 0 && k < 2 && rc == THIN_OK; ++k) {
                 std::vector<int> rest;
+                faster = -1;
                 if (hipMemcpyAsync(scratch, pristine, bytes, hipMemcpyDeviceToDevice, ctx->stream) !=
                         hipSuccess ||
                     hipStreamSynchronize(ctx->stream) != hipSuccess) {
@@ -1685,7 +1690,7 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
                 if (r != THIN_OK || !rest.empty()) break;
                 faster = std::chrono::duration<double, std::milli>(t1 - t0).count() < res.ms;
             }
-            if (!faster) ctx->tuned_flow.erase(cls);
+            if (faster == 0 || (faster < 0 && !prev_flow)) ctx->tuned_flow.erase(cls);
             save_tune_cache(ctx, cls, best, res.ms, faster);
         } else if (prev_shape.th) {
             ctx->tuned[cls] = prev_shape;

@@ -1,7 +1,7 @@
 """Paths that image sizes alone no longer lead every test to: the rounds of
 launches out of the static array, the default shape's rounds on mixed batches,
-the last images of a batch handed over, and engine launches larger than one
-block to a compute unit from several threads.  Results against the oracle, and
+the last images of a batch handed over, engine launches larger than one
+block to a compute unit from several threads, and what tuning records.  Results against the oracle, and
 the path by the launches taken."""
 import threading
 
@@ -128,3 +128,26 @@ def test_large_launches_from_several_threads(monkeypatch):
     print(launches, flush=True)
     assert wrong == []
     assert 1 in launches[0] + launches[1]      # the engine took some of them
+
+
+@pytest.mark.parametrize("kw", [dict(rounds=True), dict(graph=True), dict(max_passes=500)],
+                         ids=["rounds", "graph", "cap"])
+def test_tuning_without_the_engine_keeps_its_record(kw, tmp_path):
+    """A context that may not use the small-image engine tunes the class's shape
+    and leaves the record that the engine beat it; a file without the record
+    gets none."""
+    arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
+    F = image(300, 200, 4321, np.uint8)
+    path = tmp_path / "tune.txt"
+    line = " 15 15 64 64 16 256 3 1.0"
+    for record in (True, False):
+        path.write_text(arch + line + "\n" + (arch + "+flow" + line + "\n" if record else ""))
+        print("case tuning without the engine", kw, record, flush=True)
+        with thin.Context(tune_cache=str(path), **kw) as ctx:
+            ctx.autotune([torch.from_numpy(F.copy()).cuda()], [5], [0], reps=1)
+        names = [l.split()[0] for l in path.read_text().splitlines()]
+        assert sorted(names) == [arch] + [arch + "+flow"] * record
+        t = torch.from_numpy(F.copy()).cuda()
+        with thin.Context(tune_cache=str(path), profile=True) as ctx:
+            assert_image(t, ctx.run(t, 5, "8,4"), oracle.sweep_dirty(F, 5, "8,4"))
+            assert (ctx.profile().launches == 1) == record

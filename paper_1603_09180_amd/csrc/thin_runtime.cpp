@@ -1613,12 +1613,25 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
         work.push_back((int)j);
         ++j;
     }
-    auto run_one = [&](TileShape shape, double& ms) -> int {
+    auto restore = [&]() -> int {
         if (hipMemcpyAsync(scratch, pristine, bytes, hipMemcpyDeviceToDevice, ctx->stream) !=
                 hipSuccess ||
             hipStreamSynchronize(ctx->stream) != hipSuccess)
             return fail(ctx, THIN_EDEVICE, "autotune copy failed");
-        return timed_run(ctx, work_img.data(), work, shape, ms);
+        return THIN_OK;
+    };
+    auto run_one = [&](TileShape shape, double& ms) -> int {
+        const int rc = restore();
+        return rc ? rc : timed_run(ctx, work_img.data(), work, shape, ms);
+    };
+    // a call as it is without tuning, the small-image engine included
+    auto run_untuned = [&](double& ms) -> int {
+        int rc = restore();
+        if (rc) return rc;
+        const auto t0 = std::chrono::steady_clock::now();
+        rc = run_images(ctx, work_img.data(), (int)work_img.size(), nullptr);
+        ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
+        return rc == THIN_ELIMIT ? THIN_OK : rc;
     };
     thin_tune_result res{};
     TileShape best{0, 0, 0, 0, 0};
@@ -1632,9 +1645,8 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
             prev_shape = prev->second;
             ctx->tuned.erase(prev);
         }
-        const TileShape dflt = choose_shape(ctx, total_px, (int64_t)work_img.size());
         double ms = 0.0;
-        if ((rc = run_one(dflt, ms)) == THIN_OK) rc = run_one(dflt, ms);
+        if ((rc = run_untuned(ms)) == THIN_OK) rc = run_untuned(ms);
         res.default_ms = ms;
         std::vector<TileShape> shapes(thin::compiled_shapes(nullptr, 0));
         thin::compiled_shapes(shapes.data(), (int)shapes.size());
@@ -1677,12 +1689,7 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
             for (int k = 0; flow >= 0 && k < 2 && rc == THIN_OK; ++k) {
                 std::vector<int> rest;
                 faster = -1;
-                if (hipMemcpyAsync(scratch, pristine, bytes, hipMemcpyDeviceToDevice, ctx->stream) !=
-                        hipSuccess ||
-                    hipStreamSynchronize(ctx->stream) != hipSuccess) {
-                    rc = fail(ctx, THIN_EDEVICE, "autotune copy failed");
-                    break;
-                }
+                if ((rc = restore())) break;
                 const auto t0 = std::chrono::steady_clock::now();
                 const int r = run_flow(ctx, flow, work_img.data(), work, nullptr, rest);
                 const auto t1 = std::chrono::steady_clock::now();

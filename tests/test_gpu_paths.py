@@ -151,3 +151,18 @@ def test_tuning_without_the_engine_keeps_its_record(kw, tmp_path):
         with thin.Context(tune_cache=str(path), profile=True) as ctx:
             assert_image(t, ctx.run(t, 5, "8,4"), oracle.sweep_dirty(F, 5, "8,4"))
             assert (ctx.profile().launches == 1) == record
+
+
+def test_tuning_times_the_untuned_call():
+    """default_ms is a call of the context without tuning: for small crests one
+    launch of the engine (1.37 ms, the best shape's rounds 2.2), and with the
+    engine kept out a run in rounds (2.46)."""
+    t = torch.from_numpy(synth.ridges_512().image()).cuda()
+    print("case tuning, untuned call", flush=True)
+    with thin.Context() as ctx:
+        res = ctx.autotune([t], [20], [0], reps=2)
+    with thin.Context(rounds=True) as ctx:
+        kept_out = ctx.autotune([t], [20], [0], reps=2)
+    print(res, kept_out, flush=True)
+    assert res["default_ms"] < 0.85 * res["ms"]
+    assert kept_out["default_ms"] > 0.85 * kept_out["ms"]

@@ -24,7 +24,6 @@
 #include <map>
 #include <set>
 #include <new>
-#include <optional>
 #include <string>
 #include <vector>
 
@@ -128,7 +127,7 @@ struct thin_ctx {
     DevBuf twin, imgs, cnt, tile_img, tile_last, small, hist_bits, hist_round, wl_list, wl_meta;
     DevBuf wl_imgs, wl_bits;       // pixel work-list engine: descriptors, global pending bitmaps
     DevBuf flow_imgs, flow_ctl, flow_exch;  // small-image engine (descriptors and tile map first)
-    bool flow_held = false, hist_held = false;  // a call is using them; hist_bits
+    bool flow_held = false;        // a call is using them
     int flow_side = -1;            // small-image engine: -1 by size, 0 off (THIN_FLAG_ROUNDS),
                                    // k its k-th shape
     // Polls of a wait before it gives up, about 1 us each.  A block waits for a
@@ -211,10 +210,9 @@ int fail(thin_ctx* ctx, int code, const char* fmt, ...)
             return fail((ctx), THIN_EDEVICE, "%s failed: %s", #expr, hipGetErrorString(e_)); \
     } while (0)
 
-// Frees the scratch that a call can do without, unless it is using it: the
-// small-image engine's and the change bitmaps.  Held between calls for speed
-// alone, so a call that does not fit beside it takes its place.  Whether
-// anything was freed.
+// Frees the scratch that a call can do without: the small-image engine's,
+// unless the call is using it.  Held between calls for speed alone, so a call
+// that does not fit beside it takes its place.  Whether anything was freed.
 bool shed(thin_ctx* ctx)
 {
     bool freed = false;
@@ -228,18 +226,8 @@ bool shed(thin_ctx* ctx)
     };
     if (!ctx->flow_held)
         for (DevBuf* b : {&ctx->flow_imgs, &ctx->flow_ctl, &ctx->flow_exch}) drop(*b);
-    if (!ctx->hist_held) drop(ctx->hist_bits);
     return freed;
 }
-
-// Marks hist_bits as in use for the rest of a run.
-struct HoldHistory {
-    explicit HoldHistory(thin_ctx* c) : ctx(c) { ctx->hist_held = true; }
-    ~HoldHistory() { ctx->hist_held = false; }
-    HoldHistory(const HoldHistory&) = delete;
-    HoldHistory& operator=(const HoldHistory&) = delete;
-    thin_ctx* ctx;
-};
 
 size_t rounded(size_t bytes) { return (bytes + 255) & ~size_t(255); }
 
@@ -478,34 +466,19 @@ TileShape choose_shape(const thin_ctx* ctx, int64_t total_pixels, int64_t images
     auto it = ctx->tuned.find(size_class(total_pixels, images));
     if (it != ctx->tuned.end()) return it->second;
     // Small work lists are bound by the latency of each round: small tiles
-    // with one cell per thread and register windows, seeded (512x512 crests in
-    // rounds of launches: 2.57 ms, 3.01 unseeded).  Large ones are bound by
+    // with one cell per thread and register windows, which start with every
+    // candidate pending: seeds from change bitmaps cost more to read than the
+    // first steps take (seeded, in ms: 512x512 crests 2.48 against 2.25 without,
+    // 1000x1000 crests 8.98 and 8.14, 128x128 blobs 0.242 and 0.228, 16 of them
+    // 0.43 and 0.39), and the bitmaps take scratch.  Large ones are bound by
     // throughput: dense per-step work lists with seeded flags in 128x128
     // tiles (less halo work per pixel).  Between, it is the content that
     // decides (1400x1500 crests 14.9 ms in 32x32 tiles, 24.2 in 128x128;
     // 2048x2048 blobs 693 us and 610), so the line stays where only a few
     // hundred of the small tiles are left to a launch.
     (void)images;
-    if (total_pixels <= (int64_t)1 << 20) return TileShape{32, 32, 16, 1024, thin::kVarRegsSeeded};
+    if (total_pixels <= (int64_t)1 << 20) return TileShape{32, 32, 16, 1024, thin::kVarRegs};
     return TileShape{128, 128, 16, 512, thin::kVarBitsSeeded};
-}
-
-// The run's change bitmaps, asked for after all its other scratch (HoldHistory
-// from before).  Where they do not fit, register windows chosen by size go
-// without their seeds: every call of up to 2^20 pixels fits the cap that the
-// rest needs.
-int ensure_history(thin_ctx* ctx, TileShape& shape, int ntiles, int64_t total_pixels, int64_t images)
-{
-    auto ask = [&] {
-        return ensure(ctx, ctx->hist_bits,
-                      sizeof(uint32_t) * 2 * (size_t)ntiles * thin::history_words(shape));
-    };
-    const int rc = ask();
-    if (rc != THIN_ENOMEM || shape.var != thin::kVarRegsSeeded || ctx->forced.th ||
-        ctx->tuned.count(size_class(total_pixels, images)))
-        return rc;
-    shape.var = thin::kVarRegs;
-    return ask();
 }
 
 void fill_stats(thin_stats* st, const ImgCnt& c, int steps_done, int max_steps, bool trivial)
@@ -913,7 +886,7 @@ int run_tiled(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work
 {
     int64_t total_px = 0;
     for (int i : work) total_px += ims[i].h * ims[i].w;
-    TileShape shape = choose_shape(ctx, total_px, (int64_t)work.size());
+    const TileShape shape = choose_shape(ctx, total_px, (int64_t)work.size());
     if (!thin::tile_shape_supported(shape))
         return fail(ctx, THIN_EINVAL, "unsupported tile shape %dx%d k=%d", shape.th, shape.tw, shape.k);
     const int max_steps = steps_cap(ctx);
@@ -947,6 +920,9 @@ int run_tiled(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work
     if ((rc = ensure(ctx, ctx->cnt, sizeof(ImgCnt) * nimg))) return rc;
     if ((rc = ensure(ctx, ctx->tile_img, sizeof(int32_t) * ntiles))) return rc;
     if ((rc = ensure(ctx, ctx->tile_last, sizeof(int32_t) * 2 * (size_t)ntiles))) return rc;
+    if ((rc = ensure(ctx, ctx->hist_bits,
+                     sizeof(uint32_t) * 2 * (size_t)ntiles * thin::history_words(shape))))
+        return rc;
     if ((rc = ensure(ctx, ctx->hist_round, sizeof(int32_t) * 2 * (size_t)ntiles))) return rc;
     if ((rc = ensure_snap(ctx, nimg))) return rc;
     if ((rc = ensure(ctx, ctx->small, 64))) return rc;
@@ -954,8 +930,6 @@ int run_tiled(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work
     // by the round before.
     if ((rc = ensure(ctx, ctx->wl_list, sizeof(int32_t) * 2 * (size_t)ntiles))) return rc;
     if ((rc = ensure(ctx, ctx->wl_meta, sizeof(int32_t) * (12 + (size_t)ntiles)))) return rc;
-    std::optional<HoldHistory> hold(ctx);
-    if ((rc = ensure_history(ctx, shape, ntiles, total_px, (int64_t)work.size()))) return rc;
 
     TiledBufs b{};
     b.imgs = static_cast<ImgDev*>(ctx->imgs.ptr);
@@ -974,7 +948,6 @@ int run_tiled(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work
     Handover hand{ims, plan.src_index.data(), {}, {}, 0};
     rc = drive_tiled(ctx, shape, plan.imgs.data(), nimg, ntiles, b, plan.src_index.data(), stats,
                      true, hand_over ? &hand : nullptr);
-    hold.reset();
     if (rc || hand.images.empty()) return rc;
     // The last images, from their states in the callers' buffers; what the
     // small-image engine cannot take goes on in rounds.
@@ -1294,10 +1267,11 @@ int run_coop(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work,
     if ((rc = ensure(ctx, ctx->tile_img, sizeof(int32_t) * ntiles))) return rc;
     if ((rc = ensure(ctx, ctx->tile_last, sizeof(int32_t) * 2 * (size_t)ntiles))) return rc;
     if ((rc = ensure(ctx, ctx->small, 64))) return rc;
+    if ((rc = ensure(ctx, ctx->hist_bits,
+                     sizeof(uint32_t) * 2 * (size_t)ntiles * thin::history_words(shape))))
+        return rc;
     if ((rc = ensure(ctx, ctx->hist_round, sizeof(int32_t) * 2 * (size_t)ntiles))) return rc;
     if ((rc = ensure_snap(ctx, nimg))) return rc;
-    const HoldHistory hold(ctx);
-    if ((rc = ensure_history(ctx, shape, ntiles, total_px, (int64_t)work.size()))) return rc;
 
     ImgDev* d_imgs = static_cast<ImgDev*>(ctx->imgs.ptr);
     ImgCnt* d_cnt = static_cast<ImgCnt*>(ctx->cnt.ptr);

@@ -1,5 +1,5 @@
 """The scratch cap (thin_config.max_device_bytes): what the small-image engine
-and the seeded windows hold for speed never makes a call fail that fits the cap
+and change bitmaps hold for speed never makes a call fail that fits the cap
 without them, whatever ran on the context before."""
 import numpy as np
 import pytest
@@ -51,15 +51,15 @@ def test_many_small_images():
 @pytest.mark.parametrize("kw", [dict(), dict(max_passes=1000), dict(engine=thin.THIN_ENGINE_COOP)],
                          ids=["auto", "rounds", "coop"])
 def test_rounds_without_change_bitmaps(kw):
-    """A 512x512 image takes 273408 bytes of twin, tile state and queues; the
-    change bitmaps of the default shape (64 KB) do not fit beside them."""
+    """A 512x512 image takes 273408 bytes of twin, tile state and queues; change
+    bitmaps (64 KB in seeded tiles) would not fit beside them."""
     with thin.Context(max_device_bytes=274_000, **kw) as ctx:
         check(ctx, image(512, 512, 5), 5, "8,4")
 
 
 def test_change_bitmaps_give_way():
-    """Under 400 kB the first image has its change bitmaps, and the second one's
-    larger twin takes their place."""
+    """Under 400 kB the second image's larger twin takes the place of the first
+    one's; change bitmaps kept from the first would leave no room for it."""
     with thin.Context(max_device_bytes=400_000, max_passes=1000) as ctx:
         for h, w in [(512, 512), (600, 560), (512, 512)]:
             check(ctx, image(h, w, h), 5, "8,4")

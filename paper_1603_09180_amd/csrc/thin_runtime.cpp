@@ -1524,17 +1524,21 @@ int run_images(thin_ctx* ctx, const thin_image* ims, int n, thin_stats* stats)
     return run_tiled(ctx, ims, work, stats, rest.empty());
 }
 
-// One tiled run over `work` of ims with `shape` forced; wall time in ms
-// (the run synchronises the stream before returning).
-int timed_run(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work, TileShape shape,
-              double& ms)
+// One tiled run over `work` (of size class cls) of ims, as a call with `shape`
+// tuned for that class runs it, its last images handed over; wall time in ms
+// (the run synchronises the stream before returning).  A context with a forced
+// shape hands nothing over, and tries `shape` in its place.
+int timed_run(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& work,
+              std::pair<int, int> cls, TileShape shape, double& ms)
 {
     const TileShape saved = ctx->forced;
-    ctx->forced = shape;
+    if (saved.th) ctx->forced = shape;
+    else ctx->tuned[cls] = shape;
     const auto t0 = std::chrono::steady_clock::now();
-    int rc = run_tiled(ctx, ims, work, nullptr);
+    int rc = run_tiled(ctx, ims, work, nullptr, true);
     const auto t1 = std::chrono::steady_clock::now();
     ctx->forced = saved;
+    if (!saved.th) ctx->tuned.erase(cls);
     if (rc == THIN_ELIMIT) rc = THIN_OK;
     ms = std::chrono::duration<double, std::milli>(t1 - t0).count();
     return rc;
@@ -1571,6 +1575,7 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
         return fail(ctx, THIN_ENOMEM, "autotune copies of %zu bytes", 2 * bytes);
     }
     int rc = THIN_OK;
+    const auto cls = size_class(total_px, (int64_t)work_img.size());
     std::vector<int> work;
     for (size_t k = 0, j = 0; k < (size_t)n; ++k) {
         const thin_image& im = imgs[k];
@@ -1596,7 +1601,7 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
     };
     auto run_one = [&](TileShape shape, double& ms) -> int {
         const int rc = restore();
-        return rc ? rc : timed_run(ctx, work_img.data(), work, shape, ms);
+        return rc ? rc : timed_run(ctx, work_img.data(), work, cls, shape, ms);
     };
     // a call as it is without tuning, the small-image engine included
     auto run_untuned = [&](double& ms) -> int {
@@ -1611,9 +1616,8 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
     TileShape best{0, 0, 0, 0, 0};
     if (rc == THIN_OK) {
         // Untuned choice first (also warms the context's buffers).
-        const auto cls = size_class(total_px, (int64_t)work_img.size());
         const auto prev = ctx->tuned.find(cls);
-        const bool prev_flow = ctx->tuned_flow.count(cls) != 0;
+        const bool prev_flow = ctx->tuned_flow.erase(cls) != 0;
         TileShape prev_shape{0, 0, 0, 0, 0};
         if (prev != ctx->tuned.end()) {
             prev_shape = prev->second;
@@ -1673,8 +1677,9 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
             }
             if (faster == 0 || (faster < 0 && !prev_flow)) ctx->tuned_flow.erase(cls);
             save_tune_cache(ctx, cls, best, res.ms, faster);
-        } else if (prev_shape.th) {
-            ctx->tuned[cls] = prev_shape;
+        } else {
+            if (prev_shape.th) ctx->tuned[cls] = prev_shape;
+            if (prev_flow) ctx->tuned_flow.insert(cls);
         }
     }
     (void)hipStreamSynchronize(ctx->stream);

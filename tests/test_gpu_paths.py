@@ -166,3 +166,21 @@ def test_tuning_times_the_untuned_call():
     print(res, kept_out, flush=True)
     assert res["default_ms"] < 0.85 * res["ms"]
     assert kept_out["default_ms"] > 0.85 * kept_out["ms"]
+
+
+def test_tuning_times_shapes_as_they_run(monkeypatch):
+    """Shapes are timed with the last images handed over, as the calls that will
+    use the choice run them: far fewer launches than without the engine, though
+    the call as a whole does not qualify for it."""
+    Fs = [image(300, 300, 700 + i, np.uint8) for i in range(29)]
+    Fs.append(synth.gen_ridges(300, 300, 41, np.uint8))
+    ts = [torch.from_numpy(F).cuda() for F in Fs]
+    monkeypatch.setenv("THIN_FLOW", "2")
+    n = {}
+    for rounds in (True, False):
+        print("case tuning with hand-over", rounds, flush=True)
+        with thin.Context(rounds=rounds, profile=True) as ctx:
+            ctx.autotune(ts, [12] * 30, [0] * 30, reps=1)
+            n[rounds] = int(ctx.profile().launches)
+    print(n, flush=True)
+    assert n[False] < 0.7 * n[True]

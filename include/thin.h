@@ -132,11 +132,11 @@ enum {
                                    pixels) lowers fewer than 2048 pixels per round; results are
                                    identical, and on MI355X it is measured slower than staying
                                    on the tiles, so it is off by default */
-    THIN_FLAG_ROUNDS = 8        /* tiled engine: rounds of launches for small images too.  For
-                                   callers whose stream has few compute units, or who share the
-                                   device with other processes: one launch holds a block for
-                                   every tile, and where they cannot all run at once it gives
-                                   up after about 0.15 s (results are identical) */
+    THIN_FLAG_ROUNDS = 8        /* tiled engine: rounds of launches for small images too (as on
+                                   a stream with a compute-unit mask).  For callers who share
+                                   the device with kernels that stay: one launch holds a block
+                                   for every tile, and where they cannot all run at once it
+                                   gives up after about 0.15 s (results are identical) */
 };
 
 typedef struct thin_profile_info {

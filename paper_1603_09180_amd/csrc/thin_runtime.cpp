@@ -128,16 +128,18 @@ struct thin_ctx {
     DevBuf wl_imgs, wl_bits;       // pixel work-list engine: descriptors, global pending bitmaps
     DevBuf flow_imgs, flow_ctl, flow_exch;  // small-image engine (descriptors and tile map first)
     bool flow_held = false;        // a call is using them
-    int flow_side = -1;            // small-image engine: -1 by size, 0 off (THIN_FLAG_ROUNDS),
-                                   // k its k-th shape
+    int flow_side = -1;            // small-image engine: -1 by size, 0 off (THIN_FLAG_ROUNDS,
+                                   // or a stream of fewer compute units), k its k-th shape
     // Polls of a wait before it gives up, about 1 us each.  A block waits for a
     // step of its neighbours (microseconds), or for tiles queued behind an older
     // image (milliseconds); what waits longer is half resident beside another
     // process's kernel, and the bound is what that call loses (it goes on in
-    // rounds and does not try again).  What left it half resident often stays
-    // (another process, a stream of few compute units), so the context's calls
-    // keep to rounds for a second after it, and twice as long each time it
-    // happens again, up to 64: a stay on a shared device loses 0.15 s a minute.
+    // rounds and does not try again).  What left it half resident often stays,
+    // so the context's calls keep to rounds for a second after it, and twice as
+    // long each time it happens again, up to 64: a stay on such a device loses
+    // 0.15 s a minute.  (Two processes with 128x128 blobs, 512x512 or 1283x1025
+    // crests at once were not seen to: 0.15, 3.3 and 8.3 ms a call each, in
+    // rounds 0.58, 4.5 and 13.8.)
     int flow_polls = thin::kFlowPolls;
     int flow_off_s = 0;
     std::chrono::steady_clock::time_point flow_off_until{};
@@ -1834,6 +1836,15 @@ int thin_create(thin_ctx** out, const thin_config* cfg)
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c.device) == hipSuccess &&
             cus > 0)
             ctx->num_cus = cus;
+        // A stream restricted to some compute units cannot hold what the device
+        // does, so nothing on it may need all its blocks resident.
+        uint32_t mask[32] = {};
+        int mine = 0;
+        if (hipExtStreamGetCUMask(ctx->stream, 32, mask) == hipSuccess)
+            for (uint32_t m : mask) mine += __builtin_popcount(m);
+        else
+            (void)hipGetLastError();
+        if (mine > 0 && mine < ctx->num_cus) ctx->flow_side = 0;
         hipDeviceProp_t prop;
         if (hipGetDeviceProperties(&prop, c.device) == hipSuccess) {
             // "gfx950:sramecc+:xnack-" -> "gfx950"

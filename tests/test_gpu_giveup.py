@@ -79,6 +79,25 @@ def test_rounds_by_the_flag(env, monkeypatch):
     assert n == launches(F, 20, "8,4", ref)
 
 
+def test_a_stream_of_few_compute_units(monkeypatch):
+    """A stream with a compute-unit mask keeps to rounds: it cannot hold the blocks
+    that the device holds."""
+    import ctypes
+
+    hip = ctypes.CDLL("libamdhip64.so")
+    handle = ctypes.c_void_p()
+    mask = (ctypes.c_uint32 * 8)(*[0x0000FFFF] * 8)
+    torch.zeros(1, device="cuda")
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), 8, mask) == 0
+    F = ridges()
+    ref = oracle.sweep_dirty(F, 20, "8,4")
+    print("case masked stream", flush=True)
+    n = launches(F, 20, "8,4", ref, stream=torch.cuda.ExternalStream(handle.value))
+    assert hip.hipStreamDestroy(handle) == 0
+    monkeypatch.setenv("THIN_FLOW", "0")
+    assert n == launches(F, 20, "8,4", ref)
+
+
 def test_a_run_of_more_than_100000_passes():
     """A spiral corridor, consumed from its ends a pixel or two a pass: the
     engine stays with it to the end."""

@@ -2259,7 +2259,10 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
         uint64_t* const ex = exch + im.word0;
         const Lambda lambda = lambda_of(im.lambda);
         int lowered = 0, last = -1;  // of the wave, over all rounds
-        unsigned long long exams = 0;
+        // (a candidate is examined once, and again after a pixel of its 4x4 window
+        // fell: 768 candidates of a wave times 16 pixels of 65535 levels fit 32
+        // bits)
+        unsigned exams = 0;
         int32_t* const image_mark = &cnt[im.slot].pad;
         int32_t* const ring = ctl + im.ctl0;
         const bool counts = lt == 0 && tid < 64;  // the wave that counts the image's votes
@@ -2270,7 +2273,7 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
             typename T::Counts n;
             T::steps(q, s_img, s_flags, nullptr, K, tid, s_lut, lambda, n);
             lowered += n.lowered;
-            exams += (unsigned)n.exams;
+            exams += n.exams;
             if (n.last >= 0) last = r * K + n.last;
             if (n.last >= K - 4 && (tid & 63) == 0) s_act = 1;
             const uint32_t tag = (uint32_t)r + 1u;
@@ -2374,7 +2377,7 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
                 atomicAdd(&s_count, lowered);
                 atomicMax(&s_last, last);
             }
-            if (exams) atomicAdd(&s_exam, exams);
+            if (exams) atomicAdd(&s_exam, (unsigned long long)exams);
         }
         __syncthreads();
         if (tid == 0) {

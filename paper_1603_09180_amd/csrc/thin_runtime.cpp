@@ -475,9 +475,10 @@ TileShape choose_shape(const thin_ctx* ctx, int64_t total_pixels, int64_t images
     // 0.43 and 0.39), and the bitmaps take scratch.  Large ones are bound by
     // throughput: dense per-step work lists with seeded flags in 128x128
     // tiles (less halo work per pixel).  Between, it is the content that
-    // decides (1400x1500 crests 14.9 ms in 32x32 tiles, 24.2 in 128x128;
-    // 2048x2048 blobs 693 us and 610), so the line stays where only a few
-    // hundred of the small tiles are left to a launch.
+    // decides (1400x1500 crests 10.4 ms in 32x32 tiles, 12.5 in 128x128;
+    // 2048x2048 blobs 650 us and 517; 1000x1000 crests 8.1 ms and 8.7, blobs 450
+    // us and 500), so the line stays where only a few hundred of the small
+    // tiles are left to a launch.
     (void)images;
     if (total_pixels <= (int64_t)1 << 20) return TileShape{32, 32, 16, 1024, thin::kVarRegs};
     return TileShape{128, 128, 16, 512, thin::kVarBitsSeeded};
@@ -1085,8 +1086,9 @@ int drive_flow(thin_ctx* ctx, int which, const std::vector<thin::FlowImg>& imgs,
     run.vote_every = run.ntiles <= 64 ? 1 : 4;
     int rc;
     // (A cooperative launch keeps such kernels apart too, at 18 us a call.)
-    // An image waits for room no longer than it would take in rounds, which
-    // need none (512x512 crests 3 ms, 128x128 blobs 0.25).
+    // An image waits without seeing room given back no longer than it would
+    // take in rounds, which need none (512x512 crests 2.3 ms, 128x128 blobs
+    // 0.23; the bound is 2.9 and 0.46).
     int64_t pixels = 0;
     for (const thin::FlowImg& f : imgs) pixels += (int64_t)f.h * f.w;
     if ((rc = come_to_kernel(ctx))) return rc;
@@ -1491,6 +1493,24 @@ int run_worklist(thin_ctx* ctx, const thin_image* ims, const std::vector<int>& w
     return limited ? fail(ctx, THIN_ELIMIT, "max_passes reached before stability") : THIN_OK;
 }
 
+// `work` of ims on the tiled engine: in one launch where the small-image engine
+// takes them, else in rounds.
+int run_auto(thin_ctx* ctx, const thin_image* ims, std::vector<int> work, thin_stats* stats)
+{
+    const int flow = choose_flow(ctx, ims, work, kFlowWaves);
+    std::vector<int> rest;
+    if (flow >= 0) {
+        const int rc = run_flow(ctx, flow, ims, work, stats, rest);
+        if (rc == THIN_OK && rest.empty()) return rc;
+        // Over the scratch cap (its exchange words take more than a twin): the
+        // rounds of launches.  Images it gave up on or found no room for stay
+        // there: what kept its blocks from running together would do so again.
+        if (rc != THIN_OK && rc != THIN_ENOMEM) return rc;
+        if (rc == THIN_OK) work = rest;
+    }
+    return run_tiled(ctx, ims, work, stats, rest.empty());
+}
+
 int run_images(thin_ctx* ctx, const thin_image* ims, int n, thin_stats* stats)
 {
     if (!ctx) return THIN_EINVAL;
@@ -1512,18 +1532,7 @@ int run_images(thin_ctx* ctx, const thin_image* ims, int n, thin_stats* stats)
     if (ctx->engine == THIN_ENGINE_STEP) return run_step_engine(ctx, ims, work, stats);
     if (ctx->engine == THIN_ENGINE_WORKLIST) return run_worklist(ctx, ims, work, stats);
     if (ctx->engine == THIN_ENGINE_COOP) return run_coop(ctx, ims, work, stats);
-    const int flow = choose_flow(ctx, ims, work, kFlowWaves);
-    std::vector<int> rest;
-    if (flow >= 0) {
-        const int rc = run_flow(ctx, flow, ims, work, stats, rest);
-        if (rc == THIN_OK && rest.empty()) return rc;
-        // Over the scratch cap (its exchange words take more than a twin): the
-        // rounds of launches.  Images it gave up on or found no room for stay
-        // there: what kept its blocks from running together would do so again.
-        if (rc != THIN_OK && rc != THIN_ENOMEM) return rc;
-        if (rc == THIN_OK) work = rest;
-    }
-    return run_tiled(ctx, ims, work, stats, rest.empty());
+    return run_auto(ctx, ims, std::move(work), stats);
 }
 
 // One tiled run over `work` (of size class cls) of ims, as a call with `shape`
@@ -1605,12 +1614,12 @@ int autotune(thin_ctx* ctx, const thin_image* imgs, int n, int reps, thin_tune_r
         const int rc = restore();
         return rc ? rc : timed_run(ctx, work_img.data(), work, cls, shape, ms);
     };
-    // a call as it is without tuning, the small-image engine included
+    // a call on the tiled engine without tuning, the small-image engine included
     auto run_untuned = [&](double& ms) -> int {
         int rc = restore();
         if (rc) return rc;
         const auto t0 = std::chrono::steady_clock::now();
-        rc = run_images(ctx, work_img.data(), (int)work_img.size(), nullptr);
+        rc = run_auto(ctx, work_img.data(), work, nullptr);
         ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
         return rc == THIN_ELIMIT ? THIN_OK : rc;
     };

@@ -184,3 +184,14 @@ def test_tuning_times_shapes_as_they_run(monkeypatch):
             n[rounds] = int(ctx.profile().launches)
     print(n, flush=True)
     assert n[False] < 0.7 * n[True]
+
+
+@pytest.mark.parametrize("engine", [thin.THIN_ENGINE_STEP, thin.THIN_ENGINE_WORKLIST,
+                                    thin.THIN_ENGINE_COOP], ids=["step", "worklist", "coop"])
+def test_tuning_in_contexts_of_other_engines(engine):
+    """Tuning is the tiled engine's whatever engine the context runs: also on an
+    image longer than the work-list engine takes."""
+    t = torch.from_numpy(image(3, 131080, 8, np.uint8)).cuda()
+    print("case tuning in another engine's context", engine, flush=True)
+    with thin.Context(engine=engine) as ctx:
+        assert ctx.autotune([t], [5], [0], reps=1)["candidates"] > 40

@@ -537,7 +537,7 @@ hipError_t launch_gradient(hipStream_t stream, const void* src, int64_t src_pitc
     }
     if (e != hipSuccess) return e;
     const float top = dst_dtype == 1 ? 255.0f : 65535.0f;
-    const int per_r = rows_per_block(h, w, num);
+    const int per_r = rows_per_block(h, w, num, halves);
     if (per_r > 0) {
         if (dst_dtype == 1)
             return halves ? launch_rows_lds<uint8_t, true>(stream, cols, h, w, per_r, plane, dst,

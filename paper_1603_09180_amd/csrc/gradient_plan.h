@@ -29,9 +29,7 @@ constexpr I column_floats(I h)
 
 // Lines a block takes: as many blocks as compute units, or `waves` times that
 // many where LDS holds no more lines (0: even that leaves lines over, and the
-// passes from global memory, which run every line at once, are faster: at 4000
-// x 3000 six waves of column blocks and six of row blocks took 849 us, those
-// 493).
+// passes from global memory run every line at once).
 inline int lines_per_block(int64_t lines, int64_t floats, int64_t num_cus, int64_t waves)
 {
     const int64_t fit = (int64_t)(kLdsBytes / sizeof(float)) / floats;
@@ -41,14 +39,25 @@ inline int lines_per_block(int64_t lines, int64_t floats, int64_t num_cus, int64
     return (int)(want < most ? want : most);
 }
 
-// The column pass's and the row pass's lines per block.
+// Columns: one wave of blocks (1601x1536 in LDS 114 us a call, from global
+// memory 183; a second wave gives it back, and the rows lose the sum that the
+// LDS pass forms for them).
 inline int columns_per_block(int64_t h, int64_t w, int64_t num_cus)
 {
     return lines_per_block(w, column_floats<int64_t>(h), num_cus, 1);
 }
-inline int rows_per_block(int64_t h, int64_t w, int64_t num_cus)
+
+// Rows: one wave (1792x1283 161 us, from global memory 192), and where a block
+// holds four lines or fewer, so that a line's chain is longer than 2000 samples,
+// two (512x5080 151 us and 259; 1024x5080 280 and 299, the third wave 414 and
+// 353; shorter lines lose with the second: 1551x1600 192 and 185, 3878x640 302
+// and 274).  After LDS columns (halves not set) the rows are short or few, and
+// LDS is the faster up to all the waves there are (8192x150 189 us and 198).
+inline int rows_per_block(int64_t h, int64_t w, int64_t num_cus, bool halves)
 {
-    return lines_per_block(h, 4 * chain_floats<int64_t>(w), num_cus, 3);
+    const int64_t floats = 4 * chain_floats<int64_t>(w);
+    const bool long_lines = 5 * floats * (int64_t)sizeof(float) > (int64_t)kLdsBytes;
+    return lines_per_block(h, floats, num_cus, !halves ? 3 : long_lines ? 2 : 1);
 }
 
 }  // namespace thin

@@ -44,18 +44,22 @@ def test_gradient_lines_per_block(tmp_path):
     lib = compiled(tmp_path, "gradient_plan", """
 #include "gradient_plan.h"
 extern "C" int cols(int h, int w, int cus) { return thin::columns_per_block(h, w, cus); }
-extern "C" int rows(int h, int w, int cus) { return thin::rows_per_block(h, w, cus); }
+extern "C" int rows(int h, int w, int cus, int halves) { return thin::rows_per_block(h, w, cus, halves != 0); }
 """)
     fits = 0
     for long in SIDES:
         for short in (1, 3, 255, 256, 257, 768, 769, 4096):
             for cus in (1, 32, 256):
                 want_c = lines_per_block(short, 4 * chain_floats(long) + 4, cus, 1)
-                want_r = lines_per_block(short, 4 * chain_floats(long), cus, 3)
+                floats = 4 * chain_floats(long)
+                few = (160 * 1024 - 1024) // 4 // floats <= 4
+                want_r = lines_per_block(short, floats, cus, 2 if few else 1)
+                sums_r = lines_per_block(short, floats, cus, 3)
                 assert lib.cols(long, short, cus) == want_c, (long, short, cus)
-                assert lib.rows(short, long, cus) == want_r, (long, short, cus)
+                assert lib.rows(short, long, cus, 1) == want_r, (long, short, cus)
+                assert lib.rows(short, long, cus, 0) == sums_r, (long, short, cus)
                 if 4 * 4 * long > 160 * 1024:
-                    assert want_c == want_r == 0
+                    assert want_c == want_r == sums_r == 0
                 fits += want_c > 0
     assert fits > 50
 

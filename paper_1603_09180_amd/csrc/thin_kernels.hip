@@ -425,12 +425,13 @@ __device__ __forceinline__ void store_partial(P* p, uint2 v, int n)
 }
 
 // Region rows [0, RH) x columns [0, RW) of src, origin (ry0, rx0), into
-// s_img (u16, row pitch RWP); zeros outside the image.
-template <typename P, int RH, int RW, int RWP, int NT>
+// s_img (u16, row pitch RWP) at (y + OFF, x + OFF), OFF 0 or 1; zeros outside
+// the image.
+template <typename P, int RH, int RW, int RWP, int OFF, int NT>
 __device__ __forceinline__ void stage_wide(const View& d, const P* src, int ry0, int rx0,
                                            uint16_t* s_img, int tid)
 {
-    static_assert(RW % 4 == 0 && RWP % 4 == 0, "groups of 4 pixels");
+    static_assert(RW % 4 == 0 && RWP % (OFF ? 2 : 4) == 0 && OFF <= 1, "groups of 4 pixels");
     constexpr int GW = RW / 4, NG = RH * GW;
     constexpr int ITER = (NG + NT - 1) / NT;
     constexpr int CH = ITER < STAGE_CHUNK ? ITER : STAGE_CHUNK;
@@ -453,7 +454,14 @@ __device__ __forceinline__ void stage_wide(const View& d, const P* src, int ry0,
             const int g = tid + (k0 + c) * NT;
             if (g < NG) {
                 const int y = g / GW, x = 4 * (g - (g / GW) * GW);
-                *reinterpret_cast<uint2*>(s_img + y * RWP + x) = v[c];
+                uint16_t* p = s_img + (y + OFF) * RWP + x + OFF;
+                if constexpr (OFF == 0) {
+                    *reinterpret_cast<uint2*>(p) = v[c];
+                } else {  // p + 1 is at a word
+                    p[0] = (uint16_t)v[c].x;
+                    *reinterpret_cast<uint32_t*>(p + 1) = __builtin_amdgcn_alignbyte(v[c].y, v[c].x, 2);
+                    p[3] = (uint16_t)(v[c].y >> 16);
+                }
             }
         }
     }
@@ -511,19 +519,19 @@ __device__ __forceinline__ void stage_scalar(const View& d, const void* src, int
 }
 
 // Staging with groups of 4 pixels where the buffers allow it.
-template <int RH, int RW, int RWP, int NT>
+template <int RH, int RW, int RWP, int OFF, int NT>
 __device__ __forceinline__ void stage_region(const View& d, const void* src, const void* dst,
                                              int ry0, int rx0, uint16_t* s_img, int tid)
 {
     if (wide_ok(d, src, dst)) {
         if (d.dtype == 1)
-            stage_wide<uint8_t, RH, RW, RWP, NT>(d, static_cast<const uint8_t*>(src), ry0, rx0,
-                                                 s_img, tid);
+            stage_wide<uint8_t, RH, RW, RWP, OFF, NT>(d, static_cast<const uint8_t*>(src), ry0, rx0,
+                                                      s_img, tid);
         else
-            stage_wide<uint16_t, RH, RW, RWP, NT>(d, static_cast<const uint16_t*>(src), ry0, rx0,
-                                                  s_img, tid);
+            stage_wide<uint16_t, RH, RW, RWP, OFF, NT>(d, static_cast<const uint16_t*>(src), ry0,
+                                                       rx0, s_img, tid);
     } else {
-        stage_scalar<RH, RW, RWP, 0, 0, NT>(d, src, ry0, rx0, s_img, tid);
+        stage_scalar<RH, RW, RWP, OFF, OFF, NT>(d, src, ry0, rx0, s_img, tid);
     }
 }
 
@@ -763,7 +771,7 @@ struct Tile {
     static __device__ __forceinline__ void stage(const View& d, int gy0, int gx0, const void* src,
                                                  const void* dst, uint16_t* s_img, int tid)
     {
-        stage_region<RH, RW, RWP, NT>(d, src, dst, gy0 - K, gx0 - K, s_img, tid);
+        stage_region<RH, RW, RWP, 0, NT>(d, src, dst, gy0 - K, gx0 - K, s_img, tid);
     }
 
     // Interior of the staged tile to dst.
@@ -981,6 +989,7 @@ struct RTile {
     static_assert(TH % 2 == 0 && TW % 2 == 0, "tile sides must be even");
     static_assert(RH / 2 <= 254 && RW / 2 <= 254, "step limits are bytes");
     static_assert(LAT_W <= 64 && NT % 64 == 0, "a lattice row lies in one wave");
+    static_assert(TW % 4 == 0, "staged in groups of 4 pixels");
 
     // The lattice cell of a thread's k-th slot; false when it has none.
     static __device__ __forceinline__ bool cell(int tid, int k, int& a, int& b)
@@ -1042,10 +1051,9 @@ struct RTile {
         return s_bits;
     }
 
-    // Tile and halo from src into s_img, spare rows and columns zeroed (they
-    // are read into windows but never used by a candidate); no barrier.
-    static __device__ __forceinline__ void stage(const View& d, int gy0, int gx0, const void* src,
-                                                 const void*, uint16_t* s_img, int tid)
+    // Spare rows and columns zeroed (they are read into windows but never used
+    // by a candidate).
+    static __device__ __forceinline__ void clear_rim(uint16_t* s_img, int tid)
     {
         for (int i = tid; i < 2 * RWP + 2 * RH; i += NT) {
             int o;
@@ -1055,6 +1063,24 @@ struct RTile {
             else o = (i - 2 * RWP - RH + 1) * RWP + RWP - 1;
             s_img[o] = 0;
         }
+    }
+
+    // Tile and halo from src into s_img (no barrier), in groups of 4 pixels
+    // where the buffers allow it: a quiet tile costs its staging (serving one
+    // 4000x4001 image 1.50 ms, pixel by pixel 1.79).
+    static __device__ __forceinline__ void stage(const View& d, int gy0, int gx0, const void* src,
+                                                 const void* dst, uint16_t* s_img, int tid)
+    {
+        clear_rim(s_img, tid);
+        stage_region<RH, RW, RWP, 1, NT>(d, src, dst, gy0 - K, gx0 - K, s_img, tid);
+    }
+
+    // The same pixel by pixel, for a kernel that stages a tile once and keeps it
+    // (the groups cost k_flow 4 registers: 96 mixed images 1.972 ms, 1.960 so).
+    static __device__ __forceinline__ void stage_once(const View& d, int gy0, int gx0,
+                                                      const void* src, uint16_t* s_img, int tid)
+    {
+        clear_rim(s_img, tid);
         stage_scalar<RH, RW, RWP, 1, 1, NT>(d, src, gy0 - K, gx0 - K, s_img, tid);
     }
 
@@ -2234,7 +2260,7 @@ __global__ __launch_bounds__(NT, flow_waves_per_eu(NT, TH)) void k_flow(const Fl
             s_exam = 0ull;
         }
         if (tid < T::DIRTY_ELEMS / 4) reinterpret_cast<uint32_t*>(s_flags)[tid] = 0u;
-        T::stage(d, gy0, gx0, im.image, im.image, s_img, tid);
+        T::stage_once(d, gy0, gx0, im.image, s_img, tid);
         __syncthreads();
         typename T::Cells q;
         T::open(q, d, gy0, gx0, s_img, tid);

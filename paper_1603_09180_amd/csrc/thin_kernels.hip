@@ -2142,7 +2142,7 @@ void k_coop(const ImgDev* __restrict__ imgs, ImgCnt* cnt,
 //
 // A round of launches costs about 7500 cycles between launches, 6000 to stage
 // a tile and 4000 to set it up and store it, beside some 20000 for 16 steps
-// (512x512 ridges, 140 rounds: 2.25 ms).  Here an exchange costs about 4000
+// (512x512 ridges, 140 rounds: 2.16 ms).  Here an exchange costs about 4000
 // (one trip to memory and back, the region's windows compared), which lets a
 // round have 8 steps and a region two thirds the size: 12000 cycles a round,
 // 1.37 ms.  What bounds it now is the steps' chain of latencies (930 cycles a

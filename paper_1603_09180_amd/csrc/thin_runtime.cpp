@@ -470,14 +470,14 @@ TileShape choose_shape(const thin_ctx* ctx, int64_t total_pixels, int64_t images
     // Small work lists are bound by the latency of each round: small tiles
     // with one cell per thread and register windows, which start with every
     // candidate pending: seeds from change bitmaps cost more to read than the
-    // first steps take (seeded, in ms: 512x512 crests 2.48 against 2.25 without,
-    // 1000x1000 crests 8.98 and 8.14, 128x128 blobs 0.242 and 0.228, 16 of them
-    // 0.43 and 0.39), and the bitmaps take scratch.  Large ones are bound by
+    // first steps take (seeded, in ms: 512x512 crests 2.37 against 2.16 without,
+    // 1000x1000 crests 8.40 and 7.70, 128x128 blobs 0.226 and 0.212, 16 of them
+    // 0.40 and 0.37), and the bitmaps take scratch.  Large ones are bound by
     // throughput: dense per-step work lists with seeded flags in 128x128
     // tiles (less halo work per pixel).  Between, it is the content that
-    // decides (1400x1500 crests 10.4 ms in 32x32 tiles, 12.5 in 128x128;
-    // 2048x2048 blobs 650 us and 517; 1000x1000 crests 8.1 ms and 8.7, blobs 450
-    // us and 500), so the line stays where only a few hundred of the small
+    // decides (1400x1500 crests 10.1 ms in 32x32 tiles, 12.5 in 128x128;
+    // 2048x2048 blobs 640 us and 531; 1000x1000 crests 7.7 ms and 8.7, blobs 427
+    // us and 510), so the line stays where only a few hundred of the small
     // tiles are left to a launch.
     (void)images;
     if (total_pixels <= (int64_t)1 << 20) return TileShape{32, 32, 16, 1024, thin::kVarRegs};
@@ -1087,8 +1087,8 @@ int drive_flow(thin_ctx* ctx, int which, const std::vector<thin::FlowImg>& imgs,
     int rc;
     // (A cooperative launch keeps such kernels apart too, at 18 us a call.)
     // An image waits without seeing room given back no longer than it would
-    // take in rounds, which need none (512x512 crests 2.3 ms, 128x128 blobs
-    // 0.23; the bound is 2.9 and 0.46).
+    // take in rounds, which need none (512x512 crests 2.2 ms, 128x128 blobs
+    // 0.21; the bound is 2.9 and 0.46).
     int64_t pixels = 0;
     for (const thin::FlowImg& f : imgs) pixels += (int64_t)f.h * f.w;
     if ((rc = come_to_kernel(ctx))) return rc;
@@ -2112,7 +2112,7 @@ int thin_serve_admit(thin_ctx* ctx, const thin_image* img, uint64_t tag)
     if (!ctx->serve_ready) {
         // Latency first: register windows in 64x64 tiles.  Measured on 2000
         // requests a second of sides 64..4096 (p50, p99, capacity): register
-        // windows 0.76 ms, 2.6 ms, 7017 images/s; per-pixel flags (512
+        // windows 0.67 ms, 2.4 ms, 7095 images/s; per-pixel flags (512
         // threads) 1.02, 3.0, 7006; bit flags with dense lists 1.56, 3.4,
         // 8339 (256 threads), 128x128 tiles 1.98, 4.0, 8752.
         TileShape shape = ctx->forced.th ? ctx->forced : TileShape{64, 64, 16, 1024, thin::kVarRegs};

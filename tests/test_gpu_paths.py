@@ -155,8 +155,8 @@ def test_tuning_without_the_engine_keeps_its_record(kw, tmp_path):
 
 def test_tuning_times_the_untuned_call():
     """default_ms is a call of the context without tuning: for small crests one
-    launch of the engine (1.37 ms, the best shape's rounds 2.2), and with the
-    engine kept out a run in rounds (2.46)."""
+    launch of the engine (1.37 ms), and with the engine kept out a run in rounds
+    (2.2, as the best shape)."""
     t = torch.from_numpy(synth.ridges_512().image()).cuda()
     print("case tuning, untuned call", flush=True)
     with thin.Context() as ctx:

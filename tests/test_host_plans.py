@@ -158,7 +158,7 @@ def test_room_is_waited_for_while_it_is_given_back(room):
     back for its patience, counted anew each time some has; one that waits
     behind it then has its turn."""
     first = room.enter(62, 0, 64, 2048)
-    big = room.patient(62, 1, 242, 512, 600_000)
+    big = room.patient(62, 1, 242, 512, 3_000_000)
     for _ in range(8):
         i = room.enter(62, 2, 8, 512)
         assert (room.inside(i, 1), room.inside(big, 0)) == (1, 0)
